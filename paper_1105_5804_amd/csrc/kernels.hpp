@@ -8,9 +8,11 @@
 //             with tile labeling (Sec. II.B): each lane of a 64-lane wave owns
 //             two sites of a tile row; the row's bonds become 128-bit masks by
 //             wave ballots, right bonds turn into row runs (each site's run
-//             start from a DPP max-scan over the lanes), and down bonds join
-//             runs by a lock-free union-find over run starts in LDS, fed from
-//             compacted per-wave lists of vertical contacts.
+//             start from a DPP max-scan over the lanes), each run takes the
+//             label of one run above it as its wave goes down its rows, and the
+//             down bonds left over (a run touching several labels, or another
+//             wave's rows) join labels by a lock-free union-find in LDS, fed
+//             from compacted per-wave lists.
 //             Clusters that touch the tile border are claimed by their border
 //             sites and get a compact boundary id; every site's result is a
 //             16-bit code (boundary id, or CAP + the slot of its interior root).
@@ -303,9 +305,9 @@ struct TileSmem {
     static constexpr int TH = TH_, TSITES = TW * TH, NWAVE = TH / RPW;
     static constexpr int TL = MODE == M_SITES ? (TH < 64 ? TLIST - 16 : TLIST - 8) : TLIST;
     int P[TSITES];                     // union-find parent per site slot, as 4 x slot
-    EO Rm[TH];                         // in-tile right bonds per row
+    EO Lm[TH];                         // label sites per row (their own parents before the unions)
     EO Om[MODE == M_SITES ? TH : 1];   // occupied sites per row (images)
-    uint16_t wl[NWAVE][TL];            // per-wave work list (contacts, then run starts)
+    uint16_t wl[NWAVE][TL];            // per-wave work list (contacts, then linked labels)
     unsigned long long xr_w[NWAVE];    // right crossing bonds of each wave's rows (bit ly % 64)
     EO xd_s;                           // bottom crossing bonds
     int nb_s;
@@ -358,7 +360,7 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
     constexpr bool NEED_HALO = MODE == M_SW || MODE == M_SITES;  // column right of the tile
     constexpr int TL = TileSmem<MODE, TH_>::TL;
     int *P = sm.P;
-    EO *Rm = sm.Rm;
+    EO *Lm = sm.Lm;
     EO *Om = sm.Om;
     auto &wl = sm.wl;
     unsigned long long *xr_w = sm.xr_w;
@@ -432,14 +434,20 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         }
     }
 
-    // ---- A1: bonds as lane masks, row masks, run-start parents, and the
-    // vertical contacts of the previous row pair.  Site s repeats the contact
-    // of s-1 when s-1 has a down bond and both rows continue from s-1 to s:
-    // one union per contact segment suffices.
+    // ---- A1: bonds as lane masks, then row by row the sites' labels: a run
+    // takes the label of one run above it (one of its contacts), or its own
+    // start without a contact.  Most contacts are the only one of their run
+    // (at a critical point about 50 of a row's 128 sites have one, about 10
+    // are left to unite), so this leaves a fifth of the unions, each four
+    // dependent LDS reads and an atomic a step, and as few entries to
+    // compress: a labeled run start already points at its label.  Sweep of
+    // the q = 3 lattice 16384^2, every contact united -> labels passed down:
+    // 1.173 -> 1.026 ms; labeling of 16384^2 random bonds 1.251 -> 1.061 ms.
     unsigned long long xr = 0;
     int nact = 0;  // at most 2 * TSITES
     int ncon = 0;
-    EO prevR = EO{0ull, 0ull}, prevD = EO{0ull, 0ull};
+    int lab0 = 0, lab1 = 0;  // labels of the lane's sites in the previous row
+    EO prevD = EO{0ull, 0ull};
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         if (r >= nr) break;
@@ -544,7 +552,6 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         const EO D = last ? EO{0ull, 0ull} : EO{mD0, mD1};
         if (lane_r == 0) {
             if (last) xd_s = EO{mD0, mD1};
-            Rm[ly] = R;
             if constexpr (MODE == M_SITES) Om[ly] = EO{O0, O1};
         }
         const int base = ly * TW;
@@ -558,18 +565,35 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         const int below4 = wave_max_below(o_start ? x4 + 8 : (e_start ? x4 + 4 : 0));
         const int rs0 = e_start ? x4 : below4 - 4;
         const int rs1 = o_start ? x4 + 4 : rs0;
-        *reinterpret_cast<int2 *>(&P[base + lx0]) = make_int2(4 * base + rs0, 4 * base + rs1);
+        const int own = 4 * base + x4;  // the even site's own entry
+        int n0 = 4 * base + rs0, n1 = 4 * base + rs1;
+        *reinterpret_cast<int2 *>(&P[base + lx0]) = make_int2(n0, n1);
         if (r > 0) {
-            // contacts between this wave's own rows: a full list is united at
-            // once (only rows this wave has initialised are involved)
+            // every contact offers its upper site's label to the lower run's
+            // start (one wave's LDS operations run in order; whichever offer
+            // lands last stands); a contact whose label lost needs a union
+            wave_lds_fence();
+            if (lane_bit(prevD.e, lane)) lds_st(lds_entry<true>(P, n0), lab0);
+            if (lane_bit(prevD.o, lane)) lds_st(lds_entry<true>(P, n1), lab1);
+            wave_lds_fence();
+            n0 = lds_ld(lds_entry<true>(P, n0));
+            n1 = lds_ld(lds_entry<true>(P, n1));
+            *reinterpret_cast<int2 *>(&P[base + lx0]) = make_int2(n0, n1);
+            const EO lost = EO{lanes_ne(static_cast<uint32_t>(n0), static_cast<uint32_t>(lab0)) & prevD.e,
+                               lanes_ne(static_cast<uint32_t>(n1), static_cast<uint32_t>(lab1)) & prevD.o};
+            // a full list is united at once (only rows this wave has
+            // initialised are involved)
             if (ncon > TL - TW) {
                 unite_list(ncon);
                 ncon = 0;
             }
-            const EO X = eo_and(eo_and(prevD, prevR), R);
-            eo_append<2>(mylist, ncon, eo_andnot(prevD, eo_shift1(X)), lane, base - TW);
+            eo_append<2>(mylist, ncon, lost, lane, base - TW);
         }
-        prevR = R;
+        const EO labels = EO{lanes_eq(static_cast<uint32_t>(n0), static_cast<uint32_t>(own)),
+                             lanes_eq(static_cast<uint32_t>(n1), static_cast<uint32_t>(own + 4))};
+        if (lane_r == 0) Lm[ly] = labels;
+        lab0 = n0;
+        lab1 = n1;
         prevD = D;
     }
     if (lane == 0) {
@@ -584,9 +608,7 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
             unite_list(ncon);
             ncon = 0;
         }
-        const EO Rn = uniform_eo(Rm[ly0 + nr]);
-        const EO X = eo_and(eo_and(prevD, prevR), Rn);
-        eo_append<2>(mylist, ncon, eo_andnot(prevD, eo_shift1(X)), lane, (ly0 + nr - 1) * TW);
+        eo_append<2>(mylist, ncon, prevD, lane, (ly0 + nr - 1) * TW);
     }
     unite_list(ncon);
     __syncthreads();
@@ -604,15 +626,15 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
     };
 
     // ---- C: the clusters that touch the tile border are claimed (one
-    // thread per border position), then, after a barrier, every linked run
-    // start gets its cluster's final code, stored in its own entry as
+    // thread per border position), then, after a barrier, every linked label
+    // gets its cluster's final code, stored in its own entry as
     // -(code + 2): the boundary id of a claimed root, else CAP + the root's
     // slot (a claimed root's entry already reads -(id + 2)).  Lane L walks
-    // run starts L, L+64, ... of the wave's list up to the first entry that is
-    // negative (a claimed root, or a run start another lane has finished:
+    // labels L, L+64, ... of the wave's list up to the first entry that is
+    // negative (a claimed root, or a label another lane has finished:
     // either way the cluster's code) or its own (an unclaimed root); a lane
-    // whose walk is done takes its next run start at once.  Only linked run
-    // starts (entry neither their own nor negative) are listed.
+    // whose walk is done takes its next label at once.  Only linked labels
+    // (entry neither their own nor negative) are listed.
     auto compress_list = [&](int n) {
         wave_lds_fence();
         int i = lane, s0 = 0, x = 0;
@@ -654,7 +676,7 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
     __syncthreads();
     int nrs = 0;
     // The entries of the wave's sites are read up front (the loads overlap);
-    // a flush of the list only rewrites linked run starts of this wave.
+    // a flush of the list only rewrites linked labels of this wave.
     int2 ppr[RPW];
 #pragma unroll
     for (int r = 0; r < RPW; ++r)
@@ -668,23 +690,21 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
             compress_list(nrs);
             nrs = 0;
         }
-        const EO R = uniform_eo(Rm[ly]);
-        EO O = valid;
-        if constexpr (MODE == M_SITES) O = uniform_eo(Om[ly]);
+        const EO L = uniform_eo(Lm[ly]);
         const int2 pp = ppr[r];
         const EO linked = EO{lanes_ne(static_cast<uint32_t>(pp.x), static_cast<uint32_t>(4 * (base + lx0))) &
                                  lanes_lt(static_cast<uint32_t>(pp.x), 0x80000000u),
                              lanes_ne(static_cast<uint32_t>(pp.y), static_cast<uint32_t>(4 * (base + lx0 + 1))) &
                                  lanes_lt(static_cast<uint32_t>(pp.y), 0x80000000u)};
-        eo_append<2>(mylist, nrs, eo_and(eo_andnot(O, eo_shift1(R)), linked), lane, base);
+        eo_append<2>(mylist, nrs, eo_and(L, linked), lane, base);
     }
     compress_list(nrs);
     __syncthreads();
 
     // ---- E: per-site codes (boundary id of a claimed root, else CAP + the
     // root's slot), edge ids, crossing bits.  A site's code is one step past
-    // its entry: a run start holds its code (or, an unclaimed root, its own
-    // offset), any other site its run start's offset.
+    // its entry: a label site holds its code (or, an unclaimed root, its own
+    // offset), any other site its label's offset.
     auto code_of = [&](int x, int p) {  // x a slot, p = P[x] (byte offsets)
         x *= 4;
         if (p >= 0 && p != x) p = *lds_entry<true>(P, p);

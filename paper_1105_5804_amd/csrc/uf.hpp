@@ -76,7 +76,7 @@ __device__ __forceinline__ void unite_step(int *P, int &a, int &b, int &done)
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
     // with SAME_PARENT a common parent already makes one tree: the union ends
     // a step before both nodes reach the root (whose entry every finished
-    // lane would hit; the run-start unions of the tile kernel gain from it,
+    // lane would hit; the label unions of the tile kernel gain from it,
     // the site unions of the small-lattice kernel do not)
     // bitwise, not short-circuit: the flags stay lane masks (no selects)
     done = static_cast<int>((SAME_PARENT && pa == pb) | (roots & (!link | (old == hi))));

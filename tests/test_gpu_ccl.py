@@ -87,6 +87,26 @@ def test_structured_inputs():
     _check(spiral, "bonds_open")
 
 
+@pytest.mark.parametrize("W,H,tile_h", [(126, 15, 16), (127, 16, 16), (128, 17, 0), (129, 64, 0), (257, 65, 0),
+                                        (384, 129, 128)])
+def test_many_contacts(W, H, tile_h):
+    """Rows whose runs meet every label above them: long runs under single
+    sites (each contact another label, filling the waves' union lists), single
+    sites under long runs, and random rows of both kinds."""
+    y = np.arange(H)
+    g = wl.rng(7100 + W + H)
+    for rows in (y % 2 == 0, y % 2 == 1, y % 9 == 3, g.random(H) < 0.5):
+        right = np.where(rows[:, None], g.random((H, W)) < 0.97, g.random((H, W)) < 0.03)
+        down = g.random((H, W)) < 0.9
+        bonds = (right.astype(np.uint8) | (down.astype(np.uint8) << 1)).astype(np.uint8)
+        _check(bonds, "bonds_open", tile_h=tile_h)
+        _check(bonds, "bonds_periodic", tile_h=tile_h)
+    teeth = np.zeros((H, W), np.uint8)  # combs: separate columns joined only at their foot
+    teeth[:, ::2] = 1
+    teeth[7::8, :] = 1
+    _check(teeth, "sites_open", tile_h=tile_h)
+
+
 def test_percolation_16384():
     """Full-size labeling pass: bond percolation at p = 1/2, L = 16384."""
     L = 16384
