@@ -15,7 +15,7 @@
 //             from compacted per-wave lists.
 //             Clusters that touch the tile border are claimed by their border
 //             sites and get a compact boundary id; every site's result is a
-//             16-bit code (boundary id, or CAP + the slot of its interior root).
+//             16-bit code (the slot of its interior root, or TSITES + boundary id).
 //   k_merge   tile consolidation (Sec. II.C) in one pass: every active bond
 //             that crosses a tile edge, the periodic wrap included, unites two
 //             boundary ids in a global union-find over the compact id space
@@ -200,9 +200,7 @@ struct EO {
     uint64_t e, o;
 };
 
-__device__ __forceinline__ EO eo_and(EO a, EO b) { return EO{a.e & b.e, a.o & b.o}; }
 __device__ __forceinline__ EO eo_andnot(EO a, EO b) { return EO{a.e & ~b.e, a.o & ~b.o}; }
-__device__ __forceinline__ EO eo_shift1(EO m) { return EO{m.o << 1, m.e}; }
 
 // Set bits of m at lanes below the calling lane.
 __device__ __forceinline__ int lanes_below(uint64_t m)
@@ -211,16 +209,22 @@ __device__ __forceinline__ int lanes_below(uint64_t m)
                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
 }
 
-// Append the sites set in m (row starting at slot `base`) to a wave list in
-// ascending order, as slot << SH; n is the wave-uniform list length.
-template <int SH = 0>
-__device__ __forceinline__ void eo_append(uint16_t *list, int &n, EO m, int lane, int base)
+// Append the calling lanes' entries to a wave list: ve for the lanes of m.e,
+// then vo for those of m.o (the order does not matter); n is the wave-uniform
+// list length.
+__device__ __forceinline__ void eo_append(uint16_t *list, int &n, EO m, int ve, int vo)
 {
-    const int r0 = n + lanes_below(m.e) + lanes_below(m.o);
-    const int b0 = lane_bit(m.e, lane) ? 1 : 0;
-    if (b0) list[r0] = static_cast<uint16_t>((base + 2 * lane) << SH);
-    if (lane_bit(m.o, lane)) list[r0 + b0] = static_cast<uint16_t>((base + 2 * lane + 1) << SH);
-    n += __popcll(m.e) + __popcll(m.o);
+    const auto at = [](uint64_t mask, int from) {
+        return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask),
+                                                                                    static_cast<uint32_t>(from))));
+    };
+    const int pe = at(m.e, n);
+    n += __popcll(m.e);
+    const int po = at(m.o, n);
+    n += __popcll(m.o);
+    if (lane_bit(m.e, 0)) list[pe] = static_cast<uint16_t>(ve);
+    if (lane_bit(m.o, 0)) list[po] = static_cast<uint16_t>(vo);
 }
 
 // Wave-uniform copy of a mask read from LDS.
@@ -230,7 +234,6 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
     const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
-__device__ __forceinline__ EO uniform_eo(EO m) { return EO{uniform64(m.e), uniform64(m.o)}; }
 // A pointer the caller knows to be wave-uniform, as a scalar value.
 template <typename T>
 __device__ __forceinline__ T *uniform_ptr(T *p)
@@ -261,9 +264,14 @@ __device__ __forceinline__ int border_slot(int t, int tw, int th)
     return (t - 2 * TW - TH) < th ? (t - 2 * TW - TH) * TW + tw - 1 : -1;
 }
 
-// Claimed roots: P[root] = CLAIMING while the id is allocated, then
-// -(k + 2) for boundary id k.
+// A site's 16-bit code: the slot of its cluster's root inside the tile
+// (0 .. TSITES - 1), or TSITES + k for the cluster of boundary id k, or
+// CODE_BG.  Entries that are done hold FINAL | code << 2 (negative); the entry
+// of an unclaimed root, its own byte offset 4 slot, gives its code by the same
+// two-bit shift.  P[root] = CLAIMING while a root's id is allocated.
 constexpr int CLAIMING = -1;
+__device__ __forceinline__ int final_entry(uint32_t code) { return static_cast<int>(0x80000000u | (code << 2)); }
+__device__ __forceinline__ uint32_t entry_code(int e) { return (static_cast<uint32_t>(e) >> 2) & 0xFFFFu; }
 
 // Lane masks: bit L describes lane L (uicmp yields the mask of one compare).
 constexpr int CMP_EQ = 32, CMP_NE = 33, CMP_ULT = 36, CMP_ULE = 37;
@@ -298,17 +306,13 @@ __device__ __forceinline__ int wave_max_below(int v)
     return out;
 }
 
-// LDS of the tile phase.  The image mode's extra occupancy masks are paid
-// for by slightly shorter lists, so every mode stays under 40 KB per 64 rows.
+// LDS of the tile phase: under 40 KB per 64 rows.
 template <int MODE, int TH_>
 struct TileSmem {
     static constexpr int TH = TH_, TSITES = TW * TH, NWAVE = TH / RPW;
-    static constexpr int TL = MODE == M_SITES ? (TH < 64 ? TLIST - 16 : TLIST - 8) : TLIST;
-    int P[TSITES];                     // union-find parent per site slot, as 4 x slot
-    EO Lm[TH];                         // label sites per row (their own parents before the unions)
-    EO Om[MODE == M_SITES ? TH : 1];   // occupied sites per row (images)
-    uint16_t wl[NWAVE][TL];            // per-wave work list (contacts, then linked labels)
-    unsigned long long xr_w[NWAVE];    // right crossing bonds of each wave's rows (bit ly % 64)
+    int P[TSITES + 4];                 // union-find parent per site slot, as 4 x slot; P[TSITES]: background
+    uint16_t wl[NWAVE][TLIST];         // per-wave work list (contacts, then linked labels)
+    uint32_t xr_w[NWAVE];              // right crossing bonds of each wave's rows (bit r: its row r)
     EO xd_s;                           // bottom crossing bonds
     int nb_s;
     int act_w[NWAVE];
@@ -358,13 +362,10 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
     constexpr int NT = S::NT, NWAVE = S::NWAVE;
     constexpr bool NEED_DOWN = MODE == M_SW || MODE == M_SITES;  // bonds from two rows
     constexpr bool NEED_HALO = MODE == M_SW || MODE == M_SITES;  // column right of the tile
-    constexpr int TL = TileSmem<MODE, TH_>::TL;
+    constexpr int TL = TLIST;
+    constexpr int BG4 = 4 * TSITES;  // offset of the background entry
     int *P = sm.P;
-    EO *Lm = sm.Lm;
-    EO *Om = sm.Om;
     auto &wl = sm.wl;
-    unsigned long long *xr_w = sm.xr_w;
-    EO &xd_s = sm.xd_s;
     int &nb_s = sm.nb_s;
     int *act_w = sm.act_w;
     const int W = a.g.W, H = a.g.H;
@@ -406,14 +407,18 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         }
         wave_lds_fence();
     };
-    // wave-uniform lane masks
-    const EO valid = EO{lanes_lt(lx0, tw), lanes_lt(lx1, tw)};
+    // lane masks of the sites inside the tile, and of its last column
+    const uint64_t in0 = ~0ull >> (64 - ((tw + 1) >> 1)), in1 = in0 >> (tw & 1);
+    const uint64_t L0 = EVENW ? 0ull : in0 & ~in1, L1 = in1 & ~(in0 >> 1);
 
-    if (threadIdx.x == 0) nb_s = 0;  // first used after the barrier closing phase A
+    if (threadIdx.x == 0) {  // first used after the barrier closing phase A
+        nb_s = 0;
+        P[TSITES] = final_entry(CODE_BG);
+    }
 
     // ---- A0: issue every load of the wave's rows (and the row below) up front,
     // branch-free within the wave: invalid lanes read a clamped valid address.
-    // pr[r] holds the bytes of sites lx0 (bits 0-7) and lx1 (bits 8-15).
+    // pr[r] holds the bytes of sites lx0 (bits 0-7) and lx1 (bits 8 up).
     const int col = gx0 + (v0 ? lx0 : 0);
     uint32_t pr[RPW + 1];
     uint32_t hl[RPW];
@@ -433,6 +438,23 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
             if (NEED_HALO && r < nr) hl[r] = row[hx];  // same byte for every lane
         }
     }
+    if (tw < TW) {
+        // Sites past a ragged edge have no bonds: spins that differ from each
+        // other, from every byte on their right and from the row below
+        // (pr[r] bits 8 up exceed a byte); bond bytes and pixels 0.
+#pragma unroll
+        for (int r = 0; r <= RPW; ++r) {
+            const uint32_t no0 = MODE == M_SW ? (r & 1) : 0u, no1 = MODE == M_SW ? (0x102u + (r & 1)) << 8 : 0u;
+            pr[r] = v1 ? pr[r] : (v0 ? pr[r] & 0xFFu : no0) | no1;
+        }
+    }
+    if constexpr (MODE == M_SITES) {  // an open boundary: nothing below the last row
+        if (bottom_is_wrap) {
+#pragma unroll
+            for (int r = 1; r <= RPW; ++r)
+                if (ly0 + r == th) pr[r] = 0;
+        }
+    }
 
     // ---- A1: bonds as lane masks, then row by row the sites' labels: a run
     // takes the label of one run above it (one of its contacts), or its own
@@ -443,34 +465,35 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
     // compress: a labeled run start already points at its label.  Sweep of
     // the q = 3 lattice 16384^2, every contact united -> labels passed down:
     // 1.173 -> 1.026 ms; labeling of 16384^2 random bonds 1.251 -> 1.061 ms.
-    unsigned long long xr = 0;
+    // The labels stay in registers: the code pass reads one entry a site and
+    // packs it with a shift (codes are entries without their two low bits),
+    // and no table of run masks, label masks or occupied sites is kept in LDS.
+    // The kernel is bound by VALU issue (busy 0.95), so instructions count:
+    // with that and the masks of ragged edges folded into the loaded bytes,
+    // 185 VALU and 150 SALU a row became 143 and 111, and the same sweep
+    // 1.026 -> 0.867 ms, the labeling 1.061 -> 0.930 ms.
+    uint32_t xr = 0;
     int nact = 0;  // at most 2 * TSITES
     int ncon = 0;
-    int lab0 = 0, lab1 = 0;  // labels of the lane's sites in the previous row
+    int lab0[RPW], lab1[RPW];  // labels of the lane's sites (byte offsets), BG4 for background
     EO prevD = EO{0ull, 0ull};
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
-        if (r >= nr) break;
+        lab0[r] = lab1[r] = BG4;
+        if (r >= nr) continue;
         const int ly = ly0 + r;
         const int gy = gy0 + ly;
         const uint32_t cur = pr[r], dn = pr[r + 1];
-        // lane masks are recomputed per row (one compare each) instead of
-        // being held in scalar registers across the unrolled rows, where
-        // they would spill
-        uint32_t twr = static_cast<uint32_t>(tw);
-        int lane_r = lane;
-        asm volatile("" : "+s"(twr), "+v"(lane_r));
-        const uint64_t V0 = lanes_lt(lx0, twr), V1 = lanes_lt(lx1, twr);
-        const uint64_t L0 = lanes_eq(lx0, twr - 1), L1 = lanes_eq(lx1, twr - 1);
-        uint64_t mR0, mR1, mD0, mD1, O0 = V0, O1 = V1;
+        uint64_t mR0, mR1, mD0, mD1, O0 = ~0ull, O1 = ~0ull;
+        uint64_t cross;  // the last column's right bond, which leaves the tile
 
         if constexpr (MODE == M_SW) {
-            const uint32_t s0 = cur & 0xFFu, s1 = (cur >> 8) & 0xFFu;
-            const uint32_t d0 = dn & 0xFFu, d1 = (dn >> 8) & 0xFFu;
+            const uint32_t s0 = cur & 0xFFu, s1 = cur >> 8;
+            const uint32_t d0 = dn & 0xFFu, d1 = dn >> 8;
             const uint32_t nxt = from_next_lane(s0);
-            const uint32_t sr0 = (!EVENW && lx0 == static_cast<int>(twr) - 1) ? hl[r] : s1;
-            const uint32_t sr1 = (lx1 == static_cast<int>(twr) - 1) ? hl[r] : nxt;
-            const int64_t i0 = static_cast<int64_t>(gy) * W + gx0 + lx0;
+            const uint32_t sr0 = (!EVENW && lane_bit(L0, lane)) ? hl[r] : s1;
+            const uint32_t sr1 = lane_bit(L1, lane) ? hl[r] : nxt;
+            const uint32_t i0 = static_cast<uint32_t>(gy) * static_cast<uint32_t>(W) + static_cast<uint32_t>(gx0 + lx0);
             uint32_t r0R, r0D, r1R, r1D;
             // the key schedule is recomputed per row (scalar adds) rather than
             // held in 20 scalar registers across the unrolled row loop
@@ -478,9 +501,9 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
             asm volatile("" : "+s"(k0), "+s"(k1));
             U4 blk;
             if constexpr (RKEYS) {
-                blk = philox4x32_10_rk(static_cast<uint32_t>(i0 >> 1), a.t, TAG_BOND, a.sid, kernel_tile_args()->rk);
+                blk = philox4x32_10_rk(i0 >> 1, a.t, TAG_BOND, a.sid, kernel_tile_args()->rk);
             } else {
-                blk = philox4x32_10(static_cast<uint32_t>(i0 >> 1), a.t, TAG_BOND, a.sid, k0, k1);
+                blk = philox4x32_10(i0 >> 1, a.t, TAG_BOND, a.sid, k0, k1);
             }
             if (EVENW || (i0 & 1) == 0) {  // the pair (i0, i0+1) shares one block
                 r0R = blk.v0;
@@ -490,151 +513,153 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
             } else {  // odd row start (odd W): i0 is the second site of its block
                 r0R = blk.v2;
                 r0D = blk.v3;
-                const U4 b2 = philox4x32_10(static_cast<uint32_t>((i0 + 1) >> 1), a.t, TAG_BOND, a.sid,
-                                            k0, k1);
+                const U4 b2 = philox4x32_10((i0 + 1) >> 1, a.t, TAG_BOND, a.sid, k0, k1);
                 r1R = b2.v0;
                 r1D = b2.v1;
             }
-            // uniform flags are re-read per row as well (held across rows
-            // as lane masks, they too would spill)
+            // uniform flags are re-read per row (held across rows as lane
+            // masks, they would spill)
             uint32_t tany = __builtin_amdgcn_readfirstlane(a.tany);
             uint8_t *bonds_out = uniform_ptr(a.bonds_out);
             asm volatile("" : "+s"(tany), "+s"(bonds_out));
-            const uint64_t on0 = tany ? V0 : 0ull, on1 = tany ? V1 : 0ull;
-            mR0 = lanes_eq(s0, sr0) & lanes_le(r0R, a.tm1) & on0;
-            mD0 = lanes_eq(s0, d0) & lanes_le(r0D, a.tm1) & on0;
-            mR1 = lanes_eq(s1, sr1) & lanes_le(r1R, a.tm1) & on1;
-            mD1 = lanes_eq(s1, d1) & lanes_le(r1D, a.tm1) & on1;
+            mR0 = lanes_eq(s0, sr0) & lanes_le(r0R, a.tm1);
+            mD0 = lanes_eq(s0, d0) & lanes_le(r0D, a.tm1);
+            mR1 = lanes_eq(s1, sr1) & lanes_le(r1R, a.tm1);
+            mD1 = lanes_eq(s1, d1) & lanes_le(r1D, a.tm1);
+            if (!tany) mR0 = mR1 = mD0 = mD1 = 0ull;
             if (bonds_out) {
                 const uint32_t b0 = lane_bit(mR0, lane) | (lane_bit(mD0, lane) << 1);
                 const uint32_t b1 = lane_bit(mR1, lane) | (lane_bit(mD1, lane) << 1);
-                const bool w0 = lx0 < static_cast<int>(twr), w1 = lx1 < static_cast<int>(twr);
-                if (w1 && (EVENW || !(i0 & 1))) {
+                if (v1 && (EVENW || !(i0 & 1))) {
                     *reinterpret_cast<uint16_t *>(bonds_out + i0) = static_cast<uint16_t>(b0 | (b1 << 8));
                 } else {
-                    if (w0) bonds_out[i0] = static_cast<uint8_t>(b0);
-                    if (w1) bonds_out[i0 + 1] = static_cast<uint8_t>(b1);
+                    if (v0) bonds_out[i0] = static_cast<uint8_t>(b0);
+                    if (v1) bonds_out[i0 + 1] = static_cast<uint8_t>(b1);
                 }
             }
             nact += __popcll(mR0) + __popcll(mD0) + __popcll(mR1) + __popcll(mD1);  // 32-bit sums
+            cross = (mR0 & L0) | (mR1 & L1);
         } else if constexpr (MODE == M_BONDS_PERIODIC || MODE == M_BONDS_OPEN) {
-            mR0 = lanes_ne(cur & 0x001u, 0u) & V0;
-            mD0 = lanes_ne(cur & 0x002u, 0u) & V0;
-            mR1 = lanes_ne(cur & 0x100u, 0u) & V1;
-            mD1 = lanes_ne(cur & 0x200u, 0u) & V1;
-            if (MODE == M_BONDS_OPEN) {
-                if (right_is_wrap) {
-                    mR0 &= ~L0;
-                    mR1 &= ~L1;
-                }
-                if (bottom_is_wrap && ly == th - 1) mD0 = mD1 = 0ull;
-            }
+            mR0 = lanes_ne(cur & 0x001u, 0u);
+            mD0 = lanes_ne(cur & 0x002u, 0u);
+            mR1 = lanes_ne(cur & 0x100u, 0u);
+            mD1 = lanes_ne(cur & 0x200u, 0u);
+            cross = (mR0 & L0) | (mR1 & L1);
         } else {  // M_SITES: 4-connected occupied pixels, open boundary
-            O0 = lanes_ne(cur & 0x00FFu, 0u) & V0;
-            O1 = lanes_ne(cur & 0xFF00u, 0u) & V1;
-            const uint64_t below_occ = (gy + 1 < H) ? ~0ull : 0ull;
-            const uint64_t Dn0 = lanes_ne(dn & 0x00FFu, 0u) & below_occ;
-            const uint64_t Dn1 = lanes_ne(dn & 0xFF00u, 0u) & below_occ;
-            const uint64_t Hh = (!right_is_wrap && hl[r] != 0) ? ~0ull : 0ull;  // hl is lane-uniform
-            mR0 = O0 & ((O1 & ~L0) | (Hh & L0));
-            mR1 = O1 & (((O0 >> 1) & ~L1) | (Hh & L1));
-            mD0 = O0 & Dn0;
-            mD1 = O1 & Dn1;
+            O0 = lanes_ne(cur & 0x00FFu, 0u);
+            O1 = lanes_ne(cur & 0xFF00u, 0u);
+            mD0 = O0 & lanes_ne(dn & 0x00FFu, 0u);
+            mD1 = O1 & lanes_ne(dn & 0xFF00u, 0u);
+            mR0 = O0 & O1;         // the last column's right neighbour reads 0 here
+            mR1 = O1 & (O0 >> 1);
+            cross = lanes_ne(hl[r], 0u) & ((O0 & L0) | (O1 & L1));
         }
 
-        // Crossing bonds leave the tile: the last column's right bond and the
-        // last row's down bonds.  They are merged by k_merge.
-        if ((mR0 & L0) | (mR1 & L1)) xr |= 1ull << (ly & 63);
+        // Crossing bonds leave the tile: the last column's right bond here,
+        // the last row's down bonds below.  They are merged by k_merge.
+        xr |= cross ? 1u << r : 0u;
         const EO R = EO{mR0 & ~L0, mR1 & ~L1};
-        // the last tile row's down bonds cross the tile; selected on a uniform
-        // condition so the masks stay in scalar registers
-        const bool last = ly == th - 1;
-        const EO D = last ? EO{0ull, 0ull} : EO{mD0, mD1};
-        if (lane_r == 0) {
-            if (last) xd_s = EO{mD0, mD1};
-            if constexpr (MODE == M_SITES) Om[ly] = EO{O0, O1};
-        }
         const int base = ly * TW;
         // Run starts: site 2L starts a run unless bond 2L-1 -> 2L is present,
         // site 2L+1 unless bond 2L -> 2L+1 is; the run start of 2L is the last
-        // start at or before it (a max-scan over the lanes below).
-        // Scanned in byte offsets within the row (x4 = 4 lx0); lane 0's even
-        // site always starts a run, so every other lane finds a start below.
+        // start at or before it (a max-scan over the lanes below), in byte
+        // offsets within the row (x4 = 4 lx0); lane 0's even site always
+        // starts a run, at offset 0.
         const bool e_start = lane_bit(~(R.o << 1), lane);
         const bool o_start = lane_bit(~R.e, lane);
-        const int below4 = wave_max_below(o_start ? x4 + 8 : (e_start ? x4 + 4 : 0));
-        const int rs0 = e_start ? x4 : below4 - 4;
+        const int below4 = wave_max_below(o_start ? x4 + 4 : (e_start ? x4 : 0));
+        const int rs0 = e_start ? x4 : below4;
         const int rs1 = o_start ? x4 + 4 : rs0;
-        const int own = 4 * base + x4;  // the even site's own entry
         int n0 = 4 * base + rs0, n1 = 4 * base + rs1;
+        if constexpr (MODE == M_SITES) {
+            n0 = lane_bit(O0, lane) ? n0 : BG4;
+            n1 = lane_bit(O1, lane) ? n1 : BG4;
+        }
         *reinterpret_cast<int2 *>(&P[base + lx0]) = make_int2(n0, n1);
         if (r > 0) {
             // every contact offers its upper site's label to the lower run's
             // start (one wave's LDS operations run in order; whichever offer
             // lands last stands); a contact whose label lost needs a union
+            const int up0 = lab0[r > 0 ? r - 1 : 0], up1 = lab1[r > 0 ? r - 1 : 0];
             wave_lds_fence();
-            if (lane_bit(prevD.e, lane)) lds_st(lds_entry<true>(P, n0), lab0);
-            if (lane_bit(prevD.o, lane)) lds_st(lds_entry<true>(P, n1), lab1);
+            if (lane_bit(prevD.e, lane)) lds_st(lds_entry<true>(P, n0), up0);
+            if (lane_bit(prevD.o, lane)) lds_st(lds_entry<true>(P, n1), up1);
             wave_lds_fence();
-            n0 = lds_ld(lds_entry<true>(P, n0));
-            n1 = lds_ld(lds_entry<true>(P, n1));
+            // (the background entry reads as itself: background keeps BG4)
+            const int q0 = lds_ld(lds_entry<true>(P, n0)), q1 = lds_ld(lds_entry<true>(P, n1));
+            n0 = MODE == M_SITES && n0 == BG4 ? BG4 : q0;
+            n1 = MODE == M_SITES && n1 == BG4 ? BG4 : q1;
             *reinterpret_cast<int2 *>(&P[base + lx0]) = make_int2(n0, n1);
-            const EO lost = EO{lanes_ne(static_cast<uint32_t>(n0), static_cast<uint32_t>(lab0)) & prevD.e,
-                               lanes_ne(static_cast<uint32_t>(n1), static_cast<uint32_t>(lab1)) & prevD.o};
+            const EO lost = EO{lanes_ne(static_cast<uint32_t>(n0), static_cast<uint32_t>(up0)) & prevD.e,
+                               lanes_ne(static_cast<uint32_t>(n1), static_cast<uint32_t>(up1)) & prevD.o};
             // a full list is united at once (only rows this wave has
             // initialised are involved)
             if (ncon > TL - TW) {
                 unite_list(ncon);
                 ncon = 0;
             }
-            eo_append<2>(mylist, ncon, lost, lane, base - TW);
+            const int up_own = 4 * (base - TW) + x4;  // the upper even site
+            eo_append(mylist, ncon, lost, up_own, up_own + 4);
         }
-        const EO labels = EO{lanes_eq(static_cast<uint32_t>(n0), static_cast<uint32_t>(own)),
-                             lanes_eq(static_cast<uint32_t>(n1), static_cast<uint32_t>(own + 4))};
-        if (lane_r == 0) Lm[ly] = labels;
-        lab0 = n0;
-        lab1 = n1;
-        prevD = D;
+        lab0[r] = n0;
+        lab1[r] = n1;
+        prevD = EO{mD0, mD1};
     }
+    if (MODE == M_BONDS_OPEN || MODE == M_SITES) xr = right_is_wrap ? 0u : xr;
     if (lane == 0) {
-        xr_w[wave] = xr;
+        sm.xr_w[wave] = xr;
         act_w[wave] = nact;
+        // the last tile row's down bonds cross the tile
+        if (nr > 0 && ly0 + nr == th)
+            sm.xd_s = MODE == M_BONDS_OPEN && bottom_is_wrap ? EO{0ull, 0ull} : prevD;
+    }
+    if (tw < TW) {  // sites past a ragged edge get background codes
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+            lab0[r] = v0 ? lab0[r] : BG4;
+            lab1[r] = v1 ? lab1[r] : BG4;
+        }
     }
     __syncthreads();
 
-    // ---- B: contacts with the next wave's first row, then all unions ----
+    // ---- B: contacts with the next wave's first row, then all unions.  A
+    // lower label that is still a root of that row on is linked below the
+    // upper label by one compare-and-swap (upper labels lie above the row, so
+    // a parent stays below its child); the contacts left are united.
     if (nr > 0 && ly0 + nr < th) {
         if (ncon > TL - TW) {
             unite_list(ncon);
             ncon = 0;
         }
-        eo_append<2>(mylist, ncon, prevD, lane, (ly0 + nr - 1) * TW);
+        const int row4 = 4 * (ly0 + nr) * TW;
+        const int up0 = nr == RPW ? lab0[RPW - 1] : 0, up1 = nr == RPW ? lab1[RPW - 1] : 0;
+        const int2 low = make_int2(lds_ld(&P[(row4 >> 2) + lx0]), lds_ld(&P[(row4 >> 2) + lx0 + 1]));
+        auto link = [&](int x, int up) {  // the entry of x as it was: x (linked now) or its parent
+            int expect = x;
+            __hip_atomic_compare_exchange_strong(lds_entry<true>(P, x), &expect, up, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            return expect;
+        };
+        int got0 = -1, got1 = -1;
+        if (lane_bit(prevD.e, lane) && low.x >= row4) got0 = link(low.x, up0);
+        if (lane_bit(prevD.o, lane) && low.y >= row4) got1 = link(low.y, up1);
+        const EO met = EO{lanes_eq(static_cast<uint32_t>(got0), static_cast<uint32_t>(low.x)) |
+                              lanes_eq(static_cast<uint32_t>(got0), static_cast<uint32_t>(up0)),
+                          lanes_eq(static_cast<uint32_t>(got1), static_cast<uint32_t>(low.y)) |
+                              lanes_eq(static_cast<uint32_t>(got1), static_cast<uint32_t>(up1))};
+        eo_append(mylist, ncon, eo_andnot(prevD, met), row4 - 4 * TW + x4, row4 - 4 * TW + x4 + 4);
     }
     unite_list(ncon);
     __syncthreads();
 
-    // Occupancy of a tile slot: images keep per-row masks, every site of a
-    // bond input is a lattice site.
-    auto occupied = [&](int slot) {
-        if constexpr (MODE == M_SITES) {
-            const EO O = Om[slot >> 7];
-            const int x = slot & (TW - 1);
-            return (((x & 1) ? O.o : O.e) >> (x >> 1) & 1ull) != 0;
-        } else {
-            return true;
-        }
-    };
-
     // ---- C: the clusters that touch the tile border are claimed (one
     // thread per border position), then, after a barrier, every linked label
-    // gets its cluster's final code, stored in its own entry as
-    // -(code + 2): the boundary id of a claimed root, else CAP + the root's
-    // slot (a claimed root's entry already reads -(id + 2)).  Lane L walks
-    // labels L, L+64, ... of the wave's list up to the first entry that is
-    // negative (a claimed root, or a label another lane has finished:
-    // either way the cluster's code) or its own (an unclaimed root); a lane
-    // whose walk is done takes its next label at once.  Only linked labels
-    // (entry neither their own nor negative) are listed.
+    // gets its cluster's final entry: the claimed root's, or that of the
+    // unclaimed root's slot.  Lane L walks labels L, L+64, ... of the wave's
+    // list up to the first entry that is negative (a claimed root, or a label
+    // another lane has finished: either way the cluster's code) or its own (an
+    // unclaimed root); a lane whose walk is done takes its next label at once.
+    // Only linked labels (entry neither their own nor negative) are listed.
     auto compress_list = [&](int n) {
         wave_lds_fence();
         int i = lane, s0 = 0, x = 0;
@@ -644,7 +669,7 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
             if (p >= 0 && p != x) {
                 x = p;
             } else {
-                lds_st(lds_entry<true>(P, s0), p < 0 ? p : -(CAP + (x >> 2)) - 2);
+                lds_st(lds_entry<true>(P, s0), p | static_cast<int>(0x80000000u));
                 i += 64;
                 if (i < n) s0 = x = mylist[i];
             }
@@ -660,13 +685,14 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
     }
     for (int t = threadIdx.x; t < EDGE; t += NT) {
         const int slot = border_slot<TH>(t, tw, th);
-        if (slot < 0 || !occupied(slot)) continue;
+        if (slot < 0) continue;
         const int root4 = lroot(P, 4 * slot), root = root4 >> 2;
         int expect = root4;
+        // (background ends at its own entry, which no claim matches)
         if (__hip_atomic_compare_exchange_strong(lds_entry<true>(P, root4), &expect, CLAIMING, __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
             const int k = atomicAdd(&nb_s, 1);
-            lds_st(lds_entry<true>(P, root4), -(k + 2));
+            lds_st(lds_entry<true>(P, root4), final_entry(static_cast<uint32_t>(TSITES + k)));
             const int id = tile * CAP + k;
             gkey[id] = (gy0 + (root >> 7)) * W + gx0 + (root & (TW - 1));
             gparent[id] = id;
@@ -684,32 +710,23 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         if (r >= nr) break;
-        const int ly = ly0 + r;
-        const int base = ly * TW;
         if (nrs > TL - TW) {
             compress_list(nrs);
             nrs = 0;
         }
-        const EO L = uniform_eo(Lm[ly]);
-        const int2 pp = ppr[r];
-        const EO linked = EO{lanes_ne(static_cast<uint32_t>(pp.x), static_cast<uint32_t>(4 * (base + lx0))) &
-                                 lanes_lt(static_cast<uint32_t>(pp.x), 0x80000000u),
-                             lanes_ne(static_cast<uint32_t>(pp.y), static_cast<uint32_t>(4 * (base + lx0 + 1))) &
-                                 lanes_lt(static_cast<uint32_t>(pp.y), 0x80000000u)};
-        eo_append<2>(mylist, nrs, eo_and(L, linked), lane, base);
+        // a label site whose entry is an offset below its own (a final entry
+        // is negative, above every offset as an unsigned number)
+        const uint32_t own = static_cast<uint32_t>(4 * (ly0 + r) * TW + x4);
+        const EO linked = EO{lanes_eq(static_cast<uint32_t>(lab0[r]), own) & lanes_lt(static_cast<uint32_t>(ppr[r].x), own),
+                             lanes_eq(static_cast<uint32_t>(lab1[r]), own + 4) &
+                                 lanes_lt(static_cast<uint32_t>(ppr[r].y), own + 4)};
+        eo_append(mylist, nrs, linked, static_cast<int>(own), static_cast<int>(own + 4));
     }
     compress_list(nrs);
     __syncthreads();
 
-    // ---- E: per-site codes (boundary id of a claimed root, else CAP + the
-    // root's slot), edge ids, crossing bits.  A site's code is one step past
-    // its entry: a label site holds its code (or, an unclaimed root, its own
-    // offset), any other site its label's offset.
-    auto code_of = [&](int x, int p) {  // x a slot, p = P[x] (byte offsets)
-        x *= 4;
-        if (p >= 0 && p != x) p = *lds_entry<true>(P, p);
-        return p < 0 ? static_cast<uint32_t>(-p - 2) : static_cast<uint32_t>(CAP + (p >> 2));
-    };
+    // ---- E: per-site codes (the entry of the site's label), edge ids,
+    // crossing bits.
     uint16_t *codes = a.codes, *edges = a.edges;
     uint64_t *xbits = a.xbits;
     int32_t *nbp = a.nb, *tile_act = a.tile_act;
@@ -722,24 +739,23 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         tile_act = ka->tile_act;
     }
     uint32_t *codes32 = reinterpret_cast<uint32_t *>(codes + static_cast<int64_t>(tile) * TSITES);
-    // unrolled: the rows' lookup chains are independent, so their LDS loads overlap
+    // unrolled: the rows' lookups are independent, so their LDS loads overlap
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         if (r >= nr) break;
-        const int ly = ly0 + r;
-        EO O = valid;
-        if constexpr (MODE == M_SITES) O = Om[ly];
-        const int base = ly * TW;
-        const int2 pp = *reinterpret_cast<const int2 *>(&P[base + lx0]);
-        const uint32_t code0 = lane_bit(O.e, lane) ? code_of(base + lx0, pp.x) : CODE_BG;
-        const uint32_t code1 = lane_bit(O.o, lane) ? code_of(base + lx0 + 1, pp.y) : CODE_BG;
-        codes32[(base + lx0) >> 1] = code0 | (code1 << 16);
+        const uint32_t code0 = entry_code(lds_ld(lds_entry<true>(P, lab0[r])));
+        const uint32_t code1 = entry_code(lds_ld(lds_entry<true>(P, lab1[r])));
+        codes32[((ly0 + r) * TW + lx0) >> 1] = code0 | (code1 << 16);
     }
     uint16_t *edg = edges + static_cast<int64_t>(tile) * EDGE;
     for (int t = threadIdx.x; t < EDGE; t += NT) {
         const int slot = border_slot<TH>(t, tw, th);
         uint16_t eid = ID_NONE;
-        if (slot >= 0 && occupied(slot)) eid = static_cast<uint16_t>(code_of(slot, P[slot]));
+        if (slot >= 0) {
+            int e = P[slot];  // a claimed root or coded label, or the site's label
+            if (e >= 0) e = *lds_entry<true>(P, e);
+            eid = static_cast<uint16_t>(entry_code(e) - TSITES);  // a boundary id; background ends up past CAP
+        }
         edg[t] = eid;
     }
     if (threadIdx.x == 0) {
@@ -748,12 +764,13 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
 #pragma unroll
         for (int j = 0; j < XR; ++j) {
             unsigned long long xrt = 0;  // rows 64 j ... 64 j + 63: the waves (64 / RPW of them) holding them
-            for (int w = j * (64 / RPW); w < min(NWAVE, (j + 1) * (64 / RPW)); ++w) xrt |= xr_w[w];
+            for (int w = j * (64 / RPW); w < min(NWAVE, (j + 1) * (64 / RPW)); ++w)
+                xrt |= static_cast<unsigned long long>(sm.xr_w[w]) << ((w * RPW) & 63);
             xb[j] = xrt;
         }
         for (int w = 0; w < NWAVE; ++w) act += act_w[w];
-        xb[XR] = xd_s.e;      // bottom crossing bonds of even columns
-        xb[XR + 1] = xd_s.o;  // ... and of odd columns
+        xb[XR] = sm.xd_s.e;      // bottom crossing bonds of even columns
+        xb[XR + 1] = sm.xd_s.o;  // ... and of odd columns
         nbp[tile] = nb_s;
         if (MODE == M_SW && tile_act) tile_act[tile] = act;
     }
@@ -949,10 +966,10 @@ __global__ __launch_bounds__(NT) void k_seed(SeedArgs a)
     const int lt = (y / S::TH) * a.g.ntx + x / TW;
     const int slot = (y % S::TH) * TW + x % TW;
     const uint32_t code = a.codes[static_cast<int64_t>(lt) * S::TSITES + slot];
-    if (code < static_cast<uint32_t>(S::CAP)) {
-        a.sel[gfind(a.gparent, lt * S::CAP + static_cast<int>(code))] = a.stamp;
+    if (code >= static_cast<uint32_t>(S::TSITES)) {
+        a.sel[gfind(a.gparent, lt * S::CAP + static_cast<int>(code) - S::TSITES)] = a.stamp;
     } else {
-        const uint32_t root = code - S::CAP;
+        const uint32_t root = code;
         atomicOr(&a.seedmap[static_cast<int64_t>(lt) * (S::TSITES / 32) + (root >> 5)], 1u << (root & 31u));
     }
 }
@@ -969,8 +986,8 @@ __device__ __forceinline__ uint8_t flip_state(uint32_t R, const FlatArgs &a)
 template <int MODE, bool SIZES, int TH_>
 struct FlatSmem {
     static constexpr int TH = TH_, TSITES = TW * TH, CAP = 2 * (TW + TH), NWAVE = TH / RPW;
-    uint8_t ST[MODE == M_SW || MODE == M_FEW ? CAP + TSITES : 1];  // new state per code (boundary id or
-                                                                    // CAP + slot); M_FEW: FEW_KEEP = no change
+    uint8_t ST[MODE == M_SW || MODE == M_FEW ? TSITES + CAP : 1];  // new state per code (root slot or TSITES +
+                                                                    // boundary id); M_FEW: FEW_KEEP = no change
     int32_t Rb[CAP];                              // canonical root (site index) per boundary id
     int32_t Gid[CAP];                             // root id per boundary id
     uint16_t rl[NWAVE][WLIST];                    // interior roots of each wave's rows
@@ -1059,22 +1076,22 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
 #pragma unroll
     for (int r = 0; r < RPW; ++r) cc[r] = r < nr ? codes32[((ly0 + r) * TW + lx0) >> 1] : 0xFFFFFFFFu;
 
-    // interior roots (code = CAP + own slot) of the wave's rows, compacted
+    // interior roots (code = own slot) of the wave's rows, compacted
     int nroot = 0;
     uint16_t *mylist = rl[wave];
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         if (r >= nr) break;  // unrolled: cc[] stays indexed by constants
         const int base = (ly0 + r) * TW;
-        const EO m = EO{lanes_eq(cc[r] & 0xFFFFu, static_cast<uint32_t>(CAP + base + lx0)),
-                        lanes_eq(cc[r] >> 16, static_cast<uint32_t>(CAP + base + lx0 + 1))};
-        eo_append(mylist, nroot, m, lane, base);
+        const EO m = EO{lanes_eq(cc[r] & 0xFFFFu, static_cast<uint32_t>(base + lx0)),
+                        lanes_eq(cc[r] >> 16, static_cast<uint32_t>(base + lx0 + 1))};
+        eo_append(mylist, nroot, m, base + lx0, base + lx0 + 1);
     }
     wave_lds_fence();
     if constexpr (MODE == M_SW) {
         for (int i = lane; i < nroot; i += 64) {
             const int slot = mylist[i];
-            ST[CAP + slot] = flip_state(static_cast<uint32_t>((gy0 + (slot >> 7)) * W + gx0 + (slot & (TW - 1))), a);
+            ST[slot] = flip_state(static_cast<uint32_t>((gy0 + (slot >> 7)) * W + gx0 + (slot & (TW - 1))), a);
         }
     } else if constexpr (MODE == M_FEW) {
         // a seeded interior cluster that flips takes the other state of its
@@ -1094,7 +1111,7 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
             if (seeded) old = a.spins[R];
             uint8_t v = FEW_KEEP;
             if (seeded && few_flips(R, a)) v = static_cast<uint8_t>(1u - state_of_byte(old, a.ising));
-            ST[CAP + slot] = v;
+            ST[slot] = v;
         }
     }
     // boundary ids: the root and its key (the cluster's minimum site index),
@@ -1115,7 +1132,7 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
             Rb[k] = key;
             Gid[k] = r;
             nbr += r == id;
-            if constexpr (MODE == M_SW) ST[k] = flip_state(static_cast<uint32_t>(key), a);
+            if constexpr (MODE == M_SW) ST[TSITES + k] = flip_state(static_cast<uint32_t>(key), a);
             if constexpr (MODE == M_FEW) {
                 // seeded iff its root carries this sweep's mark; the old state
                 // was read at the id's own tile-local root (a site of this
@@ -1123,7 +1140,7 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
                 uint8_t v = FEW_KEEP;
                 if (a.sel[r] == a.stamp && few_flips(static_cast<uint32_t>(key), a))
                     v = static_cast<uint8_t>(1u - state_of_byte(old, a.ising));
-                ST[k] = v;
+                ST[TSITES + k] = v;
             }
         }
     }
@@ -1177,10 +1194,10 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const uint32_t c = cs[j];
-                const int slot = static_cast<int>(c) - CAP;
+                const int slot = static_cast<int>(c);
                 R[j] = c == CODE_BG ? -1
-                     : c < static_cast<uint32_t>(CAP) ? Rb[c]
-                                                       : (gy0 + (slot >> 7)) * W + gx0 + (slot & (TW - 1));
+                     : c >= static_cast<uint32_t>(TSITES) ? Rb[c - TSITES]
+                                                          : (gy0 + (slot >> 7)) * W + gx0 + (slot & (TW - 1));
             }
             if (v1 && !(i0 & 1)) {
                 *reinterpret_cast<int2 *>(a.labels + i0) = make_int2(R[0], R[1]);
@@ -1190,8 +1207,8 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
             }
         }
         if constexpr (SIZES) {
-            if (v0 && c0 != CODE_BG) atomicAdd(c0 < static_cast<uint32_t>(CAP) ? &Cb[c0] : &Ci[c0 - CAP], 1);
-            if (v1 && c1 != CODE_BG) atomicAdd(c1 < static_cast<uint32_t>(CAP) ? &Cb[c1] : &Ci[c1 - CAP], 1);
+            if (v0 && c0 != CODE_BG) atomicAdd(c0 < static_cast<uint32_t>(TSITES) ? &Ci[c0] : &Cb[c0 - TSITES], 1);
+            if (v1 && c1 != CODE_BG) atomicAdd(c1 < static_cast<uint32_t>(TSITES) ? &Ci[c1] : &Cb[c1 - TSITES], 1);
         }
     }
 
@@ -1214,10 +1231,10 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
                 const int s = lx0 + j;
                 const uint32_t code = (cc[r] >> (16 * j)) & 0xFFFFu;
                 const int32_t self = (gy0 + ly) * W + gx0 + s;
+                const int k = static_cast<int>(code) - TSITES;  // boundary id
                 isr[j] = s < tw && code != CODE_BG &&
-                         ((code == static_cast<uint32_t>(CAP + base + s)) ||
-                          (code < static_cast<uint32_t>(CAP) && Gid[code] == tile * CAP + static_cast<int>(code) &&
-                           Rb[code] == self));
+                         (code == static_cast<uint32_t>(base + s) ||
+                          (k >= 0 && Gid[k] == tile * CAP + k && Rb[k] == self));
             }
             rm[r] = EO{__ballot(isr[0]), __ballot(isr[1])};
             if (lane == 0) {
@@ -1253,8 +1270,9 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
                 const uint32_t code = (cc[r] >> (16 * j)) & 0xFFFFu;
                 const int64_t o = static_cast<int64_t>(tile) * TSITES + pos;
                 a.rl_slot[o] = base + s;
-                a.rl_size[o] = (code < static_cast<uint32_t>(CAP)) ? -(tile * CAP + static_cast<int>(code) + 1)
-                                                                   : Ci[base + s];
+                a.rl_size[o] = (code >= static_cast<uint32_t>(TSITES))
+                                   ? -(tile * CAP + static_cast<int>(code) - TSITES + 1)
+                                   : Ci[base + s];
             }
         }
     }
