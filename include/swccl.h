@@ -482,8 +482,8 @@ typedef struct sw3_params {
 enum { SW3_REC_ACTIVE = 0, SW3_REC_NCLUST = 1, SW3_REC_NSAT = 2, SW3_REC_COUNTS = 3, SW3_REC_LEN = 11 };
 
 /* Workspace bytes sw3_sweep needs for these parameters (0 if they are
- * invalid).  About 2 bytes per site of codes, 1 of bonds and 8 per tile
- * boundary site of ids. */
+ * invalid).  About 2 bytes per site of codes and 8 per tile boundary site
+ * of ids. */
 size_t sw3_workspace_bytes(const sw3_params *p);
 
 /* Initial states of the N sites (device, N bytes, stored as spin_kind says):

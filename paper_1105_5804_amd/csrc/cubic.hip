@@ -6,13 +6,15 @@
 //
 //   k3_tile     one 512-thread workgroup per 32 x 16 x 16 tile (the shape of
 //               8192 sites with the fewest face sites and crossing bonds);
-//               two sites per lane, a wave-wide step covering four tile rows,
-//               each wave eight steps.
+//               two sites per lane, a wave-wide step covering one row of four
+//               z-planes, each wave eight steps along y.
 //               Bond activation of the +x, +y and +z bonds (Sec. II.A) fused
-//               with a lock-free union-find in LDS over the bonds that stay in
-//               the tile (Sec. II.B.2); the clusters touching any tile face
-//               are claimed and get compact ids; every site gets a 16-bit code
-//               (its cluster's id, or CAP + the slot of its interior root).
+//               with the tile's labeling (Sec. II.B.2): labels handed along
+//               x runs, down the rows and across planes, the bonds left over
+//               united by a lock-free union-find in LDS; the clusters touching
+//               any tile face are claimed and get compact ids; every site gets
+//               a 16-bit code (the slot of its interior root, or CSITES + its
+//               cluster's id; the crossing bonds in the bits above).
 //   k3_merge    every active bond that leaves a tile through its +x, +y or +z
 //               face (periodic wraps included) unites two ids in the global
 //               union-find (Sec. II.C).  Roots are linked by a fixed random
@@ -47,27 +49,28 @@ constexpr int CX = 32, CY = 16, CZ = 16;                      // tile extent (x 
 constexpr int PLANE = CX * CY;                                 // sites of a tile z-plane
 constexpr int CSITES = PLANE * CZ;                             // sites per tile
 constexpr int CAP = CSITES - (CX - 2) * (CY - 2) * (CZ - 2);   // sites on a face of a full tile
-// Lanes: two sites each, so a wave-wide step covers 128 sites, RPI tile rows
-// of CX sites; the tile's CY * CZ rows are dealt to NW3 waves, RW rows (ITER
-// steps) each.  Row R of a tile is (ly, lz) = (R mod CY, R / CY).
+// Lanes: two sites each, so a wave-wide step covers 128 sites: one row of
+// each of SUB z-planes.  NW3 waves: wave w takes the planes (w / 2) SUB ... of
+// y range (w mod 2) ITER ..., ITER steps down its rows.
 constexpr int NW3 = 8;                                         // waves per tile workgroup
 constexpr int NT3 = 64 * NW3;
 constexpr int LPR = CX / 2;                                    // lanes per tile row
-constexpr int RPI = 64 / LPR;                                  // tile rows per step
-constexpr int RW = CY * CZ / NW3;                              // tile rows per wave
-constexpr int ITER = RW / RPI;                                 // steps per wave
-static_assert(CSITES == 128 * NW3 * ITER && ITER == 8, "eight steps of 128 sites per wave");
-static_assert(CY % (2 * RPI) == 0 && RW % (2 * RPI) == 0, "steps pair up inside a z-plane");
+constexpr int SUB = 64 / LPR;                                  // tile rows (planes) per step
+constexpr int RPI = SUB;
+constexpr int ITER = 8;                                        // steps per wave
+constexpr int TL3 = 448;                                       // per-wave lists: a step adds at most 128 entries at a
+                                                               // time, a fuller list is worked off first
+static_assert(CSITES == 128 * NW3 * ITER && CY == 2 * ITER && CZ == SUB * NW3 / 2, "the waves cover the tile");
 constexpr int MT = 256;                                        // merge workgroup
 constexpr int RT = 64;                                         // resolve workgroup: one wave per tile
 constexpr int MSEEN = 1024;                                    // merge: pair-dedup slots per face
 constexpr int FX = CY * CZ, FY = CX * CZ, FZ = CX * CY;        // sites of the +x, +y, +z faces
 constexpr uint32_t TAG_BOND = 1, TAG_FLIP = 2, TAG_BOND_Z = 5;
-constexpr int CLAIMING = -1;
-constexpr uint16_t CODE_NONE = 0xFFFF;
-static_assert(CAP + CSITES < CODE_NONE, "codes are 16-bit");
+// A code is the slot of the site's interior root or CSITES + its id; the two
+// bits above carry the +y and +z bonds of sites on the last row and plane.
+constexpr uint32_t CODE_MASK = 0x3FFF;
+static_assert(CAP + CSITES <= CODE_MASK, "codes take 14 bits");
 static_assert(CAP < (1 << 15), "merge list entries hold two ids in 15 bits each");
-static_assert(ITER * 8 <= 64, "a lane's bonds fit one 64-bit mask");
 
 // Counters of a sweep, in the order of the record fields.
 enum { S3_ACTIVE = 0, S3_NCLUST = 1, S3_NSAT = 2, S3_COUNTS = 3, S3_LEN = 11 };
@@ -95,6 +98,14 @@ __device__ __forceinline__ TileOf tile_of(const Geo3 &g, int tile)
     return t;
 }
 
+// Position of site (lx, ly, lz) in a tile's code array: the order in which the
+// waves' steps write and read them, 256 contiguous bytes a step.
+__device__ __forceinline__ int code_pos(int lx, int ly, int lz)
+{
+    const int w = lz / SUB * 2 + ly / ITER;
+    return ((w * ITER + ly % ITER) * 64 + lz % SUB * LPR) * 2 + lx;
+}
+
 // Site index of tile slot s = (lz CY + ly) CX + lx.
 __device__ __forceinline__ int32_t site_of(const Geo3 &g, const TileOf &t, int s)
 {
@@ -109,12 +120,25 @@ __device__ __forceinline__ uint32_t swap_pair_lanes(uint32_t x)
     return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0xB1, 0xF, 0xF, false));
 }
 
+// Maximum of v >= 0 over the lanes below the calling one in its group of 16
+// (0 for the first): a max-scan by row shifts (a DPP row is 16 lanes, LPR of
+// them a tile row), then a shift by one lane.
+static_assert(LPR == 16, "a tile row is a DPP row");
+__device__ __forceinline__ int row_max_below(int v)
+{
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));  // row_shr:2
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));  // row_shr:4
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));  // row_shr:8
+    return __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+}
+
 struct Tile3Args {
     Geo3 g;
-    const uint8_t *spins;
-    uint8_t *bonds;           // [N] packed bonds of the sweep (bit0 +x, bit1 +y, bit2 +z)
-    uint16_t *codes;          // [ntiles][CSITES]
-    uint16_t *xface;          // [ntiles][2][FX]: codes of the x = 0 sites, then of the x = tw - 1 sites | +x bond << 15
+    const uint8_t *in;        // spins, or the given bonds (LABEL)
+    uint8_t *bonds;           // [N] packed bonds of the sweep (bit0 +x, bit1 +y, bit2 +z), or nullptr
+    uint16_t *codes;          // [ntiles][CSITES], in the order of code_pos
+    uint16_t *xface;          // [ntiles][2][FX]: ids of the x = 0 sites, then of the x = tw - 1 sites | +x bond << 15
     int32_t *gkey, *gparent;  // [ntiles][CAP]
     int32_t *nb;              // [ntiles]: ids of the tile
     int32_t *tile_act;        // [ntiles]: active bonds owned by the tile
@@ -122,268 +146,407 @@ struct Tile3Args {
     uint32_t k0, k1, t, sid;
 };
 
-// LABEL: the bonds are given (a.bonds is read, never written); otherwise they
-// are drawn from the spins and written.
-template <bool LABEL>
-__global__ __launch_bounds__(NT3) void k3_tile(Tile3Args a)
+// Slot of face position t (the z, then y, then x faces of a full tile), or -1
+// outside a ragged tile.
+constexpr int FACES = 2 * (FZ + FY + FX);
+__device__ __forceinline__ int face_slot(int t, const TileOf &T)
 {
-    __shared__ int P[CSITES];
+    int lx, ly, lz;
+    if (t < 2 * FZ) {
+        lx = t % CX;
+        ly = t / CX % CY;
+        lz = t < FZ ? 0 : T.td - 1;
+    } else if (t < 2 * (FZ + FY)) {
+        t -= 2 * FZ;
+        lx = t % CX;
+        lz = t / CX % CZ;
+        ly = t < FY ? 0 : T.th - 1;
+    } else {
+        t -= 2 * (FZ + FY);
+        ly = t % CY;
+        lz = t / CY % CZ;
+        lx = t < FX ? 0 : T.tw - 1;
+    }
+    return lx < T.tw && ly < T.th && lz < T.td ? lz * PLANE + ly * CX + lx : -1;
+}
+
+// LABEL: the bonds are given (a.in, only read); otherwise they are drawn from
+// the spins (and written if asked for).
+//
+// A wave owns SUB z-planes of half a tile's y range and goes down their rows
+// together: lane group `sub` holds plane sub's row, two sites a lane.  +x
+// bonds become runs of a row (a max-scan over its 16 lanes), a run takes the
+// label of one run before it along y by a plain LDS write, and a label still
+// a root is linked below the plane before it by one compare-and-swap, as are
+// the contacts with other waves' rows and planes after a barrier.  Only the
+// bonds that lose (two labels already, or a root linked elsewhere) are united
+// step by step.  At the critical point 0.24 of the bonds of each direction
+// are active and about a tenth of them are left to unite, where uniting every
+// bond inside the tile cost two thirds of the kernel.  The crossing bonds go
+// out in the codes' upper bits, so no bond array is written unless asked for.
+// Still bound by VALU issue: 474 -> 293 VALU instructions per 128 sites, the
+// kernel 868 -> 473 us at 512^3 and beta_c, the sweep 1.539 -> 1.083 ms.
+// FOUR: Lx is a multiple of 4 (pairs of sites load and store as one, and
+// share random blocks); the general form serves every Lx.
+template <bool LABEL, bool FOUR>
+__global__ __launch_bounds__(NT3) __attribute__((amdgpu_waves_per_eu(8, 8))) void k3_tile(Tile3Args a)
+{
+    __shared__ int P[CSITES];             // union-find parent per slot, as 4 x slot
+    __shared__ uint16_t wl[NW3][TL3];     // per-wave list: 4 x slot | direction (0 +y, 1 +z) of a bond, or a label
+    __shared__ uint32_t zb[NW3][LPR];     // +z bonds of the wave's last plane: bit 2 it + j of a lane's sites
     __shared__ int nb_s;
     __shared__ unsigned act_w[NW3];
     const Geo3 g = a.g;
     const TileOf T = tile_of(g, xcd_remap(blockIdx.x, g.ntiles));
     const int lane = threadIdx.x & 63, w = wave_id();
-    const int sub = lane / LPR, lx0 = 2 * (lane % LPR);  // the lane's row in a step, its first site
-    // the lane's tile row at step it, and whether that row lies in the tile
-    auto row_of = [&](int it) { return w * RW + it * RPI + sub; };
-    auto row_in = [&](int R) { return R % CY < T.th && R / CY < T.td; };
+    const int sub = lane / LPR, lx0 = 2 * (lane % LPR), x4 = 4 * lx0;
+    const int lz = (w >> 1) * SUB + sub, ly0 = (w & 1) * ITER;
+    const int nr = max(0, min(ITER, T.th - ly0));  // tile rows along y owned by this wave
+    const bool zin = lz < T.td;
+    const bool v0 = zin && lx0 < T.tw, v1 = zin && lx0 + 1 < T.tw;
+    const bool ragged = T.tw < CX || T.td < CZ;
+    uint16_t *mylist = wl[w];
     if (threadIdx.x == 0) nb_s = 0;
-    for (int k = threadIdx.x; k < CSITES; k += NT3) P[k] = k;
+    // lane masks (each tile row's 16 lanes alike): the last column's sites
+    const uint32_t row0m = 0xFFFFu >> (LPR - ((T.tw + 1) >> 1)), row1m = row0m >> (T.tw & 1);
+    const uint64_t every = 0x0001000100010001ull;
+    const uint64_t L0 = (row0m & ~row1m) * every, L1 = (row1m & ~(row0m >> 1)) * every;
 
-    // Bonds of the lane's two sites at each step; bit 8 it + 4 j + d of
-    // `inside` is bond d (0 +x, 1 +y, 2 +z) of site lx0 + j of the step's row
-    // when it stays in the tile (the others cross a face and are merged by
-    // k3_merge from the bond array).  Site indices fit 32 bits.
-    uint64_t inside = 0;
-    uint32_t xbit = 0;  // bit 2 it + j: the +x bond of site lx0 + j of the step's row
-    unsigned act = 0;
+    auto unite_list = [&](int n) {  // as in the square-lattice tile
+        wave_lds_fence();
+        int i = lane, u = 0, v = 0;
+        auto next = [&]() {
+            const int e = mylist[i], c = e & ~3;
+            u = lds_ld(lds_entry<true>(P, c));
+            v = lds_ld(lds_entry<true>(P, c + ((e & 1) ? 4 * PLANE : 4 * CX)));
+        };
+        if (i < n) next();
+        while (i < n) {
+            int done;
+            unite_step<true, true>(P, u, v, done);
+            if (done) {
+                i += 64;
+                if (i < n) next();
+            }
+        }
+        wave_lds_fence();
+    };
+    int ncon = 0;
+    auto append = [&](EO m, int e) {  // the bonds m of the sites at byte offset e (| direction)
+        if (ncon > TL3 - 128) {
+            unite_list(ncon);
+            ncon = 0;
+        }
+        eo_append(mylist, ncon, m, e, e + 4);
+    };
+
+    // ---- loads of the wave's rows (site indices fit 32 bits): cur[it] is the
+    // pair of bytes at tile row ly0 + it of the lane's plane (one more row for
+    // the +y neighbours), zz[it] the pair in the next plane, hl[it] the byte
+    // right of the tile.  Lanes outside the tile read a valid address.
     const uint32_t Lx = static_cast<uint32_t>(g.Lx), Ly = static_cast<uint32_t>(g.Ly), Lz = static_cast<uint32_t>(g.Lz);
-    // a tile full along y and z: every row of every step lies in it, the
-    // lane's rows are its first one plus uniform offsets (a wave owns whole
-    // z-planes, RW a multiple of CY)
-    static_assert(RW % CY == 0, "a wave owns whole z-planes");
-    const bool full = T.th == CY && T.td == CZ;
-    const uint32_t row_first = ((static_cast<uint32_t>(T.gz0 + w * (RW / CY))) * Ly + static_cast<uint32_t>(T.gy0 + sub)) * Lx;
-    const bool ywrap_at_last = static_cast<uint32_t>(T.gy0 + CY) == Ly, zwrap_at_last = static_cast<uint32_t>(T.gz0 + CZ) == Lz;
-    // lanes past a ragged edge read a valid column and store nothing
-    const uint32_t xs0 = static_cast<uint32_t>(T.gx0 + min(lx0, T.tw - 1));
-    const uint32_t xs1 = static_cast<uint32_t>(T.gx0 + min(lx0 + 1, T.tw - 1));
-    const uint32_t xn0 = xs0 + 1u == Lx ? 0u : xs0 + 1u, xn1 = xs1 + 1u == Lx ? 0u : xs1 + 1u;
-    const bool even_lx = (Lx & 1u) == 0u;
+    const uint32_t gz = static_cast<uint32_t>(T.gz0 + min(lz, T.td - 1)), gy = static_cast<uint32_t>(T.gy0 + ly0);
+    const uint32_t row0 = (gz * Ly + gy) * Lx;
+    const uint32_t dz = (gz + 1u == Lz ? 0u - gz : 1u) * (Ly * Lx);  // to the next plane (modulo 2^32)
+    const uint32_t xs0 = static_cast<uint32_t>(T.gx0 + (lx0 < T.tw ? lx0 : 0));
+    const uint32_t xs1 = static_cast<uint32_t>(T.gx0 + (lx0 + 1 < T.tw ? lx0 + 1 : 0));
+    const uint32_t hx = static_cast<uint32_t>(T.gx0 + T.tw) == Lx ? 0u : static_cast<uint32_t>(T.gx0 + T.tw);
+    const bool even_lx = FOUR || (Lx & 1u) == 0u;
+    auto pair_at = [&](uint32_t row) -> uint32_t {
+        if (even_lx) return *reinterpret_cast<const uint16_t *>(a.in + row + xs0);  // every row starts even
+        return static_cast<uint32_t>(a.in[row + xs0]) | (static_cast<uint32_t>(a.in[row + xs1]) << 8);
+    };
+    uint32_t cur[ITER + 1], zz[ITER], hl[ITER];
+#pragma unroll
+    for (int it = 0; it <= ITER; ++it) {
+        cur[it] = 0;
+        if (it < ITER) zz[it] = hl[it] = 0;
+        if (nr > 0 && (it < nr || (!LABEL && it == nr))) {
+            const bool wrap = gy + static_cast<uint32_t>(it) == Ly;
+            const uint32_t row = row0 + static_cast<uint32_t>(it) * Lx - (wrap ? Ly * Lx : 0u);
+            cur[it] = pair_at(row);
+            if (!LABEL && it < nr) {
+                zz[it] = pair_at(row + dz);
+                hl[it] = a.in[row + hx];
+            }
+        }
+    }
+    if (ragged) {
+        // sites outside the tile have no bonds: spins that differ from each
+        // other, from every byte and from the next row's (bits 8 up exceed a
+        // byte in the upper site); bond bytes 0
+#pragma unroll
+        for (int it = 0; it <= ITER; ++it) {
+            const uint32_t no0 = LABEL ? 0u : (it & 1), no1 = LABEL ? 0u : (0x102u + (it & 1)) << 8;
+            cur[it] = v1 ? cur[it] : (v0 ? cur[it] & 0xFFu : no0) | no1;
+            if (!LABEL && it < ITER && !v0) zz[it] = hl[it] = 0x80u;
+        }
+    }
+
+    // ---- bonds and labels, row by row
     // with Lx a multiple of 4 every row starts at a multiple of 4, so the two
-    // lanes of a pair share one +z block per row: in a tile full along y and
-    // z each draws the block of one of two consecutive steps' rows and the
-    // halves are swapped between the pair
-    const bool zpairs = (Lx & 3u) == 0u && T.th == CY && T.td == CZ;
+    // lanes of a pair share one +z block per row: each draws the block of one
+    // of two consecutive rows and the halves are swapped between the pair
+    constexpr bool zpairs = FOUR;
     const bool odd_lane = (lane & 1) != 0;
-    uint32_t zpend0 = 0, zpend1 = 0;  // +z words of the next step's row, drawn with this one
+    uint32_t zpend0 = 0, zpend1 = 0;  // +z words of the next row, drawn with this one
+    int lab0[ITER], lab1[ITER];       // labels of the lane's sites (byte offsets)
+    uint32_t xbit = 0, zbit = 0;      // the lane's +x bonds that leave the tile (bit it), its +z bonds (bit 2 it + j)
+    unsigned act = 0;
+    EO prevY = EO{0ull, 0ull};
+    const int own_first = 4 * (lz * PLANE + ly0 * CX) + x4;  // the lane's first site, as a byte offset
+    const int next_plane4 = 4 * (lz + 1) * PLANE;
+    const uint64_t inner = __ballot(sub < SUB - 1 && lz + 1 < T.td);  // lanes whose next plane is this wave's
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) lab0[it] = lab1[it] = 0;
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
-        const int R = row_of(it), ly = R % CY, lz = R / CY;
-        const bool rin = row_in(R);
-        const bool v0 = rin && lx0 < T.tw, v1 = rin && lx0 + 1 < T.tw;
-        const bool next_in = rin && lx0 + 2 < T.tw;  // the +x neighbour of site lx0 + 1 is the next lane's first
-        // rows outside the tile read a valid row and store nothing
-        uint32_t row, rowy, rowz;
-        if (full) {
-            // the lane's first row plus a wave-uniform offset: RPI rows a
-            // step, a plane every CY / RPI steps; the +y and +z rows follow
-            // by Lx and Lx Ly except across the lattice's own boundary
-            row = row_first + static_cast<uint32_t>(((it * RPI) / CY) * Ly + (it * RPI) % CY) * Lx;
-            rowy = ywrap_at_last && ly == CY - 1 ? row - (Ly - 1u) * Lx : row + Lx;
-            rowz = zwrap_at_last && lz == CZ - 1 ? row - (Lz - 1u) * Ly * Lx : row + Ly * Lx;
-        } else {
-            const uint32_t gy = static_cast<uint32_t>(T.gy0 + min(ly, T.th - 1));
-            const uint32_t gz = static_cast<uint32_t>(T.gz0 + min(lz, T.td - 1));
-            const uint32_t yn = gy + 1u == Ly ? 0u : gy + 1u, zn = gz + 1u == Lz ? 0u : gz + 1u;
-            row = (gz * Ly + gy) * Lx;
-            rowy = (gz * Ly + yn) * Lx;
-            rowz = (zn * Ly + gy) * Lx;
-        }
-        const uint32_t i0 = row + static_cast<uint32_t>(T.gx0 + lx0);
-        uint32_t m0 = 0, m1 = 0;
+        if (it >= nr) break;
+        const uint32_t i0 = row0 + static_cast<uint32_t>(it) * Lx + static_cast<uint32_t>(T.gx0 + lx0);
+        uint64_t mX0, mX1, mY0, mY1, mZ0, mZ1;
         if constexpr (LABEL) {
-            (void)rowy;
-            (void)rowz;
-            if (even_lx && v1) {  // the pair in one aligned 16-bit load
-                const uint32_t c = *reinterpret_cast<const uint16_t *>(a.bonds + i0);
-                m0 = c & 7u;
-                m1 = (c >> 8) & 7u;
-            } else {
-                if (v0) m0 = a.bonds[i0] & 7u;
-                if (v1) m1 = a.bonds[i0 + 1] & 7u;
-            }
+            const uint32_t c = cur[it];
+            mX0 = lanes_ne(c & 0x001u, 0u);
+            mY0 = lanes_ne(c & 0x002u, 0u);
+            mZ0 = lanes_ne(c & 0x004u, 0u);
+            mX1 = lanes_ne(c & 0x100u, 0u);
+            mY1 = lanes_ne(c & 0x200u, 0u);
+            mZ1 = lanes_ne(c & 0x400u, 0u);
         } else {
-            uint32_t s0, s1, y0, y1, z0, z1;
-            if (even_lx && v1) {  // the pair in one aligned 16-bit load per row (every row starts even)
-                const uint32_t c = *reinterpret_cast<const uint16_t *>(a.spins + row + xs0);
-                const uint32_t yy = *reinterpret_cast<const uint16_t *>(a.spins + rowy + xs0);
-                const uint32_t zz = *reinterpret_cast<const uint16_t *>(a.spins + rowz + xs0);
-                s0 = c & 0xFFu;
-                s1 = c >> 8;
-                y0 = yy & 0xFFu;
-                y1 = yy >> 8;
-                z0 = zz & 0xFFu;
-                z1 = zz >> 8;
-            } else {
-                s0 = a.spins[row + xs0];
-                s1 = a.spins[row + xs1];
-                y0 = a.spins[rowy + xs0];
-                y1 = a.spins[rowy + xs1];
-                z0 = a.spins[rowz + xs0];
-                z1 = a.spins[rowz + xs1];
-            }
+            const uint32_t s0 = cur[it] & 0xFFu, s1 = cur[it] >> 8;
+            const uint32_t y0 = cur[it + 1] & 0xFFu, y1 = cur[it + 1] >> 8;
+            const uint32_t z0 = zz[it] & 0xFFu, z1 = zz[it] >> 8;
             const uint32_t nxt = from_next_lane(s0);
-            const uint32_t x0 = v1 ? s1 : a.spins[row + xn0];
-            const uint32_t x1 = next_in ? nxt : a.spins[row + xn1];
+            const uint32_t x0 = lane_bit(L0, lane) ? hl[it] : s1;
+            const uint32_t x1 = lane_bit(L1, lane) ? hl[it] : nxt;
             // words: +x and +y from block(i >> 1, BOND) as on the square
             // lattice, +z word i & 3 of block(i >> 2, BOND_Z)
-            const uint32_t c0 = i0 >> 1;
-            const U4 bk = philox4x32_10(c0, a.t, TAG_BOND, a.sid, a.k0, a.k1);
-            uint32_t rx0, ry0, rx1, ry1;
-            if ((i0 & 1u) == 0u) {
-                rx0 = bk.v0;
-                ry0 = bk.v1;
-                rx1 = bk.v2;
-                ry1 = bk.v3;
-            } else {  // odd row start (odd Lx): i0 is the second site of its block
+            uint32_t k0 = a.k0, k1 = a.k1;  // the key schedule is recomputed per row, not held across rows
+            asm volatile("" : "+s"(k0), "+s"(k1));
+            const U4 bk = philox4x32_10(i0 >> 1, a.t, TAG_BOND, a.sid, k0, k1);
+            uint32_t rx0 = bk.v0, ry0 = bk.v1, rx1 = bk.v2, ry1 = bk.v3;
+            if (!even_lx && (i0 & 1u) != 0u) {  // odd row start: i0 is the second site of its block
                 rx0 = bk.v2;
                 ry0 = bk.v3;
-                const U4 b2 = philox4x32_10(c0 + 1u, a.t, TAG_BOND, a.sid, a.k0, a.k1);
+                const U4 b2 = philox4x32_10((i0 >> 1) + 1u, a.t, TAG_BOND, a.sid, k0, k1);
                 rx1 = b2.v0;
                 ry1 = b2.v1;
             }
             uint32_t rz0, rz1;
             if (zpairs && (it & 1) == 0) {
-                // the even lane draws its pair's block of this row, the odd lane
-                // that of the next step's row (RPI rows on, same plane, no wrap)
-                const uint32_t pair = static_cast<uint32_t>(T.gx0 + 2 * ((lane % LPR) & ~1));
-                const U4 bz = philox4x32_10((odd_lane ? row + RPI * Lx + pair : row + pair) >> 2, a.t, TAG_BOND_Z,
-                                            a.sid, a.k0, a.k1);
+                // the even lane draws its pair's block of this row, the odd
+                // lane that of the next row
+                const uint32_t pair = i0 - (odd_lane ? 2u : 0u) + (odd_lane ? Lx : 0u);
+                const U4 bz = philox4x32_10(pair >> 2, a.t, TAG_BOND_Z, a.sid, k0, k1);
                 const uint32_t ra = swap_pair_lanes(odd_lane ? bz.v0 : bz.v2);
                 const uint32_t rb = swap_pair_lanes(odd_lane ? bz.v1 : bz.v3);
                 rz0 = odd_lane ? ra : bz.v0;  // this row: words 0, 1 (even lane) or 2, 3 (odd lane)
                 rz1 = odd_lane ? rb : bz.v1;
-                zpend0 = odd_lane ? bz.v2 : ra;  // the next step's row
+                zpend0 = odd_lane ? bz.v2 : ra;  // the next row
                 zpend1 = odd_lane ? bz.v3 : rb;
             } else if (zpairs) {
                 rz0 = zpend0;
                 rz1 = zpend1;
             } else {
-                const U4 bz = philox4x32_10(i0 >> 2, a.t, TAG_BOND_Z, a.sid, a.k0, a.k1);
+                const U4 bz = philox4x32_10(i0 >> 2, a.t, TAG_BOND_Z, a.sid, k0, k1);
                 rz0 = pick(bz, i0 & 3u);
-                if (((i0 + 1u) & 3u) != 0u) {
-                    rz1 = pick(bz, (i0 + 1u) & 3u);
-                } else {  // site i0 + 1 starts the next block
-                    rz1 = philox4x32_10((i0 + 1u) >> 2, a.t, TAG_BOND_Z, a.sid, a.k0, a.k1).v0;
+                rz1 = pick(bz, (i0 + 1u) & 3u);
+                if (((i0 + 1u) & 3u) == 0u)  // site i0 + 1 starts the next block
+                    rz1 = philox4x32_10((i0 + 1u) >> 2, a.t, TAG_BOND_Z, a.sid, k0, k1).v0;
+            }
+            mX0 = lanes_eq(s0, x0) & lanes_le(rx0, a.tm1);
+            mY0 = lanes_eq(s0, y0) & lanes_le(ry0, a.tm1);
+            mZ0 = lanes_eq(s0, z0) & lanes_le(rz0, a.tm1);
+            mX1 = lanes_eq(s1, x1) & lanes_le(rx1, a.tm1);
+            mY1 = lanes_eq(s1, y1) & lanes_le(ry1, a.tm1);
+            mZ1 = lanes_eq(s1, z1) & lanes_le(rz1, a.tm1);
+            if (!a.tany) mX0 = mX1 = mY0 = mY1 = mZ0 = mZ1 = 0ull;
+            act += __popcll(mX0) + __popcll(mX1) + __popcll(mY0) + __popcll(mY1) + __popcll(mZ0) + __popcll(mZ1);
+            if (a.bonds) {
+                const uint32_t b0 = lane_bit(mX0, lane) | (lane_bit(mY0, lane) << 1) | (lane_bit(mZ0, lane) << 2);
+                const uint32_t b1 = lane_bit(mX1, lane) | (lane_bit(mY1, lane) << 1) | (lane_bit(mZ1, lane) << 2);
+                if (even_lx && v1) {
+                    *reinterpret_cast<uint16_t *>(a.bonds + i0) = static_cast<uint16_t>(b0 | (b1 << 8));
+                } else {
+                    if (v0) a.bonds[i0] = static_cast<uint8_t>(b0);
+                    if (v1) a.bonds[i0 + 1] = static_cast<uint8_t>(b1);
                 }
             }
-            if (v0 && a.tany)
-                m0 = (s0 == x0 && rx0 <= a.tm1 ? 1u : 0u) | (s0 == y0 && ry0 <= a.tm1 ? 2u : 0u) |
-                     (s0 == z0 && rz0 <= a.tm1 ? 4u : 0u);
-            if (v1 && a.tany)
-                m1 = (s1 == x1 && rx1 <= a.tm1 ? 1u : 0u) | (s1 == y1 && ry1 <= a.tm1 ? 2u : 0u) |
-                     (s1 == z1 && rz1 <= a.tm1 ? 4u : 0u);
-            act += __popc(m0) + __popc(m1);
-            if ((i0 & 1u) == 0u && v1) {
-                *reinterpret_cast<uint16_t *>(a.bonds + i0) = static_cast<uint16_t>(m0 | (m1 << 8));
-            } else {
-                if (v0) a.bonds[i0] = static_cast<uint8_t>(m0);
-                if (v1) a.bonds[i0 + 1] = static_cast<uint8_t>(m1);
-            }
         }
-        xbit |= ((m0 & 1u) | ((m1 & 1u) << 1)) << (2 * it);
-        const uint32_t in_x = (lx0 + 1 < T.tw ? 0x01u : 0u) | (lx0 + 2 < T.tw ? 0x10u : 0u);
-        const uint32_t in_y = ly + 1 < T.th ? 0x22u : 0u, in_z = lz + 1 < T.td ? 0x44u : 0u;
-        inside |= static_cast<uint64_t>((m0 | (m1 << 4)) & (in_x | in_y | in_z)) << (8 * it);
+        // bonds that leave the tile: +x of the last column, +y of the last row
+        // (the next wave's rows excepted, after the loop), +z of the last plane
+        xbit |= lane_bit((mX0 & L0) | (mX1 & L1), lane) ? 1u << it : 0u;
+        zbit |= (lane_bit(mZ0, lane) ? 1u << (2 * it) : 0u) | (lane_bit(mZ1, lane) ? 2u << (2 * it) : 0u);
+        const EO R = EO{mX0 & ~L0, mX1 & ~L1};
+        // run starts in the row, as byte offsets (the row's first site always
+        // starts a run, at offset 0)
+        const bool e_start = lane_bit(~(R.o << 1), lane);
+        const bool o_start = lane_bit(~R.e, lane);
+        const int below4 = row_max_below(o_start ? x4 + 4 : (e_start ? x4 : 0));
+        const int own = own_first + it * 4 * CX, row4 = own - x4;
+        int n0 = row4 + (e_start ? x4 : below4);
+        int n1 = o_start ? own + 4 : n0;
+        *reinterpret_cast<int2 *>(lds_entry<true>(P, own)) = make_int2(n0, n1);
+        if (it > 0) {
+            // every +y bond offers its site's label to the next row's run
+            // (one wave's LDS operations run in order; whichever offer lands
+            // last stands); a bond whose label lost needs a union
+            const int up0 = lab0[it > 0 ? it - 1 : 0], up1 = lab1[it > 0 ? it - 1 : 0];
+            wave_lds_fence();
+            if (lane_bit(prevY.e, lane)) lds_st(lds_entry<true>(P, n0), up0);
+            if (lane_bit(prevY.o, lane)) lds_st(lds_entry<true>(P, n1), up1);
+            wave_lds_fence();
+            n0 = lds_ld(lds_entry<true>(P, n0));
+            n1 = lds_ld(lds_entry<true>(P, n1));
+            *reinterpret_cast<int2 *>(lds_entry<true>(P, own)) = make_int2(n0, n1);
+            append(EO{lanes_ne(static_cast<uint32_t>(n0), static_cast<uint32_t>(up0)) & prevY.e,
+                      lanes_ne(static_cast<uint32_t>(n1), static_cast<uint32_t>(up1)) & prevY.o},
+                   own - 4 * CX);
+        }
+        lab0[it] = n0;
+        lab1[it] = n1;
+        prevY = EO{mY0, mY1};
+        {
+            // +z bonds to the wave's next plane (the lanes of the next group):
+            // a label there that is still a root is linked below this one
+            const EO Z = EO{mZ0 & inner, mZ1 & inner};
+            wave_lds_fence();
+            int got0 = -1, got1 = -1, up0 = 0, up1 = 0;
+            if (sub < SUB - 1) {
+                up0 = lds_ld(lds_entry<true>(P, own + 4 * PLANE));
+                up1 = lds_ld(lds_entry<true>(P, own + 4 * PLANE + 4));
+            }
+            if (lane_bit(Z.e, lane) && up0 >= next_plane4) got0 = link_root(P, up0, n0);
+            if (lane_bit(Z.o, lane) && up1 >= next_plane4) got1 = link_root(P, up1, n1);
+            const EO met = EO{lanes_eq(static_cast<uint32_t>(got0), static_cast<uint32_t>(up0)) |
+                                  lanes_eq(static_cast<uint32_t>(got0), static_cast<uint32_t>(n0)),
+                              lanes_eq(static_cast<uint32_t>(got1), static_cast<uint32_t>(up1)) |
+                                  lanes_eq(static_cast<uint32_t>(got1), static_cast<uint32_t>(n1))};
+            append(eo_andnot(Z, met), own | 1);
+        }
     }
+    if (sub == SUB - 1) zb[w][lane % LPR] = zin && lz + 1 < T.td ? zbit : 0u;
     __syncthreads();
 
-    // unions of the bonds inside the tile, one flat loop per lane: a finished
-    // union takes the lane's next bond at once
-    {
-        uint64_t todo = inside;
-        int u = 0, v = 0, busy = 0;
-        while (busy || todo) {
-            if (!busy) {
-                const int bit = __ffsll(static_cast<unsigned long long>(todo)) - 1;
-                todo &= todo - 1;
-                const int it = bit >> 3, j = (bit >> 2) & 1, d = bit & 3;
-                u = row_of(it) * CX + lx0 + j;
-                v = u + (d == 0 ? 1 : d == 1 ? CX : PLANE);
-                busy = 1;
-            }
-            int done;
-            unite_step(P, u, v, done);
-            busy = !done;
-        }
-    }
-    __syncthreads();
-
-    // Every site's root, walked once (the trees are final after the unions)
-    // and kept in registers for the claims and the codes.  Other waves may
-    // already be claiming: a claimed root's entry is negative, and the walk
-    // ends there too.
-    auto root_of = [&](int x) {
-        for (;;) {
-            const int p = lds_ld(&P[x]);
-            if (p == x || p < 0) return x;
-            x = p;
-        }
+    // ---- bonds to other waves' rows and planes, then all unions
+    auto link_across = [&](EO m, int own, int up4, int n0, int n1, int dir) {
+        // the sites at `own` with labels n0, n1 and bonds m to the sites
+        // `up4` bytes on; labels there below their first slot are left to the list
+        const int q0 = lds_ld(lds_entry<true>(P, own + up4)), q1 = lds_ld(lds_entry<true>(P, own + up4 + 4));
+        const int first = dir == 0 ? own + up4 - x4 : (own + up4) & ~(4 * PLANE - 1);
+        int got0 = -1, got1 = -1;
+        if (lane_bit(m.e, lane) && q0 >= first) got0 = link_root(P, q0, n0);
+        if (lane_bit(m.o, lane) && q1 >= first) got1 = link_root(P, q1, n1);
+        const EO met = EO{lanes_eq(static_cast<uint32_t>(got0), static_cast<uint32_t>(q0)) |
+                              lanes_eq(static_cast<uint32_t>(got0), static_cast<uint32_t>(n0)),
+                          lanes_eq(static_cast<uint32_t>(got1), static_cast<uint32_t>(q1)) |
+                              lanes_eq(static_cast<uint32_t>(got1), static_cast<uint32_t>(n1))};
+        append(eo_andnot(m, met), own | dir);
     };
-    int rt[ITER][2];
+    if (nr == ITER && ly0 + ITER < T.th)  // the y range's second half
+        link_across(prevY, own_first + (ITER - 1) * 4 * CX, 4 * CX, lab0[ITER - 1], lab1[ITER - 1], 0);
+    {
+        // the wave's last plane to the next wave's first: RPI rows a step
+        const int lz_last = (w >> 1) * SUB + SUB - 1;
 #pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-        const int R = row_of(it);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            rt[it][j] = 0;
-            if (row_in(R) && lx0 + j < T.tw) rt[it][j] = root_of(R * CX + lx0 + j);
+        for (int s = 0; s < ITER / RPI; ++s) {
+            const int it = s * RPI + sub;
+            const uint32_t z = zb[w][lane % LPR] >> (2 * it);
+            const EO m = EO{lanes_ne(z & 1u, 0u), lanes_ne(z & 2u, 0u)};
+            if ((m.e | m.o) == 0ull) continue;
+            const int own = 4 * (lz_last * PLANE + (ly0 + it) * CX) + x4;
+            const int n0 = lds_ld(lds_entry<true>(P, own)), n1 = lds_ld(lds_entry<true>(P, own + 4));
+            link_across(m, own, 4 * PLANE, n0, n1, 1);
         }
     }
-    // claims: the root of every cluster that touches a tile face gets an id
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-        const int R = row_of(it), ly = R % CY, lz = R / CY;
-        if (!row_in(R)) continue;
-        const bool plane_face = ly == 0 || ly == T.th - 1 || lz == 0 || lz == T.td - 1;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int lx = lx0 + j;
-            if (lx >= T.tw || !(plane_face || lx == 0 || lx == T.tw - 1)) continue;
-            const int r = rt[it][j];
-            int expect = r;
-            if (__hip_atomic_compare_exchange_strong(&P[r], &expect, CLAIMING, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                const int k = atomicAdd(&nb_s, 1);
-                lds_st(&P[r], -(k + 2));
-                const int id = T.tile * CAP + k;
-                a.gkey[id] = site_of(g, T, r);
-                a.gparent[id] = id;
-            }
+    unite_list(ncon);
+    __syncthreads();
+
+    // ---- claims: the root of every cluster that touches a tile face gets an id
+    for (int t = threadIdx.x; t < FACES; t += NT3) {
+        const int slot = face_slot(t, T);
+        if (slot < 0) continue;
+        const int r4 = lroot(P, 4 * slot);
+        int expect = r4;
+        if (__hip_atomic_compare_exchange_strong(lds_entry<true>(P, r4), &expect, CLAIMING, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
+            const int k = atomicAdd(&nb_s, 1);
+            lds_st(lds_entry<true>(P, r4), final_entry(static_cast<uint32_t>(CSITES + k)));
+            const int id = T.tile * CAP + k;
+            a.gkey[id] = site_of(g, T, r4 >> 2);
+            a.gparent[id] = id;
         }
     }
     __syncthreads();
 
-    // codes: the id of a claimed root (its entry reads -(id + 2)), else CAP +
-    // the root's slot
+    // ---- every linked label gets its cluster's final entry (as in the
+    // square-lattice tile: a walk ends at a claimed root, at a label another
+    // lane has finished, or at an unclaimed root, its own parent)
+    auto compress_list = [&](int n) {
+        wave_lds_fence();
+        int i = lane, s0 = 0, x = 0;
+        if (i < n) s0 = x = mylist[i];
+        while (i < n) {
+            const int p = lds_ld(lds_entry<true>(P, x));
+            if (p >= 0 && p != x) {
+                x = p;
+            } else {
+                lds_st(lds_entry<true>(P, s0), p | static_cast<int>(0x80000000u));
+                i += 64;
+                if (i < n) s0 = x = mylist[i];
+            }
+        }
+        wave_lds_fence();
+    };
+    int nls = 0;
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) {
+        if (it >= nr) break;
+        if (nls > TL3 - 128) {
+            compress_list(nls);
+            nls = 0;
+        }
+        // a label site whose entry is an offset below its own (a final entry
+        // is negative, above every offset as an unsigned number)
+        const uint32_t own = static_cast<uint32_t>(own_first + it * 4 * CX);
+        const int2 p = *reinterpret_cast<const int2 *>(lds_entry<true>(P, static_cast<int>(own)));
+        const EO linked = EO{lanes_eq(static_cast<uint32_t>(lab0[it]), own) & lanes_lt(static_cast<uint32_t>(p.x), own),
+                             lanes_eq(static_cast<uint32_t>(lab1[it]), own + 4) &
+                                 lanes_lt(static_cast<uint32_t>(p.y), own + 4)};
+        eo_append(mylist, nls, linked, static_cast<int>(own), static_cast<int>(own + 4));
+    }
+    compress_list(nls);
+    __syncthreads();
+
+    // ---- codes: the entry of the site's label; on the tile's last row the +y
+    // bond in bit 15, on its last plane the +z bond in bit 14 (all such sites
+    // carry ids)
     {
-        uint16_t *codes = a.codes + static_cast<int64_t>(T.tile) * CSITES;
+        uint32_t *codes32 = reinterpret_cast<uint32_t *>(a.codes + static_cast<int64_t>(T.tile) * CSITES) +
+                            w * ITER * 64 + lane;
+        uint16_t *xf = a.xface + static_cast<int64_t>(T.tile) * (2 * FX) + lz * CY + ly0;
+        const bool z_last = lz == T.td - 1;
 #pragma unroll
         for (int it = 0; it < ITER; ++it) {
-            const int R = row_of(it);
-            if (!row_in(R)) continue;
-            const int s = R * CX + lx0;
-            uint32_t c[2] = {CODE_NONE, CODE_NONE};
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                if (lx0 + j >= T.tw) continue;
-                const int r = rt[it][j];
-                const int pr = lds_ld(&P[r]);
-                c[j] = pr < 0 ? static_cast<uint32_t>(-pr - 2) : static_cast<uint32_t>(CAP + r);
+            if (it >= nr) break;
+            const uint32_t c0 = entry_code(lds_ld(lds_entry<true>(P, lab0[it])));
+            const uint32_t c1 = entry_code(lds_ld(lds_entry<true>(P, lab1[it])));
+            uint32_t c = c0 | (c1 << 16);
+            if (ly0 + it == T.th - 1)
+                c |= (lane_bit(prevY.e, lane) ? 0x8000u : 0u) | (lane_bit(prevY.o, lane) ? 0x80000000u : 0u);
+            if (z_last) c |= ((zbit >> (2 * it)) & 1u) << 14 | ((zbit >> (2 * it + 1)) & 1u) << 30;
+            codes32[it * 64] = c;
+            // the x faces' ids again, packed by row (the merge reads them
+            // whole); a row's x-face position is lz CY + ly
+            if (zin) {
+                const int jl = T.tw - 1 - lx0;
+                if (lx0 == 0) xf[it] = static_cast<uint16_t>(c0 - CSITES);
+                if (jl == 0 || jl == 1)
+                    xf[FX + it] = static_cast<uint16_t>(((jl == 0 ? c0 : c1) - CSITES) | (((xbit >> it) & 1u) << 15));
             }
-            *reinterpret_cast<uint32_t *>(codes + s) = c[0] | (c[1] << 16);
-            // the x faces again, packed by row (the merge reads them whole);
-            // a row's x-face position is its tile row R
-            uint16_t *xf = a.xface + static_cast<int64_t>(T.tile) * (2 * FX);
-            if (lx0 == 0) xf[R] = static_cast<uint16_t>(c[0]);
-            const int jl = T.tw - 1 - lx0;
-            if (jl == 0 || jl == 1)
-                xf[FX + R] = static_cast<uint16_t>((jl == 0 ? c[0] : c[1]) | (((xbit >> (2 * it + jl)) & 1u) << 15));
         }
     }
-    const unsigned long long tot = wave_sum(act);
-    if (lane == 0) act_w[w] = static_cast<unsigned>(tot);
+    if (lane == 0) act_w[w] = act;
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned sum = 0;
@@ -395,7 +558,6 @@ __global__ __launch_bounds__(NT3) void k3_tile(Tile3Args a)
 
 struct Merge3Args {
     Geo3 g;
-    const uint8_t *bonds;
     const uint16_t *codes;
     const uint16_t *xface;  // as written by k3_tile
     int32_t *gparent;
@@ -440,8 +602,8 @@ __device__ __forceinline__ void gunite_prio(int *G, int a, int b)
 // +z face joins the ids of its two ends (both are face sites, hence claimed).
 // Every face has one neighbouring tile, so (face, id, id across) names a
 // union.  The workgroup first gathers its distinct unions into a list (the
-// bond bits of all its face positions loaded at once, then the codes of the
-// active ones, duplicates dropped), then works the list off with every lane
+// codes of all its face positions, which carry the bond bits, loaded at once,
+// then the codes across the active ones, duplicates dropped), then works the list off with every lane
 // busy: a lane no longer waits for its wave's deepest union at each of its
 // face positions.
 constexpr int MPOS = (FX + FY + FZ + MT - 1) / MT;  // face positions per merge thread
@@ -464,59 +626,58 @@ __global__ __launch_bounds__(MT) void k3_merge(Merge3Args a)
     const int nbr[3] = {(tz * g.nty + ty) * g.ntx + (tx + 1 == g.ntx ? 0 : tx + 1),
                         (tz * g.nty + (ty + 1 == g.nty ? 0 : ty + 1)) * g.ntx + tx,
                         ((tz + 1 == g.ntz ? 0 : tz + 1) * g.nty + ty) * g.ntx + tx};
-    // site index and the neighbour's slot of face position f, or -1
-    auto face = [&](int f, int &d, int &s1, int &s2) -> int64_t {
+    // face position f: its direction, and the positions of its site's code and
+    // of the code across the face; false outside a ragged tile
+    auto face = [&](int f, int &d, int &s1, int &s2) -> bool {
         int lx, ly, lz;
         if (f < FX) {
             d = 0;
             lx = T.tw - 1;
             ly = f % CY;
             lz = f / CY;
+            s1 = FX + f;  // in the packed x faces
+            s2 = f;
         } else if (f < FX + FY) {
             d = 1;
             lx = (f - FX) % CX;
             ly = T.th - 1;
             lz = (f - FX) / CX;
+            s1 = code_pos(lx, ly, lz);
+            s2 = code_pos(lx, 0, lz);
         } else {
             d = 2;
             lx = (f - FX - FY) % CX;
             ly = (f - FX - FY) / CX;
             lz = T.td - 1;
+            s1 = code_pos(lx, ly, lz);
+            s2 = code_pos(lx, ly, 0);
         }
-        if (f >= FX + FY + FZ || lx >= T.tw || ly >= T.th || lz >= T.td) return -1;
-        s1 = (lz * CY + ly) * CX + lx;
-        // across the face the neighbour sits at coordinate 0 of that axis
-        s2 = d == 0 ? (lz * CY + ly) * CX : d == 1 ? lz * PLANE + lx : ly * CX + lx;
-        return (static_cast<int64_t>(T.gz0 + lz) * g.Ly + T.gy0 + ly) * g.Lx + T.gx0 + lx;
+        return f < FX + FY + FZ && lx < T.tw && ly < T.th && lz < T.td;
     };
     int ca[MPOS], cb[MPOS], dd[MPOS];
     bool act[MPOS];
 #pragma unroll
-    for (int j = 0; j < MPOS; ++j) {  // every bond bit first (independent loads)
+    for (int j = 0; j < MPOS; ++j) {  // every own code, its bond bit with it, first (independent loads)
         int s1, s2;
         const int f = j * MT + static_cast<int>(threadIdx.x);
-        const int64_t i = face(f, dd[j], s1, s2);
-        if (dd[j] == 0) {  // the +x face from the packed x faces: bond bit and code at once
-            const uint32_t h = i >= 0 ? a.xface[static_cast<int64_t>(T.tile) * (2 * FX) + FX + f] : 0u;
-            act[j] = ((h >> 15) & 1u) != 0u;
-            ca[j] = static_cast<int>(h & 0x7FFFu);
-            cb[j] = f;
-        } else {
-            act[j] = i >= 0 && ((a.bonds[i] >> dd[j]) & 1u);
-            ca[j] = s1;
-            cb[j] = s2;
-        }
+        const bool in = face(f, dd[j], s1, s2);
+        uint32_t c = 0;
+        if (in)
+            c = dd[j] == 0 ? a.xface[static_cast<int64_t>(T.tile) * (2 * FX) + s1]
+                           : a.codes[static_cast<int64_t>(T.tile) * CSITES + s1];
+        act[j] = ((c >> (dd[j] == 2 ? 14 : 15)) & 1u) != 0u;
+        ca[j] = dd[j] == 0 ? static_cast<int>(c & 0x7FFFu) : static_cast<int>(c & CODE_MASK) - CSITES;
+        cb[j] = s2;
     }
 #pragma unroll
-    for (int j = 0; j < MPOS; ++j) {  // then the codes of the active ones
+    for (int j = 0; j < MPOS; ++j) {  // then the codes across the active ones
         if (!act[j]) continue;
-        if (dd[j] == 0) {
+        if (dd[j] == 0)
             cb[j] = a.xface[static_cast<int64_t>(nbr[0]) * (2 * FX) + cb[j]];
-        } else {
-            ca[j] = a.codes[static_cast<int64_t>(T.tile) * CSITES + ca[j]];
-            cb[j] = a.codes[static_cast<int64_t>(nbr[dd[j]]) * CSITES + cb[j]];
-        }
-        if (ca[j] >= CAP || cb[j] >= CAP) act[j] = false;  // face sites always hold ids
+        else
+            cb[j] = static_cast<int>(a.codes[static_cast<int64_t>(nbr[dd[j]]) * CSITES + cb[j]] & CODE_MASK) - CSITES;
+        if (static_cast<unsigned>(ca[j]) >= CAP || static_cast<unsigned>(cb[j]) >= CAP)
+            act[j] = false;  // face sites always hold ids
     }
     __syncthreads();  // seen and nlist are set
 #pragma unroll
@@ -599,71 +760,88 @@ __global__ __launch_bounds__(RT) void k3_resolve(Resolve3Args a)
 template <bool LABEL>
 __global__ __launch_bounds__(NT3) void k3_flatten(Flat3Args a)
 {
-    __shared__ uint8_t ST[CAP + CSITES];          // new state per code
+    constexpr uint32_t NCODE = CSITES + CAP;
+    __shared__ uint8_t ST[NCODE];                 // new state per code
     __shared__ int32_t Rb[CAP];                   // canonical label per id (labels only)
     __shared__ uint16_t roots[NW3][128 * ITER];   // interior root slots of each wave's rows
     __shared__ unsigned ncl_w[NW3];
     const Geo3 g = a.g;
     const TileOf T = tile_of(g, xcd_remap(blockIdx.x, g.ntiles));
     const int lane = threadIdx.x & 63, w = wave_id();
-    const int sub = lane / LPR, lx0 = 2 * (lane % LPR);
-    auto row_of = [&](int it) { return w * RW + it * RPI + sub; };
-    auto row_in = [&](int R) { return R % CY < T.th && R / CY < T.td; };
+    // the tile kernel's lanes: two sites of plane lz, rows ly0 ...
+    const int lx0 = 2 * (lane % LPR), lz = (w >> 1) * SUB + lane / LPR, ly0 = (w & 1) * ITER;
+    const int nr = max(0, min(ITER, T.th - ly0));
+    const bool v0 = lz < T.td && lx0 < T.tw, v1 = lz < T.td && lx0 + 1 < T.tw;
     const int nbt = a.nb[T.tile];
     unsigned nbroot = 0;
     for (int k = threadIdx.x; k < nbt; k += NT3) {
         const int id = T.tile * CAP + k;
         const int r = a.gparent[id];  // resolved: the entry is the root
         const int32_t key = a.gkey[r];
-        if constexpr (!LABEL) ST[k] = static_cast<uint8_t>(new_state(static_cast<uint32_t>(key), a));
+        if constexpr (!LABEL) ST[CSITES + k] = static_cast<uint8_t>(new_state(static_cast<uint32_t>(key), a));
         Rb[k] = key;
         nbroot += r == id ? 1u : 0u;
     }
-    // the lane's codes (two per step); the interior roots (code CAP + own
-    // slot) of the wave's rows are listed, then draw their states 64 at a time
-    const uint16_t *codes = a.codes + static_cast<int64_t>(T.tile) * CSITES;
+    // the lane's codes (two per step); the interior roots (code: own slot) of
+    // the wave's rows are listed, then draw their states 64 at a time
+    const uint32_t *codes32 = reinterpret_cast<const uint32_t *>(a.codes + static_cast<int64_t>(T.tile) * CSITES) +
+                              w * ITER * 64 + lane;
+    const uint64_t in0 = __ballot(v0), in1 = __ballot(v1);
+    const int own_first = lz * PLANE + ly0 * CX + lx0;
     uint32_t cc[ITER];
     int nroot = 0;
     uint16_t *mylist = roots[w];
-    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) cc[it] = it < nr ? codes32[it * 64] & (CODE_MASK | CODE_MASK << 16) : 0u;
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
-        const int R = row_of(it);
-        const bool rin = row_in(R);
-        const bool v0 = rin && lx0 < T.tw, v1 = rin && lx0 + 1 < T.tw;
-        const int s = R * CX + lx0;
-        cc[it] = rin ? *reinterpret_cast<const uint32_t *>(codes + s) : 0xFFFFFFFFu;
-        const bool r0 = v0 && (cc[it] & 0xFFFFu) == static_cast<uint32_t>(CAP + s);
-        const bool r1 = v1 && (cc[it] >> 16) == static_cast<uint32_t>(CAP + s + 1);
-        const uint64_t m0 = __ballot(r0), m1 = __ballot(r1);
-        const int at = nroot + __popcll(m0 & below) + __popcll(m1 & below);
-        if (r0) mylist[at] = static_cast<uint16_t>(s);
-        if (r1) mylist[at + (r0 ? 1 : 0)] = static_cast<uint16_t>(s + 1);
-        nroot += __popcll(m0) + __popcll(m1);
+        if (it >= nr) break;
+        const int s = own_first + it * CX;
+        const EO m = EO{lanes_eq(cc[it] & 0xFFFFu, static_cast<uint32_t>(s)) & in0,
+                        lanes_eq(cc[it] >> 16, static_cast<uint32_t>(s + 1)) & in1};
+        eo_append(mylist, nroot, m, s, s + 1);
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    wave_lds_fence();
     if constexpr (!LABEL) {
         for (int k = lane; k < nroot; k += 64) {
             const int s = mylist[k];
-            ST[CAP + s] = static_cast<uint8_t>(new_state(static_cast<uint32_t>(site_of(g, T, s)), a));
+            ST[s] = static_cast<uint8_t>(new_state(static_cast<uint32_t>(site_of(g, T, s)), a));
         }
     }
     __syncthreads();
+    const bool even_lx = (g.Lx & 1) == 0;  // every row starts even: both sites in one store
+    const uint32_t i_first = (static_cast<uint32_t>(T.gz0 + lz) * static_cast<uint32_t>(g.Ly) +
+                              static_cast<uint32_t>(T.gy0 + ly0)) * static_cast<uint32_t>(g.Lx) +
+                             static_cast<uint32_t>(T.gx0 + lx0);
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
-        const int R = row_of(it), ly = R % CY, lz = R / CY;
-        if (!row_in(R)) continue;
-        const int64_t i0 = (static_cast<int64_t>(T.gz0 + lz) * g.Ly + T.gy0 + ly) * g.Lx + T.gx0 + lx0;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            if (lx0 + j >= T.tw) continue;
-            const uint32_t c = (cc[it] >> (16 * j)) & 0xFFFFu;
-            if constexpr (!LABEL) {
-                const uint32_t st = ST[c];
-                a.spins[i0 + j] = static_cast<uint8_t>(a.ising ? 2u * st - 1u : st);
+        if (it >= nr) break;
+        const uint32_t i0 = i_first + static_cast<uint32_t>(it) * static_cast<uint32_t>(g.Lx);
+        const uint32_t c0 = cc[it] & 0xFFFFu, c1 = cc[it] >> 16;
+        if constexpr (!LABEL) {
+            // (the sites outside a ragged tile carry some code: looked up
+            // inside the table, never stored)
+            const uint32_t st0 = ST[min(c0, NCODE - 1u)], st1 = ST[min(c1, NCODE - 1u)];
+            const uint32_t b0 = a.ising ? (2u * st0 - 1u) & 0xFFu : st0, b1 = a.ising ? (2u * st1 - 1u) & 0xFFu : st1;
+            if (even_lx) {
+                if (v1) *reinterpret_cast<uint16_t *>(a.spins + i0) = static_cast<uint16_t>(b0 | (b1 << 8));
+            } else {
+                if (v0) a.spins[i0] = static_cast<uint8_t>(b0);
+                if (v1) a.spins[i0 + 1] = static_cast<uint8_t>(b1);
             }
-            if (a.labels)
-                a.labels[i0 + j] = c < static_cast<uint32_t>(CAP) ? Rb[c] : site_of(g, T, static_cast<int>(c) - CAP);
+        }
+        if (a.labels) {
+            auto label = [&](uint32_t c) {
+                return c >= static_cast<uint32_t>(CSITES) ? Rb[min(c, NCODE - 1u) - CSITES]
+                                                          : site_of(g, T, static_cast<int>(c));
+            };
+            const int32_t R0 = label(c0), R1 = label(c1);
+            if (even_lx) {
+                if (v1) *reinterpret_cast<int2 *>(a.labels + i0) = make_int2(R0, R1);
+            } else {
+                if (v0) a.labels[i0] = R0;
+                if (v1) a.labels[i0 + 1] = R1;
+            }
         }
     }
     const unsigned long long tot = wave_sum(nbroot);
@@ -775,7 +953,7 @@ int64_t cdiv3(int64_t a, int64_t b) { return (a + b - 1) / b; }
 struct Layout3 {
     Geo3 g;
     int64_t N;
-    size_t codes, xface, gkey, gparent, nb, tile_act, tile_ncl, stats, bonds, total;
+    size_t codes, xface, gkey, gparent, nb, tile_act, tile_ncl, stats, total;
 };
 
 // Extents >= 1, N < 2^31, and the ids of all tiles (ntiles x CAP) index
@@ -800,7 +978,7 @@ sw_status check3(const sw3_params *p)
     return check_shape3(p->Lx, p->Ly, p->Lz);
 }
 
-Layout3 layout3(int32_t Lx, int32_t Ly, int32_t Lz, bool own_bonds = true)
+Layout3 layout3(int32_t Lx, int32_t Ly, int32_t Lz)
 {
     Layout3 L{};
     L.g.Lx = Lx;
@@ -826,12 +1004,21 @@ Layout3 layout3(int32_t Lx, int32_t Ly, int32_t Lz, bool own_bonds = true)
     L.tile_act = take(nt * sizeof(int32_t));
     L.tile_ncl = take(nt * sizeof(int32_t));
     L.stats = take(16 * sizeof(unsigned long long));
-    L.bonds = own_bonds ? take(static_cast<size_t>(L.N)) : 0;
     L.total = off;
     return L;
 }
 
 Layout3 layout3(const sw3_params *p) { return layout3(p->Lx, p->Ly, p->Lz); }
+
+template <bool LABEL>
+void launch_tile3(const Tile3Args &ta, hipStream_t s)
+{
+    const dim3 tiles(static_cast<unsigned>(ta.g.ntiles));
+    if (ta.g.Lx % 4 == 0)
+        hipLaunchKernelGGL((k3_tile<LABEL, true>), tiles, dim3(NT3), 0, s, ta);
+    else
+        hipLaunchKernelGGL((k3_tile<LABEL, false>), tiles, dim3(NT3), 0, s, ta);
+}
 
 template <typename T>
 T *at3(void *ws, size_t off)
@@ -862,7 +1049,7 @@ sw_status sw3_init_spins(const sw3_params *p, uint8_t *spins, void *stream)
 size_t ccl3_workspace_bytes(int32_t Lx, int32_t Ly, int32_t Lz)
 {
     if (check_shape3(Lx, Ly, Lz) != SW_OK) return 0;
-    return layout3(Lx, Ly, Lz, false).total;
+    return layout3(Lx, Ly, Lz).total;
 }
 
 sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, int32_t *labels, int32_t *n_clusters,
@@ -871,14 +1058,14 @@ sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, i
     const sw_status st = check_shape3(Lx, Ly, Lz);
     if (st != SW_OK) return st;
     if (!bonds || !labels) return SW_ERR_ARG;
-    const Layout3 L = layout3(Lx, Ly, Lz, false);
+    const Layout3 L = layout3(Lx, Ly, Lz);
     if (!workspace || workspace_bytes < L.total || reinterpret_cast<uintptr_t>(workspace) % ALIGN3)
         return SW_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     unsigned long long *stats = at3<unsigned long long>(workspace, L.stats);
     Tile3Args ta{};
     ta.g = L.g;
-    ta.bonds = const_cast<uint8_t *>(bonds);  // LABEL mode only reads them
+    ta.in = bonds;
     ta.codes = at3<uint16_t>(workspace, L.codes);
     ta.xface = at3<uint16_t>(workspace, L.xface);
     ta.gkey = at3<int32_t>(workspace, L.gkey);
@@ -888,7 +1075,6 @@ sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, i
     ta.tany = 1u;
     Merge3Args ma{};
     ma.g = L.g;
-    ma.bonds = bonds;
     ma.codes = ta.codes;
     ma.xface = ta.xface;
     ma.gparent = ta.gparent;
@@ -906,7 +1092,7 @@ sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, i
     fa.nb = ta.nb;
     fa.tile_ncl = at3<int32_t>(workspace, L.tile_ncl);
     const dim3 tiles(static_cast<unsigned>(L.g.ntiles));
-    hipLaunchKernelGGL(k3_tile<true>, tiles, dim3(NT3), 0, s, ta);
+    launch_tile3<true>(ta, s);
     hipLaunchKernelGGL(k3_merge, tiles, dim3(MT), 0, s, ma);
     hipLaunchKernelGGL(k3_resolve, tiles, dim3(RT), 0, s, ra);
     hipLaunchKernelGGL(k3_flatten<true>, tiles, dim3(NT3), 0, s, fa);
@@ -934,8 +1120,8 @@ sw_status sw3_sweep(const sw3_params *p, uint8_t *spins, uint32_t t0, int32_t n,
 
     Tile3Args ta{};
     ta.g = L.g;
-    ta.spins = spins;
-    ta.bonds = bonds ? bonds : at3<uint8_t>(workspace, L.bonds);
+    ta.in = spins;
+    ta.bonds = bonds;
     ta.codes = at3<uint16_t>(workspace, L.codes);
     ta.xface = at3<uint16_t>(workspace, L.xface);
     ta.gkey = at3<int32_t>(workspace, L.gkey);
@@ -950,7 +1136,6 @@ sw_status sw3_sweep(const sw3_params *p, uint8_t *spins, uint32_t t0, int32_t n,
 
     Merge3Args ma{};
     ma.g = L.g;
-    ma.bonds = ta.bonds;
     ma.codes = ta.codes;
     ma.xface = ta.xface;
     ma.gparent = ta.gparent;
@@ -984,7 +1169,7 @@ sw_status sw3_sweep(const sw3_params *p, uint8_t *spins, uint32_t t0, int32_t n,
         ta.t = t;
         fa.t = t;
         fa.labels = k + 1 == n ? labels : nullptr;
-        hipLaunchKernelGGL(k3_tile<false>, tiles, dim3(NT3), 0, s, ta);
+        launch_tile3<false>(ta, s);
         hipLaunchKernelGGL(k3_merge, tiles, dim3(MT), 0, s, ma);
         hipLaunchKernelGGL(k3_resolve, tiles, dim3(RT), 0, s, ra);
         hipLaunchKernelGGL(k3_flatten<false>, tiles, dim3(NT3), 0, s, fa);

@@ -193,40 +193,6 @@ struct TileArgs {
                               // rk[2r], rk[2r + 1]
 };
 
-// A tile row as two wave ballots: lane L owns sites 2L and 2L+1, bit L of `e`
-// belongs to site 2L and bit L of `o` to site 2L+1.  The masks stay in scalar
-// registers; the natural-order shift s -> s+1 is (o << 1, e).
-struct EO {
-    uint64_t e, o;
-};
-
-__device__ __forceinline__ EO eo_andnot(EO a, EO b) { return EO{a.e & ~b.e, a.o & ~b.o}; }
-
-// Set bits of m at lanes below the calling lane.
-__device__ __forceinline__ int lanes_below(uint64_t m)
-{
-    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
-}
-
-// Append the calling lanes' entries to a wave list: ve for the lanes of m.e,
-// then vo for those of m.o (the order does not matter); n is the wave-uniform
-// list length.
-__device__ __forceinline__ void eo_append(uint16_t *list, int &n, EO m, int ve, int vo)
-{
-    const auto at = [](uint64_t mask, int from) {
-        return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
-                                                          __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask),
-                                                                                    static_cast<uint32_t>(from))));
-    };
-    const int pe = at(m.e, n);
-    n += __popcll(m.e);
-    const int po = at(m.o, n);
-    n += __popcll(m.o);
-    if (lane_bit(m.e, 0)) list[pe] = static_cast<uint16_t>(ve);
-    if (lane_bit(m.o, 0)) list[po] = static_cast<uint16_t>(vo);
-}
-
 // Wave-uniform copy of a mask read from LDS.
 __device__ __forceinline__ uint64_t uniform64(uint64_t v)
 {
@@ -239,17 +205,6 @@ template <typename T>
 __device__ __forceinline__ T *uniform_ptr(T *p)
 {
     return reinterpret_cast<T *>(static_cast<uintptr_t>(uniform64(static_cast<uint64_t>(reinterpret_cast<uintptr_t>(p)))));
-}
-
-// Root of x (a byte offset, as the tile kernel's parents) once all unions are
-// done; a claimed root (negative entry) is a root.
-__device__ __forceinline__ int lroot(int *P, int x)
-{
-    for (;;) {
-        const int p = lds_ld(lds_entry<true>(P, x));
-        if (p == x || p < 0) return x;
-        x = p;
-    }
 }
 
 // Border position t of a tile in the layout of the edge arrays: top row,
@@ -266,19 +221,7 @@ __device__ __forceinline__ int border_slot(int t, int tw, int th)
 
 // A site's 16-bit code: the slot of its cluster's root inside the tile
 // (0 .. TSITES - 1), or TSITES + k for the cluster of boundary id k, or
-// CODE_BG.  Entries that are done hold FINAL | code << 2 (negative); the entry
-// of an unclaimed root, its own byte offset 4 slot, gives its code by the same
-// two-bit shift.  P[root] = CLAIMING while a root's id is allocated.
-constexpr int CLAIMING = -1;
-__device__ __forceinline__ int final_entry(uint32_t code) { return static_cast<int>(0x80000000u | (code << 2)); }
-__device__ __forceinline__ uint32_t entry_code(int e) { return (static_cast<uint32_t>(e) >> 2) & 0xFFFFu; }
-
-// Lane masks: bit L describes lane L (uicmp yields the mask of one compare).
-constexpr int CMP_EQ = 32, CMP_NE = 33, CMP_ULT = 36, CMP_ULE = 37;
-__device__ __forceinline__ uint64_t lanes_eq(uint32_t x, uint32_t y) { return __builtin_amdgcn_uicmp(x, y, CMP_EQ); }
-__device__ __forceinline__ uint64_t lanes_ne(uint32_t x, uint32_t y) { return __builtin_amdgcn_uicmp(x, y, CMP_NE); }
-__device__ __forceinline__ uint64_t lanes_lt(uint32_t x, uint32_t y) { return __builtin_amdgcn_uicmp(x, y, CMP_ULT); }
-__device__ __forceinline__ uint64_t lanes_le(uint32_t x, uint32_t y) { return __builtin_amdgcn_uicmp(x, y, CMP_ULE); }
+// CODE_BG.
 
 // Maximum of v over the lanes below the calling one (0 for lane 0), v >= 0:
 // an inclusive max-scan by row shifts and row broadcasts, then a shift by one
@@ -478,9 +421,10 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
     int lab0[RPW], lab1[RPW];  // labels of the lane's sites (byte offsets), BG4 for background
     EO prevD = EO{0ull, 0ull};
 #pragma unroll
+    for (int r = 0; r < RPW; ++r) lab0[r] = lab1[r] = BG4;
+#pragma unroll
     for (int r = 0; r < RPW; ++r) {
-        lab0[r] = lab1[r] = BG4;
-        if (r >= nr) continue;
+        if (r >= nr) break;
         const int ly = ly0 + r;
         const int gy = gy0 + ly;
         const uint32_t cur = pr[r], dn = pr[r + 1];
@@ -634,15 +578,9 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         const int row4 = 4 * (ly0 + nr) * TW;
         const int up0 = nr == RPW ? lab0[RPW - 1] : 0, up1 = nr == RPW ? lab1[RPW - 1] : 0;
         const int2 low = make_int2(lds_ld(&P[(row4 >> 2) + lx0]), lds_ld(&P[(row4 >> 2) + lx0 + 1]));
-        auto link = [&](int x, int up) {  // the entry of x as it was: x (linked now) or its parent
-            int expect = x;
-            __hip_atomic_compare_exchange_strong(lds_entry<true>(P, x), &expect, up, __ATOMIC_RELAXED,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            return expect;
-        };
         int got0 = -1, got1 = -1;
-        if (lane_bit(prevD.e, lane) && low.x >= row4) got0 = link(low.x, up0);
-        if (lane_bit(prevD.o, lane) && low.y >= row4) got1 = link(low.y, up1);
+        if (lane_bit(prevD.e, lane) && low.x >= row4) got0 = link_root(P, low.x, up0);
+        if (lane_bit(prevD.o, lane) && low.y >= row4) got1 = link_root(P, low.y, up1);
         const EO met = EO{lanes_eq(static_cast<uint32_t>(got0), static_cast<uint32_t>(low.x)) |
                               lanes_eq(static_cast<uint32_t>(got0), static_cast<uint32_t>(up0)),
                           lanes_eq(static_cast<uint32_t>(got1), static_cast<uint32_t>(low.y)) |
@@ -738,14 +676,15 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         nbp = ka->nb;
         tile_act = ka->tile_act;
     }
-    uint32_t *codes32 = reinterpret_cast<uint32_t *>(codes + static_cast<int64_t>(tile) * TSITES);
+    uint32_t *codes32 = reinterpret_cast<uint32_t *>(codes + static_cast<int64_t>(tile) * TSITES) +
+                        ly0 * (TW / 2) + lane;
     // unrolled: the rows' lookups are independent, so their LDS loads overlap
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         if (r >= nr) break;
         const uint32_t code0 = entry_code(lds_ld(lds_entry<true>(P, lab0[r])));
         const uint32_t code1 = entry_code(lds_ld(lds_entry<true>(P, lab1[r])));
-        codes32[((ly0 + r) * TW + lx0) >> 1] = code0 | (code1 << 16);
+        codes32[r * (TW / 2)] = code0 | (code1 << 16);
     }
     uint16_t *edg = edges + static_cast<int64_t>(tile) * EDGE;
     for (int t = threadIdx.x; t < EDGE; t += NT) {

@@ -26,6 +26,47 @@ __device__ __forceinline__ bool lane_bit(uint64_t m, int lane)
 }
 
 
+// Lane masks: bit L describes lane L (uicmp yields the mask of one compare).
+constexpr int CMP_EQ = 32, CMP_NE = 33, CMP_ULT = 36, CMP_ULE = 37;
+__device__ __forceinline__ uint64_t lanes_eq(uint32_t x, uint32_t y) { return __builtin_amdgcn_uicmp(x, y, CMP_EQ); }
+__device__ __forceinline__ uint64_t lanes_ne(uint32_t x, uint32_t y) { return __builtin_amdgcn_uicmp(x, y, CMP_NE); }
+__device__ __forceinline__ uint64_t lanes_lt(uint32_t x, uint32_t y) { return __builtin_amdgcn_uicmp(x, y, CMP_ULT); }
+__device__ __forceinline__ uint64_t lanes_le(uint32_t x, uint32_t y) { return __builtin_amdgcn_uicmp(x, y, CMP_ULE); }
+
+// A tile row as two wave ballots: lane L owns sites 2L and 2L+1, bit L of `e`
+// belongs to site 2L and bit L of `o` to site 2L+1.  The masks stay in scalar
+// registers; the natural-order shift s -> s+1 is (o << 1, e).
+struct EO {
+    uint64_t e, o;
+};
+
+__device__ __forceinline__ EO eo_andnot(EO a, EO b) { return EO{a.e & ~b.e, a.o & ~b.o}; }
+
+// Set bits of m at lanes below the calling lane.
+__device__ __forceinline__ int lanes_below(uint64_t m)
+{
+    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
+}
+
+// Append the calling lanes' entries to a wave list: ve for the lanes of m.e,
+// then vo for those of m.o (the order does not matter); n is the wave-uniform
+// list length.
+__device__ __forceinline__ void eo_append(uint16_t *list, int &n, EO m, int ve, int vo)
+{
+    const auto at = [](uint64_t mask, int from) {
+        return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask),
+                                                                                    static_cast<uint32_t>(from))));
+    };
+    const int pe = at(m.e, n);
+    n += __popcll(m.e);
+    const int po = at(m.o, n);
+    n += __popcll(m.o);
+    if (lane_bit(m.e, 0)) list[pe] = static_cast<uint16_t>(ve);
+    if (lane_bit(m.o, 0)) list[po] = static_cast<uint16_t>(vo);
+}
+
 // Value of x held by the next lane (DPP wave shift; the last lane gets 0).
 __device__ __forceinline__ uint32_t from_next_lane(uint32_t x)
 {
@@ -82,6 +123,35 @@ __device__ __forceinline__ void unite_step(int *P, int &a, int &b, int &done)
     done = static_cast<int>((SAME_PARENT && pa == pb) | (roots & (!link | (old == hi))));
     a = link ? old : ga;
     b = link ? lo : gb;
+}
+
+// Root of x (a byte offset, as the tile kernel's parents) once all unions are
+// done; a claimed root (negative entry) is a root.
+__device__ __forceinline__ int lroot(int *P, int x)
+{
+    for (;;) {
+        const int p = lds_ld(lds_entry<true>(P, x));
+        if (p == x || p < 0) return x;
+        x = p;
+    }
+}
+
+// Entries that are done hold FINAL | code << 2 (negative); the entry of an
+// unclaimed root, its own byte offset 4 slot, gives its code by the same
+// two-bit shift.  P[root] = CLAIMING while a root's id is allocated.
+constexpr int CLAIMING = -1;
+__device__ __forceinline__ int final_entry(uint32_t code) { return static_cast<int>(0x80000000u | (code << 2)); }
+__device__ __forceinline__ uint32_t entry_code(int e) { return (static_cast<uint32_t>(e) >> 2) & 0xFFFFu; }
+
+// Link label x below `up` if x is still a root; returns the entry of x as it
+// was: x (linked now), or the parent it has.  The caller knows up < x, so a
+// parent stays below its child.
+__device__ __forceinline__ int link_root(int *P, int x, int up)
+{
+    int expect = x;
+    __hip_atomic_compare_exchange_strong(lds_entry<true>(P, x), &expect, up, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+    return expect;
 }
 
 // ---- global union-find over boundary ids ----

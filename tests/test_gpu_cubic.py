@@ -246,3 +246,32 @@ def test_ccl3_percolation_512():
     assert np.array_equal(labels.cpu().numpy().reshape(-1), want)
     labels2, n2 = sw.ccl3_label(g, workspace=ws)
     assert n2 == n and torch.equal(labels, labels2)
+
+
+@pytest.mark.parametrize("Lx,Ly,Lz", [(32, 16, 16), (31, 8, 4), (33, 9, 5), (36, 17, 15), (64, 7, 3), (5, 24, 31),
+                                       (30, 1, 12)])
+def test_tile_edges(Lx, Ly, Lz):
+    """Extents at the edges of the tile, of a wave's rows and of its planes:
+    sweeps with bonds, labels and records (active bonds of ragged tiles), and
+    labelings whose rows meet many labels (dense along some axes, sparse along
+    the others)."""
+    q, K, seed = 2, 0.7, wl.SEED_BASE | 0x3E1
+    print(f"cubic tile edges Lx={Lx} Ly={Ly} Lz={Lz}", flush=True)
+    lat = sw.CubicLattice(Lx, Ly, Lz, q=q, K=K, seed=seed, keep_labels=True, keep_bonds=True)
+    plain = sw.CubicLattice(Lx, Ly, Lz, q=q, K=K, seed=seed)  # bonds not kept
+    st = oracle.init_states3(Lx, Ly, Lz, q, seed)
+    for t in range(3):
+        rec = lat.sweep(1, records=True)
+        plain.sweep(1)
+        st, bonds, labels, want = oracle.sw3_sweep(Lx, Ly, Lz, q, oracle.threshold(K), seed, 0, t, st)
+        torch.cuda.synchronize()
+        assert np.array_equal(lat.bonds.cpu().numpy().reshape(-1), bonds), t
+        assert np.array_equal(lat.labels.cpu().numpy().reshape(-1), labels), t
+        assert np.array_equal(_state(lat), st) and np.array_equal(_state(plain), st), t
+        assert [int(v) for v in rec[0].cpu()] == [int(v) for v in want], t
+    rng = np.random.default_rng(8100 + Lx)
+    for p in ((0.9, 0.1, 0.1), (0.1, 0.9, 0.1), (0.1, 0.1, 0.9), (0.05, 0.9, 0.9), (0.9, 0.9, 0.05)):
+        b = ((rng.random((Lx * Ly * Lz, 3)) < np.array(p)) @ np.array([1, 2, 4])).astype(np.uint8)
+        got, n = sw.ccl3_label(torch.from_numpy(b.reshape(Lz, Ly, Lx)).cuda())
+        want, nref = oracle.label_bonds3(Lx, Ly, Lz, b)
+        assert n == nref and np.array_equal(got.cpu().numpy().reshape(-1), want), p
