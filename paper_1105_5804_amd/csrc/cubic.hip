@@ -27,8 +27,8 @@
 //               and its interior roots, then every site's new state (and
 //               optionally label) from its code.
 //
-// With per-sweep records, k3_observe counts the satisfied bonds and states of
-// the new spins and k3_record moves the counters into the record.
+// With per-sweep records, k_observe counts the satisfied bonds and states of
+// the new spins, adds up the tiles' counters and writes the record.
 //
 // ccl3_label runs the same tile, merge, resolve and flatten kernels on given
 // bond bytes (LABEL = true): no spins, no draws, labels out.
@@ -39,6 +39,7 @@
 
 #include "../../include/swccl.h"
 #include "internal.hpp"
+#include "observe.hpp"
 #include "philox.hpp"
 #include "uf.hpp"
 
@@ -71,9 +72,6 @@ constexpr uint32_t TAG_BOND = 1, TAG_FLIP = 2, TAG_BOND_Z = 5;
 constexpr uint32_t CODE_MASK = 0x3FFF;
 static_assert(CAP + CSITES <= CODE_MASK, "codes take 14 bits");
 static_assert(CAP < (1 << 15), "merge list entries hold two ids in 15 bits each");
-
-// Counters of a sweep, in the order of the record fields.
-enum { S3_ACTIVE = 0, S3_NCLUST = 1, S3_NSAT = 2, S3_COUNTS = 3, S3_LEN = 11 };
 
 struct Geo3 {
     int Lx, Ly, Lz;
@@ -144,6 +142,7 @@ struct Tile3Args {
     int32_t *tile_act;        // [ntiles]: active bonds owned by the tile
     uint32_t tm1, tany;       // a bond is active iff its word r <= tm1 and tany (T > 0; tm1 = T - 1)
     uint32_t k0, k1, t, sid;
+    uint32_t *ticket;         // cleared for the observables that follow, or nullptr
 };
 
 // Slot of face position t (the z, then y, then x faces of a full tile), or -1
@@ -207,6 +206,7 @@ __global__ __launch_bounds__(NT3) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     const bool ragged = T.tw < CX || T.td < CZ;
     uint16_t *mylist = wl[w];
     if (threadIdx.x == 0) nb_s = 0;
+    if (T.tile == 0 && threadIdx.x == 0 && a.ticket) *a.ticket = 0u;
     // lane masks (each tile row's 16 lanes alike): the last column's sites
     const uint32_t row0m = 0xFFFFu >> (LPR - ((T.tw + 1) >> 1)), row1m = row0m >> (T.tw & 1);
     const uint64_t every = 0x0001000100010001ull;
@@ -854,88 +854,20 @@ __global__ __launch_bounds__(NT3) void k3_flatten(Flat3Args a)
     }
 }
 
-// The sweep's active bonds and clusters from the per-tile counts.
-__global__ __launch_bounds__(1024) void k3_reduce_tiles(const int32_t *tile_act, const int32_t *tile_ncl, int ntiles,
-                                                        unsigned long long *stats)
+// The cluster count of a labeling from the tiles' counts, by one workgroup.
+__global__ __launch_bounds__(1024) void k3_count_out(const int32_t *tile_ncl, int ntiles, int32_t *n_clusters)
 {
-    __shared__ unsigned long long red[2][16];
-    unsigned long long act = 0, ncl = 0;
-    for (int t = threadIdx.x; t < ntiles; t += 1024) {
-        act += static_cast<unsigned>(tile_act[t]);
-        ncl += static_cast<unsigned>(tile_ncl[t]);
-    }
-    act = wave_sum(act);
-    ncl = wave_sum(ncl);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) {
-        red[0][w] = act;
-        red[1][w] = ncl;
-    }
+    __shared__ uint32_t red[16];
+    uint32_t ncl = 0;
+    for (int t = threadIdx.x; t < ntiles; t += 1024) ncl += static_cast<uint32_t>(tile_ncl[t]);
+    ncl = wave_sum_u32(ncl);
+    if ((threadIdx.x & 63) == 0) red[wave_id()] = ncl;
     __syncthreads();
-    if (threadIdx.x < 2) {
-        unsigned long long v = 0;
-        for (int k = 0; k < 16; ++k) v += red[threadIdx.x][k];
-        stats[threadIdx.x == 0 ? S3_ACTIVE : S3_NCLUST] = v;
+    if (threadIdx.x == 0) {
+        uint32_t v = 0;
+        for (int k = 0; k < 16; ++k) v += red[k];
+        *n_clusters = static_cast<int32_t>(v);
     }
-}
-
-// Satisfied bonds among the 3N pairs and state counts 0..7 of the spins
-// (-H/J of Eq. potts_hamiltonian on the cubic lattice).
-__global__ __launch_bounds__(512) void k3_observe(const uint8_t *spins, Geo3 g, int ising, unsigned long long *stats)
-{
-    // a wave per row segment of 64 sites, a lane per site: no division per site
-    const uint32_t Lx = static_cast<uint32_t>(g.Lx), Ly = static_cast<uint32_t>(g.Ly);
-    const uint32_t Lz = static_cast<uint32_t>(g.Lz);
-    const uint32_t segs = (Lx + 63u) / 64u;
-    const uint32_t nseg = Ly * Lz * segs;
-    const uint32_t plane = Lx * Ly;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t nwaves = gridDim.x * 8u;
-    unsigned nsat = 0, cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (uint32_t w = blockIdx.x * 8u + (threadIdx.x >> 6); w < nseg; w += nwaves) {
-        const uint32_t row = w / segs, x = (w - row * segs) * 64u + lane;
-        if (x >= Lx) continue;
-        const uint32_t y = row % Ly, z = row / Ly;
-        const uint32_t base = row * Lx;
-        const uint32_t ry = y + 1u == Ly ? base - y * Lx : base + Lx;  // the row at y + 1
-        const uint32_t rz = z + 1u == Lz ? y * Lx : base + plane;      // the row at z + 1
-        const uint32_t s = spins[base + x];
-        const uint32_t xn = x + 1u == Lx ? 0u : x + 1u;
-        nsat += (s == spins[base + xn] ? 1u : 0u) + (s == spins[ry + x] ? 1u : 0u) + (s == spins[rz + x] ? 1u : 0u);
-        const uint32_t st = ising ? (s == 1u ? 1u : 0u) : s;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) cnt[k] += st == static_cast<uint32_t>(k) ? 1u : 0u;
-    }
-    // one atomic per counter and workgroup
-    __shared__ unsigned long long red[9][8];
-    const unsigned long long ns = wave_sum(nsat);
-    if (lane == 0) red[0][threadIdx.x >> 6] = ns;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const unsigned long long c = wave_sum(cnt[k]);
-        if (lane == 0) red[1 + k][threadIdx.x >> 6] = c;
-    }
-    __syncthreads();
-    if (threadIdx.x < 9) {
-        unsigned long long v = 0;
-        for (int w = 0; w < 8; ++w) v += red[threadIdx.x][w];
-        add_stat(&stats[threadIdx.x == 0 ? S3_NSAT : S3_COUNTS + threadIdx.x - 1], v);
-    }
-}
-
-// The cluster count of a labeling into the caller's int32.
-__global__ void k3_count_out(const unsigned long long *stats, int32_t *n_clusters)
-{
-    if (threadIdx.x == 0) *n_clusters = static_cast<int32_t>(stats[S3_NCLUST]);
-}
-
-// Move the sweep's counters into its record and clear them for the next one.
-__global__ void k3_record(unsigned long long *stats, int64_t *row)
-{
-    const int k = threadIdx.x;
-    if (k >= S3_LEN) return;
-    if (row) row[k] = static_cast<int64_t>(stats[k]);
-    stats[k] = 0ull;
 }
 
 }  // namespace cubic
@@ -953,7 +885,7 @@ int64_t cdiv3(int64_t a, int64_t b) { return (a + b - 1) / b; }
 struct Layout3 {
     Geo3 g;
     int64_t N;
-    size_t codes, xface, gkey, gparent, nb, tile_act, tile_ncl, stats, total;
+    size_t codes, xface, gkey, gparent, nb, tile_act, tile_ncl, ticket, obs_part, total;
 };
 
 // Extents >= 1, N < 2^31, and the ids of all tiles (ntiles x CAP) index
@@ -1003,7 +935,8 @@ Layout3 layout3(int32_t Lx, int32_t Ly, int32_t Lz)
     L.nb = take(nt * sizeof(int32_t));
     L.tile_act = take(nt * sizeof(int32_t));
     L.tile_ncl = take(nt * sizeof(int32_t));
-    L.stats = take(16 * sizeof(unsigned long long));
+    L.ticket = take(sizeof(uint32_t));
+    L.obs_part = take(OBS_PART_BYTES);
     L.total = off;
     return L;
 }
@@ -1062,7 +995,6 @@ sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, i
     if (!workspace || workspace_bytes < L.total || reinterpret_cast<uintptr_t>(workspace) % ALIGN3)
         return SW_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    unsigned long long *stats = at3<unsigned long long>(workspace, L.stats);
     Tile3Args ta{};
     ta.g = L.g;
     ta.in = bonds;
@@ -1096,10 +1028,7 @@ sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, i
     hipLaunchKernelGGL(k3_merge, tiles, dim3(MT), 0, s, ma);
     hipLaunchKernelGGL(k3_resolve, tiles, dim3(RT), 0, s, ra);
     hipLaunchKernelGGL(k3_flatten<true>, tiles, dim3(NT3), 0, s, fa);
-    if (n_clusters) {
-        hipLaunchKernelGGL(k3_reduce_tiles, dim3(1), dim3(1024), 0, s, ta.tile_act, fa.tile_ncl, L.g.ntiles, stats);
-        hipLaunchKernelGGL(k3_count_out, dim3(1), dim3(64), 0, s, stats, n_clusters);
-    }
+    if (n_clusters) hipLaunchKernelGGL(k3_count_out, dim3(1), dim3(1024), 0, s, fa.tile_ncl, L.g.ntiles, n_clusters);
     return swccl_internal::device_error(hipGetLastError(), "ccl3_label");
 }
 
@@ -1116,7 +1045,6 @@ sw_status sw3_sweep(const sw3_params *p, uint8_t *spins, uint32_t t0, int32_t n,
     if (n == 0) return SW_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint64_t T = swccl_internal::bond_threshold(p->K);
-    unsigned long long *stats = at3<unsigned long long>(workspace, L.stats);
 
     Tile3Args ta{};
     ta.g = L.g;
@@ -1133,6 +1061,7 @@ sw_status sw3_sweep(const sw3_params *p, uint8_t *spins, uint32_t t0, int32_t n,
     ta.k0 = static_cast<uint32_t>(p->seed);
     ta.k1 = static_cast<uint32_t>(p->seed >> 32);
     ta.sid = p->stream_id;
+    if (records) ta.ticket = at3<uint32_t>(workspace, L.ticket);
 
     Merge3Args ma{};
     ma.g = L.g;
@@ -1161,9 +1090,16 @@ sw_status sw3_sweep(const sw3_params *p, uint8_t *spins, uint32_t t0, int32_t n,
     ra.nb = ta.nb;
 
     const dim3 tiles(static_cast<unsigned>(L.g.ntiles));
-    const int64_t segs = static_cast<int64_t>(L.g.Ly) * L.g.Lz * cdiv3(L.g.Lx, 64);
-    const unsigned obs_blocks = static_cast<unsigned>(std::min<int64_t>(cdiv3(segs, 8), 1024));
-    hipLaunchKernelGGL(k3_record, dim3(1), dim3(64), 0, s, stats, static_cast<int64_t *>(nullptr));  // clear
+    ObsArgs oa{};
+    oa.spins = spins;
+    oa.Lx = static_cast<uint32_t>(L.g.Lx);
+    oa.Ly = static_cast<uint32_t>(L.g.Ly);
+    oa.Lz = static_cast<uint32_t>(L.g.Lz);
+    oa.tile_act = ta.tile_act;
+    oa.tile_ncl = fa.tile_ncl;
+    oa.ntiles = L.g.ntiles;
+    oa.part = at3<uint32_t>(workspace, L.obs_part);
+    oa.ticket = ta.ticket;
     for (int32_t k = 0; k < n; ++k) {
         const uint32_t t = t0 + static_cast<uint32_t>(k);
         ta.t = t;
@@ -1174,10 +1110,8 @@ sw_status sw3_sweep(const sw3_params *p, uint8_t *spins, uint32_t t0, int32_t n,
         hipLaunchKernelGGL(k3_resolve, tiles, dim3(RT), 0, s, ra);
         hipLaunchKernelGGL(k3_flatten<false>, tiles, dim3(NT3), 0, s, fa);
         if (records) {
-            hipLaunchKernelGGL(k3_reduce_tiles, dim3(1), dim3(1024), 0, s, ta.tile_act, fa.tile_ncl, L.g.ntiles, stats);
-            hipLaunchKernelGGL(k3_observe, dim3(obs_blocks), dim3(512), 0, s, spins, L.g, static_cast<int>(fa.ising),
-                               stats);
-            hipLaunchKernelGGL(k3_record, dim3(1), dim3(64), 0, s, stats, records + static_cast<int64_t>(k) * SW3_REC_LEN);
+            oa.out = records + static_cast<int64_t>(k) * SW3_REC_LEN;
+            launch_observe<true, OBS_RECORD3>(oa, fa.ising != 0, s);
         }
     }
     return swccl_internal::device_error(hipGetLastError(), "sw3_sweep");

@@ -80,8 +80,10 @@ enum : uint32_t { TAG_INIT = 0, TAG_BOND = 1, TAG_FLIP = 2, TAG_SEED = 3, TAG_FE
 // tile and merge kernels and flips in k_flatten<M_FEW>.
 enum Mode : int { M_SW = 0, M_BONDS_PERIODIC = 1, M_BONDS_OPEN = 2, M_SITES = 3, M_FEW = 4 };
 
-// Observable counters (unsigned 64-bit, two's complement for signed values).
-enum { ST_ACTIVE = 0, ST_NCLUST = 1, ST_NSAT = 2, ST_MAGNET = 3, ST_COUNTS = 4, ST_DIGEST = 12, ST_LEN = 16 };
+// Observable counters (unsigned 64-bit, two's complement for signed values),
+// and the observables' workgroup ticket.
+enum { ST_ACTIVE = 0, ST_NCLUST = 1, ST_NSAT = 2, ST_MAGNET = 3, ST_COUNTS = 4, ST_DIGEST = 12, ST_TICKET = 15,
+       ST_LEN = 16 };
 
 struct Grid {
     int W, H, ntx, nty, ntiles;
@@ -853,6 +855,7 @@ struct FlatArgs {
     uint32_t *seedmap;        // [ntiles][TSITES / 32]: interior roots that hold a seed (cleared here)
     uint32_t stamp;           // this sweep's mark (t + 1)
     uint32_t tflip;           // a seeded cluster flips iff its FEW word is below this
+    uint32_t *ticket;         // cleared for the observables that follow, or nullptr
 };
 
 // The seed of seed tile j (Sec. III, few-cluster variant): the lattice is cut
@@ -978,6 +981,7 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
     const int ly0 = wave * RPW;
     const int nr = max(0, min(RPW, th - ly0));
     const int nbt = a.nb[tile];
+    if (lt == 0 && threadIdx.x == 0 && a.ticket) *a.ticket = 0u;
     // each boundary id's parent and key (ids threadIdx.x + j NT), issued with
     // the count's loads (entries past nb are read, not used); a root's key is
     // its cluster's canonical label
@@ -1232,23 +1236,19 @@ __global__ __launch_bounds__(Tile<TH_>::NT) void k_flatten(FlatArgs a)
     flatten_body<MODE, SIZES, TH_>(a, tile, lt, sm);
 }
 
-// Sum of n per-tile int32 counters into *out64 and/or *out32 (one atomic per
-// workgroup; both outputs are cleared by the caller).
-__global__ __launch_bounds__(NT) void k_reduce_tiles(const int32_t *v, int n, unsigned long long *out64,
-                                                      int32_t *out32)
+// Sum of n per-tile int32 counters by one workgroup.
+__global__ __launch_bounds__(1024) void k_sum_tiles(const int32_t *v, int n, int32_t *out)
 {
-    __shared__ unsigned long long red[NWAVE];
-    unsigned long long acc = 0;
-    for (int i = blockIdx.x * NT + threadIdx.x; i < n; i += gridDim.x * NT) acc += static_cast<unsigned>(v[i]);
-    acc = wave_sum(acc);
-    const int lane = threadIdx.x & 63, wave = wave_id();
-    if (lane == 0) red[wave] = acc;
+    __shared__ uint32_t red[16];
+    uint32_t acc = 0;
+    for (int i = threadIdx.x; i < n; i += 1024) acc += static_cast<uint32_t>(v[i]);
+    acc = wave_sum_u32(acc);
+    if ((threadIdx.x & 63) == 0) red[wave_id()] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long t = 0;
-        for (int w = 0; w < NWAVE; ++w) t += red[w];
-        if (out64) add_stat(out64, t);
-        if (out32 && t) atomicAdd(out32, static_cast<int32_t>(t));
+        uint32_t t = 0;
+        for (int w = 0; w < 16; ++w) t += red[w];
+        *out = static_cast<int32_t>(t);
     }
 }
 
@@ -1554,21 +1554,6 @@ __global__ __launch_bounds__(SMALL_NT) void k_small(SmallArgs a)
     small_body<SMALL_NT, SMALL_SITES>(a, sm);
 }
 
-// One per-sweep record from the observable slots (after k_observe and the
-// per-tile reductions of the sweep).
-__global__ void k_hist_row(const unsigned long long *st, const int32_t *max_size, int64_t *row)
-{
-    const int k = threadIdx.x;
-    if (k >= HIST_LEN) return;
-    int64_t v;
-    if (k == HIST_ACTIVE) v = static_cast<int64_t>(st[ST_ACTIVE]);
-    else if (k == HIST_NCLUST) v = static_cast<int64_t>(st[ST_NCLUST]);
-    else if (k == HIST_MAXCL) v = max_size ? static_cast<int64_t>(*max_size) : -1;
-    else if (k == HIST_NSAT) v = static_cast<int64_t>(st[ST_NSAT]);
-    else v = static_cast<int64_t>(st[ST_COUNTS + k - HIST_COUNTS]);
-    row[k] = v;
-}
-
 // --------------------------------------------------------------- digest ---
 
 // Check-sum of an array: the sum over i of the low 64 bits of the Philox block
@@ -1603,76 +1588,6 @@ __global__ __launch_bounds__(NT) void k_digest(const void *v, int64_t n, unsigne
         for (int w = 0; w < NWAVE; ++w) t += red[w];
         add_stat(out, t);
     }
-}
-
-// ----------------------------------------------------------- observables ---
-
-// Satisfied bonds, magnetisation (Ising) and state counts of the spins
-// (Eq. potts_hamiltonian: -H/J = number of satisfied bonds).  Blocks take whole
-// rows; a thread takes 4 consecutive sites per step.  State counts go to
-// packed 16-bit counters (states 0-3 and 4-7), flushed after every row.
-__global__ __launch_bounds__(NT) void k_observe(const uint8_t *s, int W, int H, uint32_t q, int ising,
-                                                unsigned long long *out)
-{
-    __shared__ unsigned long long red[NWAVE][10];
-    unsigned long long nsat = 0, cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int y = blockIdx.x; y < H; y += gridDim.x) {
-        const uint8_t *row = s + static_cast<int64_t>(y) * W;
-        const uint8_t *dwn = s + static_cast<int64_t>(y + 1 == H ? 0 : y + 1) * W;
-        uint64_t h03 = 0, h47 = 0;
-        int steps = 0;  // a 16-bit field takes at most 4 per step: flushed every 8192 steps
-        for (int x = threadIdx.x * 4; x < W; x += NT * 4) {
-            if (++steps == 8192) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    cnt[k] += (h03 >> (16 * k)) & 0xFFFFull;
-                    cnt[k + 4] += (h47 >> (16 * k)) & 0xFFFFull;
-                }
-                h03 = h47 = 0;
-                steps = 0;
-            }
-            uint32_t v[5], d[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int xj = min(x + j, W - 1);
-                v[j] = row[xj];
-                d[j] = dwn[xj];
-            }
-            v[4] = row[x + 4 < W ? x + 4 : (x + 4 == W ? 0 : W - 1)];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (x + j >= W) break;
-                const uint32_t vr = (x + j + 1 == W) ? row[0] : v[j + 1];
-                nsat += (v[j] == vr) + (v[j] == d[j]);
-                const uint32_t st = ising ? (v[j] == 1u ? 1u : 0u) : v[j];
-                if (st < 4) h03 += 1ull << (16 * st);
-                else if (st < 8) h47 += 1ull << (16 * (st - 4));
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            cnt[k] += (h03 >> (16 * k)) & 0xFFFFull;
-            cnt[k + 4] += (h47 >> (16 * k)) & 0xFFFFull;
-        }
-    }
-    const int lane = threadIdx.x & 63, wave = wave_id();
-    unsigned long long vals[10];
-    vals[0] = nsat;
-    vals[1] = 0;
-    for (int k = 0; k < 8; ++k) vals[2 + k] = cnt[k];
-    for (int k = 0; k < 10; ++k) {
-        const unsigned long long w = wave_sum(vals[k]);
-        if (lane == 0) red[wave][k] = w;
-    }
-    __syncthreads();
-    // the magnetisation of the Ising case follows from the counts on the host
-    if (threadIdx.x < 10 && threadIdx.x != 1) {
-        unsigned long long t = 0;
-        for (int w = 0; w < NWAVE; ++w) t += red[w][threadIdx.x];
-        const int slot = threadIdx.x == 0 ? ST_NSAT : ST_COUNTS + threadIdx.x - 2;
-        add_stat(&out[slot], t);
-    }
-    (void)q;
 }
 
 // ------------------------------------------------ batched labeling requests --

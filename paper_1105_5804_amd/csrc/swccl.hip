@@ -16,6 +16,7 @@
 #include "../../include/swccl.h"
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "observe.hpp"
 
 using namespace swccl;
 
@@ -61,6 +62,7 @@ struct Layout {
     size_t row_count, row_off, scan_tmp, rl_slot, rl_size;
     size_t lat_desc, lat_of_tile, t_dev;  // batches only
     size_t small_lat, ftile, mgroup, counters, fault;  // fused batch sweeps
+    size_t obs_part;      // sweeps only: the observables' partial sums
     size_t sel, seedmap;  // few-cluster sweeps: seed marks per root id, seed bits per interior root slot
     bool few;
     size_t total;
@@ -112,7 +114,7 @@ size_t carve_tiles(Layout &L, size_t nt)
 }
 
 Layout make_layout(int32_t W, int32_t H, bool sizes, int th = TH_DEFAULT, int mw = MERGE_WAVES_DEFAULT,
-                   bool few = false)
+                   bool few = false, bool observed = false)
 {
     Layout L{};
     L.d = dims_of(th);
@@ -140,6 +142,7 @@ Layout make_layout(int32_t W, int32_t H, bool sizes, int th = TH_DEFAULT, int mw
         L.rl_slot = take(nt * static_cast<size_t>(L.d.tsites) * sizeof(int32_t));
         L.rl_size = take(nt * static_cast<size_t>(L.d.tsites) * sizeof(int32_t));
     }
+    if (observed) L.obs_part = take(OBS_PART_BYTES);
     L.few = few;
     if (few) {
         L.sel = take(nt * static_cast<size_t>(L.d.cap) * sizeof(uint32_t));
@@ -176,6 +179,8 @@ Layout make_batch_layout(int64_t ntiles, int32_t nlat, int th, int mw)
     off += align_up((2 + 2 * static_cast<size_t>(nlat)) * sizeof(unsigned long long));
     L.fault = off;
     off += align_up(sizeof(int32_t));
+    L.obs_part = off;
+    off += align_up(OBS_PART_BYTES);
     L.total = off;
     return L;
 }
@@ -395,7 +400,8 @@ static uint32_t prob_threshold(double p)
 
 static Layout layout_of(const sw_params *p)
 {
-    return make_layout(p->W, p->H, (p->flags & SW_F_SIZES) != 0, tile_h_of(p), merge_waves_of(p), p->few_b > 0);
+    return make_layout(p->W, p->H, (p->flags & SW_F_SIZES) != 0, tile_h_of(p), merge_waves_of(p), p->few_b > 0,
+                       true);
 }
 
 size_t sw_workspace_bytes(const sw_params *p)
@@ -523,6 +529,7 @@ static sw_status launch_phase(sw_lattice *h, int32_t phase, hipStream_t s)
     fa.t = t;
     fa.sid = h->p.stream_id;
     fa.ising = h->p.spin_kind == SW_SPIN_ISING_I8 ? 1 : 0;
+    fa.ticket = reinterpret_cast<uint32_t *>(at<unsigned long long>(ws, L.stats) + ST_TICKET);
     if (L.few) {
         // few-cluster flip: mark the boundary clusters that hold a seed, then
         // flatten with the seeded clusters' flips
@@ -626,25 +633,34 @@ sw_status sw_sweep(sw_lattice *h, int32_t n_sweeps, void *stream)
     return SW_OK;
 }
 
+static ObsArgs obs_args(const sw_params &p, const void *spins, const Layout &L, void *ws)
+{
+    ObsArgs a{};
+    a.spins = static_cast<const uint8_t *>(spins);
+    a.Lx = static_cast<uint32_t>(p.W);
+    a.Ly = static_cast<uint32_t>(p.H);
+    a.Lz = 1u;
+    a.part = at<uint32_t>(ws, L.obs_part);
+    a.ticket = reinterpret_cast<uint32_t *>(at<unsigned long long>(ws, L.stats) + ST_TICKET);
+    return a;
+}
+
 // Observables of one lattice (spins, digests, and the last sweep's per-tile
 // counters tile_act / tile_ncl of its ntiles tiles); waits for the stream.
 static sw_status measure(const sw_params &p, const sw_buffers &b, bool swept, const int32_t *tile_act,
-                         const int32_t *tile_ncl, int ntiles, unsigned long long *obs, const int32_t *max_size_dev,
+                         const int32_t *tile_ncl, int ntiles, const Layout &L, void *ws, const int32_t *max_size_dev,
                          uint64_t T, uint64_t t, sw_obs *out, hipStream_t s)
 {
+    unsigned long long *obs = at<unsigned long long>(ws, L.stats);
     hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, obs, ST_LEN);
     const int64_t N = static_cast<int64_t>(p.W) * p.H;
-    const unsigned blocks = static_cast<unsigned>(std::min<int64_t>(p.H, 2048));
     const int ising = p.spin_kind == SW_SPIN_ISING_I8 ? 1 : 0;
-    hipLaunchKernelGGL(k_observe, dim3(blocks), dim3(NT), 0, s, static_cast<const uint8_t *>(b.spins), p.W, p.H,
-                       static_cast<uint32_t>(p.q), ising, obs);
-    if (swept) {
-        const unsigned rb = static_cast<unsigned>(std::min<int64_t>(cdiv(ntiles, NT), 64));
-        hipLaunchKernelGGL(k_reduce_tiles, dim3(rb), dim3(NT), 0, s, tile_act, ntiles, obs + ST_ACTIVE,
-                           static_cast<int32_t *>(nullptr));
-        hipLaunchKernelGGL(k_reduce_tiles, dim3(rb), dim3(NT), 0, s, tile_ncl, ntiles, obs + ST_NCLUST,
-                           static_cast<int32_t *>(nullptr));
-    }
+    ObsArgs oa = obs_args(p, b.spins, L, ws);
+    oa.tile_act = tile_act;
+    oa.tile_ncl = tile_ncl;
+    oa.ntiles = swept ? ntiles : 0;
+    oa.out = reinterpret_cast<int64_t *>(obs);
+    launch_observe<false, OBS_SLOTS>(oa, ising != 0, s);
     const unsigned db = static_cast<unsigned>(std::min<int64_t>(cdiv(N, NT), 4096));
     if (ising)
         hipLaunchKernelGGL(k_digest<DIG_ISING_I8>, dim3(db), dim3(NT), 0, s, b.spins, N, obs + ST_DIGEST);
@@ -689,8 +705,7 @@ sw_status sw_observables(sw_lattice *h, sw_obs *out, void *stream)
     void *ws = h->b.workspace;
     const int32_t *max_dev = L.sizes ? at<int32_t>(ws, L.row_count) + L.nrow + 1 : nullptr;
     return measure(h->p, h->b, h->swept, at<int32_t>(ws, L.tile_act), at<int32_t>(ws, L.tile_ncl),
-                   h->small_last ? 1 : L.g.ntiles,
-                   at<unsigned long long>(ws, L.stats), max_dev, h->T, h->t, out, static_cast<hipStream_t>(stream));
+                   h->small_last ? 1 : L.g.ntiles, L, ws, max_dev, h->T, h->t, out, static_cast<hipStream_t>(stream));
 }
 
 sw_status sw_sweep_history(sw_lattice *h, int32_t n_sweeps, int64_t *history, void *stream)
@@ -710,10 +725,11 @@ sw_status sw_sweep_history(sw_lattice *h, int32_t n_sweeps, int64_t *history, vo
     }
     const Layout &L = h->L;
     void *ws = h->b.workspace;
-    unsigned long long *obs = at<unsigned long long>(ws, L.stats);
-    const int32_t *max_dev = L.sizes ? at<int32_t>(ws, L.row_count) + L.nrow + 1 : nullptr;
-    const unsigned blocks = static_cast<unsigned>(std::min<int64_t>(h->p.H, 2048));
-    const unsigned rb = static_cast<unsigned>(std::min<int64_t>(cdiv(L.g.ntiles, NT), 64));
+    ObsArgs oa = obs_args(h->p, h->b.spins, L, ws);
+    oa.tile_act = at<int32_t>(ws, L.tile_act);
+    oa.tile_ncl = at<int32_t>(ws, L.tile_ncl);
+    oa.ntiles = L.g.ntiles;
+    oa.max_size = L.sizes ? at<int32_t>(ws, L.row_count) + L.nrow + 1 : nullptr;
     for (int32_t n = 0; n < n_sweeps; ++n) {
         for (int32_t ph = SW_PHASE_TILE; ph <= SW_PHASE_FLIP; ++ph) {
             const sw_status st = launch_phase(h, ph, s);
@@ -722,14 +738,8 @@ sw_status sw_sweep_history(sw_lattice *h, int32_t n_sweeps, int64_t *history, vo
         h->t += 1;
         h->swept = true;
         h->small_last = false;
-        hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, obs, ST_LEN);
-        hipLaunchKernelGGL(k_observe, dim3(blocks), dim3(NT), 0, s, static_cast<const uint8_t *>(h->b.spins), h->p.W,
-                           h->p.H, static_cast<uint32_t>(h->p.q), h->p.spin_kind == SW_SPIN_ISING_I8 ? 1 : 0, obs);
-        hipLaunchKernelGGL(k_reduce_tiles, dim3(rb), dim3(NT), 0, s, at<int32_t>(ws, L.tile_act), L.g.ntiles,
-                           obs + ST_ACTIVE, static_cast<int32_t *>(nullptr));
-        hipLaunchKernelGGL(k_reduce_tiles, dim3(rb), dim3(NT), 0, s, at<int32_t>(ws, L.tile_ncl), L.g.ntiles,
-                           obs + ST_NCLUST, static_cast<int32_t *>(nullptr));
-        hipLaunchKernelGGL(k_hist_row, dim3(1), dim3(64), 0, s, obs, max_dev, history + static_cast<int64_t>(n) * HIST_LEN);
+        oa.out = history + static_cast<int64_t>(n) * HIST_LEN;
+        launch_observe<false, OBS_RECORD>(oa, h->p.spin_kind == SW_SPIN_ISING_I8, s);
         const sw_status st = launch_status("sw_sweep_history");
         if (st != SW_OK) return st;
     }
@@ -816,10 +826,7 @@ sw_status ccl_enqueue(const Layout &L, const uint8_t *in, int32_t mode, int32_t 
         launch_flatten<M_BONDS_PERIODIC, false, false>(L, fa, L.g.ntiles, s);
     }
     if (n_clusters && !want_sizes) {
-        hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s, n_clusters, 1);
-        const unsigned rb = static_cast<unsigned>(std::min<int64_t>(cdiv(L.g.ntiles, NT), 64));
-        hipLaunchKernelGGL(k_reduce_tiles, dim3(rb), dim3(NT), 0, s, fa.tile_ncl, L.g.ntiles,
-                           static_cast<unsigned long long *>(nullptr), n_clusters);
+        hipLaunchKernelGGL(k_sum_tiles, dim3(1), dim3(1024), 0, s, fa.tile_ncl, L.g.ntiles, n_clusters);
     }
     return SW_OK;
 }
@@ -1305,7 +1312,7 @@ sw_status swb_observables(swb_batch *h, int32_t j, sw_obs *out, void *stream)
     hipStream_t s = static_cast<hipStream_t>(stream);
     const sw_status st = measure(h->p[static_cast<size_t>(j)], h->b[static_cast<size_t>(j)], h->swept,
                                  at<int32_t>(h->ws, L.tile_act) + d.tile0, at<int32_t>(h->ws, L.tile_ncl) + d.tile0,
-                                 in_lds ? 1 : d.g.ntiles, at<unsigned long long>(h->ws, L.stats), nullptr,
+                                 in_lds ? 1 : d.g.ntiles, L, h->ws, nullptr,
                                  h->T[static_cast<size_t>(j)], h->t, out, s);
     if (st != SW_OK || !h->fused) return st;
     int32_t fault = 0;

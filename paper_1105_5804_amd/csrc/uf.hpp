@@ -217,6 +217,20 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v)
     return v;
 }
 
+// The same for 32-bit values, in all lanes: row sums by DPP row shifts, then
+// row broadcasts (rows outside a broadcast's row mask add 0).
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t u)
+{
+    int v = static_cast<int>(u);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15, rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31, rows 2 and 3
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(v, 63));
+}
+
 // Index of the calling wave in its workgroup, as a wave-uniform (scalar)
 // value: everything derived from it (rows, row pointers, loop bounds) then
 // stays in scalar registers and branches on it need no exec masking.
