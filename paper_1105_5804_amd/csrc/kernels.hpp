@@ -1374,6 +1374,7 @@ struct SmallArgs {
     int32_t *tile_ncl;    // [1]: clusters of the last sweep
     uint32_t tm1, tany, k0, k1, sid, q, t0;
     int ising, n;
+    uint32_t *words;      // [n][chunks][64] random words of the sweeps (small_word), or nullptr
 };
 
 // Row of site i < 2^13 in a lattice of width W <= 128: the float quotient is
@@ -1382,65 +1383,136 @@ __device__ __forceinline__ int small_row(int i, float inv_w) { return static_cas
 
 constexpr int SMALL_NT = 1024;  // 16 waves: more LDS round trips in flight on the one CU
 
+// The random words of sites i0 (even) and i0 + 1 in sweep t, as they are used:
+// bits 0 .. 3 whether the right and down bonds of the two would be active
+// between equal spins, bytes 2 and 3 the states they would draw as roots.
+__device__ __forceinline__ uint32_t small_word(uint32_t i0, uint32_t t, const SmallArgs &a)
+{
+    const U4 b = philox4x32_10(i0 >> 1, t, TAG_BOND, a.sid, a.k0, a.k1);
+    const U4 f = philox4x32_10(i0 >> 2, t, TAG_FLIP, a.sid, a.k0, a.k1);
+    const uint32_t on = (b.v0 <= a.tm1 ? 1u : 0u) | (b.v1 <= a.tm1 ? 2u : 0u) | (b.v2 <= a.tm1 ? 4u : 0u) |
+                        (b.v3 <= a.tm1 ? 8u : 0u);
+    const uint32_t w0 = (i0 & 2u) ? f.v2 : f.v0, w1 = (i0 & 2u) ? f.v3 : f.v1;
+    return (a.tany ? on : 0u) | (draw_state(w0, a.q) << 16) | (draw_state(w1, a.q) << 24);
+}
+
 // LDS of a lattice swept whole by an NT_-thread workgroup (at most SITES sites).
 template <int NT_, int SITES>
 struct SmallSmem {
-    int P[SITES];
-    uint8_t S[SITES];  // states 0..q-1
-    unsigned long long red[NT_ / 64][3];
+    // Per-wave list: a step adds at most 128 entries, a fuller list is worked
+    // off first (workgroups of 16 waves have a CU to themselves; the others
+    // share its LDS).
+    static constexpr int TL = NT_ >= 1024 ? 448 : 132;
+    int P[SITES];           // union-find parent per site, as 4 x site
+    uint8_t S[SITES + 4];   // states 0..q-1
+    uint32_t red[NT_ / 64][12];
+    uint16_t wl[NT_ / 64][TL];
 };
 
 // All a.n sweeps of a lattice of at most SITES sites (W <= SMALL_W, H <=
 // SMALL_H) in one NT_-thread workgroup.
-template <int NT_, int SITES>
+//
+// The sites are taken in chunks of 128 consecutive site indices, two sites a
+// lane, whatever W is: a lane's pair shares one Philox block, and rows begin
+// and end anywhere in a chunk.  Right bonds inside a chunk become runs (the
+// tile kernel's max-scan); every other bond is first tried as one
+// compare-and-swap between the labels of its two ends, and only those that
+// lose are united step by step, from per-wave lists.  The spin bytes, no longer
+// needed once the bonds stand, then take the state each site would give its
+// cluster; every site walks to its root and takes the root's (which the root
+// itself keeps, so the bytes can be overwritten in place).  The counters of a
+// record are popcounts of lane masks.
+// PRE: the random words do not depend on the spins, so k_small_words has drawn
+// them on the whole chip (a.words); otherwise they are drawn here.
+// Bound by one workgroup's latency: chains of dependent LDS reads between three
+// barriers (of 6.5 us a sweep at 64 x 64: bonds and runs 2.2, unions 2.6, walks
+// and states 1.6).  Every bond united step by step, a draw at every site and
+// records summed by 64-bit shuffles took 13.4 us a sweep with its record, this
+// with the words drawn in the kernel 8.3, drawn ahead 6.6; 128 x 64 without
+// records, 4 sweeps: 87 -> 42 us.
+template <int NT_, int SITES, bool PRE>
 __device__ __forceinline__ void small_body(const SmallArgs &a, SmallSmem<NT_, SITES> &sm)
 {
-    constexpr int NT = NT_, NWAVE = NT_ / 64, TSITES = SITES;
-    constexpr int PAIRS_PER_THREAD = (TSITES / 2 + NT - 1) / NT;  // site pairs 2p, 2p+1 with p = tid + NT m
-    static_assert(PAIRS_PER_THREAD <= 8, "a thread's bonds fit one 32-bit mask");
+    constexpr int NT = NT_, NWAVE = NT_ / 64;
+    constexpr int MAXM = (SITES / 128 + NWAVE - 1) / NWAVE;  // chunks per wave
+    constexpr int U = MAXM <= 4 ? MAXM : 1;  // chunks worked at once (more would not fit the registers)
+    constexpr int TL = SmallSmem<NT_, SITES>::TL;
+    static_assert(SITES % 128 == 0 && MAXM <= 8 && SITES <= 1 << 13, "four bits a chunk, 13-bit sites");
     int *P = sm.P;
     uint8_t *S = sm.S;
     auto &red = sm.red;
-    static_assert(2 * TSITES < (1 << 16), "per-workgroup counters fit 16-bit fields");
     const int W = a.W, H = a.H, N = W * H;
-    const float inv_w = 1.0f / static_cast<float>(W);
     const int lane = threadIdx.x & 63, wave = wave_id();
-    auto right_of = [&](int i) {
-        const int y = small_row(i, inv_w), x = i - y * W;
-        return y * W + (x + 1 == W ? 0 : x + 1);
-    };
-    auto down_of = [&](int i) {
-        const int y = small_row(i, inv_w);
-        return y + 1 == H ? i - y * W : i + W;
-    };
+    const int nchunk = (N + 127) >> 7, M = (nchunk + NWAVE - 1) / NWAVE;
+    const int c0 = wave * M;  // the wave's chunks c0 ... (those below nchunk)
+    uint16_t *mylist = sm.wl[wave];
+    auto down_of = [&](int i) { return i + W < N ? i + W : i + W - N; };
     for (int i = threadIdx.x; i < N; i += NT) {
         const uint32_t b = a.spins[i];
         S[i] = static_cast<uint8_t>(a.ising ? (b == 1u ? 1u : 0u) : b);
     }
-    __syncthreads();
-    // Counters of a sweep's new spins (satisfied bonds, state counts) are
-    // taken during the next sweep's bond pass, which compares every
-    // neighbour pair anyway; those of the last sweep by one pass at the end.
-    // They are reduced as 16-bit fields, four to a word: no total of a
-    // workgroup exceeds 2 x 8192 (the bonds of a full tile).
-    auto reduce_record = [&](unsigned long long act, unsigned long long ncl, unsigned long long nsat,
-                             const unsigned long long (&cnt)[8]) {
-        unsigned long long pk[3] = {act | (ncl << 16) | (nsat << 32) | (cnt[0] << 48),
-                                    cnt[1] | (cnt[2] << 16) | (cnt[3] << 32) | (cnt[4] << 48),
-                                    cnt[5] | (cnt[6] << 16) | (cnt[7] << 32)};
+    uint32_t ends = 0;  // bit 2m + j: site j of the lane's pair in chunk m ends a row
+    {
+        const float inv_w = 1.0f / static_cast<float>(W);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const unsigned long long w = wave_sum(pk[k]);
-            if (lane == 0) red[wave][k] = w;
+        for (int m = 0; m < MAXM; ++m) {
+            const int i0 = (c0 + m) * 128 + 2 * lane;
+            ends |= (i0 + 1 == (small_row(i0, inv_w) + 1) * W ? 1u : 0u) << (2 * m);
+            ends |= (i0 + 2 == (small_row(i0 + 1, inv_w) + 1) * W ? 1u : 0u) << (2 * m + 1);
         }
+    }
+    __syncthreads();
+    // counters of the calling wave's sites (wave-uniform)
+    uint32_t nsat = 0, cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    // Equal-neighbour masks of chunk m: right and down of the even and the odd
+    // sites; with records their numbers and the states' are added up.
+    struct Equal {
+        uint64_t r0, r1, d0, d1;
+    };
+    auto equal_masks = [&](int m) {
+        const int i0 = (c0 + m) * 128 + 2 * lane;
+        const uint64_t V0 = lanes_lt(static_cast<uint32_t>(i0), static_cast<uint32_t>(N));
+        const uint64_t V1 = lanes_lt(static_cast<uint32_t>(i0 + 1), static_cast<uint32_t>(N));
+        const bool end0 = (ends >> (2 * m)) & 1u, end1 = (ends >> (2 * m + 1)) & 1u;
+        const uint32_t pair = *reinterpret_cast<const uint16_t *>(&S[i0]);
+        const uint32_t s0 = pair & 0xFFu, s1 = pair >> 8;
+        // (lanes past the lattice read some byte of S and are masked out)
+        const uint32_t x0 = (W & 1) && end0 ? S[max(i0 + 1 - W, 0)] : s1;
+        const uint32_t x1 = S[end1 ? max(i0 + 2 - W, 0) : i0 + 2];
+        const uint32_t y0 = S[min(down_of(i0), SITES - 1)], y1 = S[min(down_of(i0 + 1), SITES - 1)];
+        Equal e;
+        e.r0 = lanes_eq(s0, x0) & V0;
+        e.r1 = lanes_eq(s1, x1) & V1;
+        e.d0 = lanes_eq(s0, y0) & V0;
+        e.d1 = lanes_eq(s1, y1) & V1;
+        if (a.hist) {
+            nsat += __popcll(e.r0) + __popcll(e.r1) + __popcll(e.d0) + __popcll(e.d1);
+            cnt[0] += __popcll(lanes_eq(s0, 0u) & V0) + __popcll(lanes_eq(s1, 0u) & V1);
+            if (a.q == 2u) {
+                cnt[1] += __popcll(lanes_ne(s0, 0u) & V0) + __popcll(lanes_ne(s1, 0u) & V1);
+            } else {
+#pragma unroll
+                for (int k = 1; k < 8; ++k) cnt[k] += __popcll(lanes_eq(s0, k) & V0) + __popcll(lanes_eq(s1, k) & V1);
+            }
+        }
+        return e;
+    };
+    auto put_record = [&](uint32_t act, uint32_t ncl) {
+        if (lane != 0) return;
+        uint32_t *r = red[wave];
+        r[0] = act;
+        r[1] = ncl;
+        r[2] = nsat;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) r[3 + k] = cnt[k];
     };
     // after a barrier: thread k < 11 writes field k of the record of `sweep`
     auto write_record = [&](int sweep, bool last) {
         if (threadIdx.x >= 11) return;
         const int k = threadIdx.x;
-        unsigned long long sum = 0;
-        for (int w = 0; w < NWAVE; ++w) sum += red[w][k >> 2];
-        const unsigned long long tot = (sum >> (16 * (k & 3))) & 0xFFFFull;
+        uint32_t tot = 0;
+#pragma unroll
+        for (int w = 0; w < NWAVE; ++w) tot += red[w][k];
         if (a.hist) {
             int64_t *row = a.hist + static_cast<int64_t>(sweep) * HIST_LEN;
             const int col = k == 0 ? HIST_ACTIVE : k == 1 ? HIST_NCLUST : k == 2 ? HIST_NSAT : HIST_COUNTS + k - 3;
@@ -1450,80 +1522,156 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, SmallSmem<NT_, SI
         if (last && k == 0) a.tile_act[0] = static_cast<int32_t>(tot);
         if (last && k == 1) a.tile_ncl[0] = static_cast<int32_t>(tot);
     };
-    unsigned long long prev_act = 0, prev_ncl = 0;
+    // Unite the n listed bonds (site | kind << 13; kind 0: down, 1: the next
+    // site, 2: the row's first site), lanes refilled from the list.
+    auto unite_list = [&](int n) {
+        wave_lds_fence();
+        int i = lane, u = 0, v = 0;
+        auto next = [&]() {
+            const int e = mylist[i], s = e & 0x1FFF, kind = e >> 13;
+            u = lds_ld(&P[s]);
+            v = lds_ld(&P[kind == 0 ? down_of(s) : kind == 1 ? s + 1 : s + 1 - W]);
+        };
+        if (i < n) next();
+        while (i < n) {
+            int done;
+            unite_step<true, true>(P, u, v, done);
+            if (done) {
+                i += 64;
+                if (i < n) next();
+            }
+        }
+        wave_lds_fence();
+    };
+    uint32_t prev_act = 0, prev_ncl = 0;
+    uint32_t next_word[PRE ? MAXM : 1];  // of the next sweep, loaded a sweep ahead
+    auto load_words = [&](int sweep) {
+#pragma unroll
+        for (int m = 0; m < MAXM; ++m)
+            next_word[m] = a.words[(static_cast<size_t>(sweep) * nchunk + min(c0 + m, nchunk - 1)) * 64 + lane];
+    };
+    if constexpr (PRE) load_words(0);
     for (int sweep = 0; sweep < a.n; ++sweep) {
         const uint32_t t = a.t0 + static_cast<uint32_t>(sweep);
         const bool last = sweep + 1 == a.n;
-        for (int i = threadIdx.x; i < N; i += NT) P[i] = i;
-        // bonds of the thread's site pairs (one Philox block per pair): bit
-        // 4m + 2j + k of `bonds` is bond k (0 right, 1 down) of site 2p + j
-        uint32_t bonds = 0;
-        unsigned long long nsat = 0, cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        uint32_t act = 0, ncl = 0;
+        uint32_t word[MAXM];
+        uint32_t pend = 0;  // bit 4m + 2j: down bond of site j, 4m + 2j + 1: its right bond if outside the runs
 #pragma unroll
-        for (int m = 0; m < PAIRS_PER_THREAD; ++m) {
-            const int p = threadIdx.x + NT * m;
-            if (2 * p >= N) break;
-            const U4 blk = philox4x32_10(static_cast<uint32_t>(p), t, TAG_BOND, a.sid, a.k0, a.k1);
+        for (int k = 0; k < 8; ++k) cnt[k] = 0;
+        nsat = 0;
+        for (int g = 0; g < MAXM; g += U) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int i = 2 * p + j;
-                if (i >= N) break;
-                const uint32_t wr = j ? blk.v2 : blk.v0, wd = j ? blk.v3 : blk.v1;
-                const uint32_t si = S[i];
-                const bool er = si == S[right_of(i)], ed = si == S[down_of(i)];
-                if (a.hist) {
-                    nsat += static_cast<unsigned>(er) + static_cast<unsigned>(ed);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) cnt[k] += si == static_cast<uint32_t>(k) ? 1u : 0u;
+            for (int k = 0; k < U; ++k) {
+                const int m = g + k, c = c0 + m;
+                if (m >= M || c >= nchunk) break;
+                const int i0 = c * 128 + 2 * lane;
+                word[m] = PRE ? next_word[m] : small_word(static_cast<uint32_t>(i0), t, a);
+                const uint32_t on = word[m];
+                const Equal e = equal_masks(m);
+                const uint64_t mR0 = e.r0 & lanes_ne(on & 1u, 0u), mD0 = e.d0 & lanes_ne(on & 2u, 0u);
+                const uint64_t mR1 = e.r1 & lanes_ne(on & 4u, 0u), mD1 = e.d1 & lanes_ne(on & 8u, 0u);
+                act += __popcll(mR0) + __popcll(mR1) + __popcll(mD0) + __popcll(mD1);
+                if (last && a.bonds_out) {
+                    const uint32_t b0 = lane_bit(mR0, lane) | (lane_bit(mD0, lane) << 1);
+                    const uint32_t b1 = lane_bit(mR1, lane) | (lane_bit(mD1, lane) << 1);
+                    if (i0 < N) a.bonds_out[i0] = static_cast<uint8_t>(b0);
+                    if (i0 + 1 < N) a.bonds_out[i0 + 1] = static_cast<uint8_t>(b1);
                 }
-                const bool br = a.tany && er && wr <= a.tm1;
-                const bool bd = a.tany && ed && wd <= a.tm1;
-                bonds |= (br ? 1u : 0u) << (4 * m + 2 * j);
-                bonds |= (bd ? 1u : 0u) << (4 * m + 2 * j + 1);
-                if (last && a.bonds_out) a.bonds_out[i] = static_cast<uint8_t>((br ? 1 : 0) | (bd ? 2 : 0));
+                // runs: right bonds that neither end a row nor leave the chunk
+                const uint64_t E0 = lanes_ne((ends >> (2 * m)) & 1u, 0u), E1 = lanes_ne((ends >> (2 * m + 1)) & 1u, 0u);
+                const uint64_t out0 = mR0 & E0, out1 = mR1 & (E1 | 1ull << 63);
+                const EO R = EO{mR0 & ~out0, mR1 & ~out1};
+                pend |= ((lane_bit(mD0, lane) ? 1u : 0u) | (lane_bit(out0, lane) ? 2u : 0u) |
+                         (lane_bit(mD1, lane) ? 4u : 0u) | (lane_bit(out1, lane) ? 8u : 0u)) << (4 * m);
+                const bool e_start = lane_bit(~(R.o << 1), lane), o_start = lane_bit(~R.e, lane);
+                const int x4 = 8 * lane, base4 = 512 * c;
+                const int below4 = wave_max_below(o_start ? x4 + 4 : (e_start ? x4 : 0));
+                const int n0 = base4 + (e_start ? x4 : below4);
+                *reinterpret_cast<int2 *>(&P[i0]) = make_int2(n0, o_start ? base4 + x4 + 4 : n0);
             }
         }
-        const unsigned long long act = static_cast<unsigned>(__popc(bonds));
-        if (sweep > 0 && a.hist) reduce_record(prev_act, prev_ncl, nsat, cnt);  // the previous sweep's record
+        if (sweep > 0 && a.hist) put_record(prev_act, prev_ncl);  // the previous sweep's record
         __syncthreads();
         if (sweep > 0 && a.hist) write_record(sweep - 1, false);
-        // unions of the thread's active bonds, one flat loop: a finished union
-        // takes the next bond at once
-        {
-            uint32_t todo = bonds;
-            int u = 0, v = 0, busy = 0;
-            while (busy || todo) {
-                if (!busy) {
-                    const int b = __ffs(todo) - 1;
-                    todo &= todo - 1;
-                    const int i = 2 * (threadIdx.x + NT * (b >> 2)) + ((b >> 1) & 1);
-                    u = i;
-                    v = (b & 1) ? down_of(i) : right_of(i);
-                    busy = 1;
+        if constexpr (PRE)
+            if (!last) load_words(sweep + 1);
+        // every down bond: the higher of its ends' labels, if still a root, is
+        // linked below the other (a parent stays below its child)
+        int ncon = 0;
+        for (int g = 0; g < MAXM; g += U) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int m = g + k, c = c0 + m;
+                if (m >= M || c >= nchunk) break;
+                const int i0 = c * 128 + 2 * lane;
+                *reinterpret_cast<uint16_t *>(&S[i0]) = static_cast<uint16_t>(word[m] >> 16);
+                const uint32_t bits = pend >> (4 * m);
+                const int u0 = lds_ld(&P[i0]), u1 = lds_ld(&P[i0 + 1]);
+                const int v0 = lds_ld(&P[min(down_of(i0), SITES - 1)]), v1 = lds_ld(&P[min(down_of(i0 + 1), SITES - 1)]);
+                const int hi0 = max(u0, v0), lo0 = min(u0, v0), hi1 = max(u1, v1), lo1 = min(u1, v1);
+                int got0 = hi0, got1 = hi1;
+                if ((bits & 1u) && hi0 != lo0) got0 = link_root(P, hi0, lo0);
+                if ((bits & 4u) && hi1 != lo1) got1 = link_root(P, hi1, lo1);
+                const EO lost = EO{lanes_ne(static_cast<uint32_t>(got0), static_cast<uint32_t>(hi0)) &
+                                       lanes_ne(static_cast<uint32_t>(got0), static_cast<uint32_t>(lo0)),
+                                   lanes_ne(static_cast<uint32_t>(got1), static_cast<uint32_t>(hi1)) &
+                                       lanes_ne(static_cast<uint32_t>(got1), static_cast<uint32_t>(lo1))};
+                const EO out = EO{lanes_ne(bits & 2u, 0u), lanes_ne(bits & 8u, 0u)};
+                if (ncon > TL - 128) {
+                    unite_list(ncon);
+                    ncon = 0;
                 }
-                int done;
-                unite_step(P, u, v, done);
-                busy = !done;
+                eo_append(mylist, ncon, lost, i0, i0 + 1);
+                if ((out.e | out.o) != 0ull) {
+                    if (ncon > TL - 128) {
+                        unite_list(ncon);
+                        ncon = 0;
+                    }
+                    eo_append(mylist, ncon, out, i0 | 2 << 13, (i0 + 1) | ((ends >> (2 * m + 1)) & 1u ? 2 << 13 : 1 << 13));
+                }
             }
         }
+        unite_list(ncon);
         __syncthreads();
-        // Every site to its root (replacing parents by ancestors on the way),
-        // then the new state of its cluster: the draw at the canonical root
-        // (one uniform per cluster), which each site evaluates itself; with
-        // roots spread over the lanes a wave would pay for every draw anyway,
-        // and no table of new states (nor its barrier) is needed.
-        unsigned long long ncl = 0;
-        for (int i = threadIdx.x; i < N; i += NT) {
-            int x = i, px = lds_ld(&P[x]);
-            while (px != x) {
-                x = px;
-                px = lds_ld(&P[x]);
+        // every site's root, by pointer jumping (the trees are final: every
+        // entry only moves up its chain; the chains of a lane's sites are
+        // walked at once; lanes past the lattice are roots of their own)
+        for (int g = 0; g < MAXM; g += U) {
+            int x0[U], x1[U];
+#pragma unroll
+            for (int m = 0; m < U; ++m) {
+                const int2 x = *reinterpret_cast<const int2 *>(&P[(min(c0 + g + m, nchunk - 1)) * 128 + 2 * lane]);
+                x0[m] = x.x;
+                x1[m] = x.y;
             }
-            if (x != i) lds_st(&P[i], x);
-            ncl += x == i ? 1u : 0u;
-            const U4 b = philox4x32_10(static_cast<uint32_t>(x) >> 2, t, TAG_FLIP, a.sid, a.k0, a.k1);
-            S[i] = static_cast<uint8_t>(draw_state(pick(b, static_cast<uint32_t>(x) & 3u), a.q));
-            if (last && a.labels) a.labels[i] = x;
+            for (bool more = true; more;) {
+                more = false;
+#pragma unroll
+                for (int m = 0; m < U; ++m) {
+                    const int p0 = lds_ld(lds_entry<true>(P, x0[m])), p1 = lds_ld(lds_entry<true>(P, x1[m]));
+                    more |= (p0 != x0[m]) | (p1 != x1[m]);
+                    x0[m] = p0;
+                    x1[m] = p1;
+                    *reinterpret_cast<int2 *>(&P[(min(c0 + g + m, nchunk - 1)) * 128 + 2 * lane]) = make_int2(p0, p1);
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < U; ++m) {
+                const int c = c0 + g + m;
+                if (g + m >= M || c >= nchunk) break;
+                const int i0 = c * 128 + 2 * lane;
+                const uint32_t s0 = S[x0[m] >> 2], s1 = S[x1[m] >> 2];
+                *reinterpret_cast<uint16_t *>(&S[i0]) = static_cast<uint16_t>(s0 | (s1 << 8));
+                ncl += __popcll(lanes_eq(static_cast<uint32_t>(x0[m]), static_cast<uint32_t>(4 * i0)) &
+                                lanes_lt(static_cast<uint32_t>(i0), static_cast<uint32_t>(N))) +
+                       __popcll(lanes_eq(static_cast<uint32_t>(x1[m]), static_cast<uint32_t>(4 * i0 + 4)) &
+                                lanes_lt(static_cast<uint32_t>(i0 + 1), static_cast<uint32_t>(N)));
+                if (last && a.labels) {
+                    if (i0 < N) a.labels[i0] = x0[m] >> 2;
+                    if (i0 + 1 < N) a.labels[i0 + 1] = x1[m] >> 2;
+                }
+            }
         }
         __syncthreads();
         prev_act = act;
@@ -1531,14 +1679,17 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, SmallSmem<NT_, SI
     }
     {
         // the last sweep's record, from the final spins
-        unsigned long long nsat = 0, cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int i = threadIdx.x; i < N; i += NT) {
-            const uint32_t si = S[i];
-            nsat += static_cast<unsigned>(si == S[right_of(i)]) + static_cast<unsigned>(si == S[down_of(i)]);
+        nsat = 0;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) cnt[k] += si == static_cast<uint32_t>(k) ? 1u : 0u;
+        for (int k = 0; k < 8; ++k) cnt[k] = 0;
+        if (a.hist) {
+#pragma unroll 1
+            for (int m = 0; m < MAXM; ++m) {
+                if (m >= M || c0 + m >= nchunk) break;
+                (void)equal_masks(m);
+            }
         }
-        reduce_record(prev_act, prev_ncl, nsat, cnt);
+        put_record(prev_act, prev_ncl);
         __syncthreads();
         write_record(a.n - 1, true);
     }
@@ -1548,10 +1699,21 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, SmallSmem<NT_, SI
     }
 }
 
+template <bool PRE>
 __global__ __launch_bounds__(SMALL_NT) void k_small(SmallArgs a)
 {
     __shared__ SmallSmem<SMALL_NT, SMALL_SITES> sm;
-    small_body<SMALL_NT, SMALL_SITES>(a, sm);
+    small_body<SMALL_NT, SMALL_SITES, PRE>(a, sm);
+}
+
+// The words of a.n sweeps from a.t0 on: a wave per chunk and sweep.
+__global__ __launch_bounds__(256) void k_small_words(SmallArgs a)
+{
+    const int nchunk = (a.W * a.H + 127) >> 7, lane = threadIdx.x & 63;
+    const int job = static_cast<int>(blockIdx.x) * 4 + wave_id(), sweep = job / nchunk, c = job - sweep * nchunk;
+    if (sweep >= a.n) return;
+    a.words[static_cast<size_t>(job) * 64 + lane] =
+        small_word(static_cast<uint32_t>(c * 128 + 2 * lane), a.t0 + static_cast<uint32_t>(sweep), a);
 }
 
 // --------------------------------------------------------------- digest ---
@@ -1870,7 +2032,7 @@ __global__ __launch_bounds__(Tile<TH_>::NT) __attribute__((amdgpu_waves_per_eu(8
             s.t0 = t;
             s.ising = L.ising;
             s.n = 1;
-            small_body<NT, SMALL>(s, sm.small);
+            small_body<NT, SMALL, false>(s, sm.small);
             __syncthreads();  // the LDS is reused by the next item
             continue;
         }
