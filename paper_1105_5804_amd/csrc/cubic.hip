@@ -857,17 +857,7 @@ __global__ __launch_bounds__(NT3) void k3_flatten(Flat3Args a)
 // The cluster count of a labeling from the tiles' counts, by one workgroup.
 __global__ __launch_bounds__(1024) void k3_count_out(const int32_t *tile_ncl, int ntiles, int32_t *n_clusters)
 {
-    __shared__ uint32_t red[16];
-    uint32_t ncl = 0;
-    for (int t = threadIdx.x; t < ntiles; t += 1024) ncl += static_cast<uint32_t>(tile_ncl[t]);
-    ncl = wave_sum_u32(ncl);
-    if ((threadIdx.x & 63) == 0) red[wave_id()] = ncl;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t v = 0;
-        for (int k = 0; k < 16; ++k) v += red[k];
-        *n_clusters = static_cast<int32_t>(v);
-    }
+    sum_tiles(tile_ncl, ntiles, n_clusters);
 }
 
 }  // namespace cubic

@@ -747,17 +747,26 @@ struct MergeArgs {
     Batch b;                  // batched launches only
 };
 
-// A wave per tile: its lanes walk the bonds crossing the tile's right edge
-// (TH rows, 64 per pass) and bottom edge (TW columns, two passes).
-// Consecutive crossing bonds that join the same pair of boundary ids are
-// skipped.  The workgroup size (tiles per workgroup, one wave each) is the
-// merge schedule's free parameter; it is read from blockDim.
-// The merge of one tile by the calling wave (`tile` indexes the tile arrays).
-template <bool BATCH, int TH_>
-__device__ __forceinline__ void merge_tile(MergeArgs a, const int tile)
+// Tile consolidation in passes of 64 crossing bonds: a tile's right edge (TH
+// rows, 64 a pass) and its bottom edge (TW columns, two passes); a lane takes
+// one crossing bond of a pass, and consecutive bonds that join the same pair of
+// boundary ids are skipped.  A wave takes all passes of a tile or, on lattices
+// whose passes fit the chip at once, one of them (see the launch): what bounds
+// a pass is its chain of dependent global accesses (edge ids, then parents and
+// keys, then swaps).  The workgroup size (blockDim, in waves) is the merge
+// schedule's free parameter.
+template <int TH_>
+struct MergePasses {
+    static constexpr int RIGHT = (TH_ + 63) / 64, N = RIGHT + 2;
+};
+
+// Passes pass0 .. pass0 + PASSES - 1 of one tile by the calling wave (`tile`
+// indexes the tile arrays).
+template <bool BATCH, int TH_, int PASSES>
+__device__ __forceinline__ void merge_tile(MergeArgs a, const int tile, const int pass0)
 {
     using S = Tile<TH_>;
-    constexpr int TH = S::TH, CAP = S::CAP, EDGE = S::EDGE, XR = S::XR, XW = S::XW;
+    constexpr int TH = S::TH, CAP = S::CAP, EDGE = S::EDGE, XR = S::XR, XW = S::XW, RIGHT = MergePasses<TH_>::RIGHT;
     const int lane = threadIdx.x & 63;
     int tile0 = 0;  // first tile of the lattice in the arrays
     if constexpr (BATCH) {
@@ -768,59 +777,54 @@ __device__ __forceinline__ void merge_tile(MergeArgs a, const int tile)
     const int lt = tile - tile0;
     const int tx = lt % a.g.ntx, ty = lt / a.g.ntx;
     const int tw = min(TW, a.g.W - tx * TW), th = min(TH, a.g.H - ty * TH);
-    const uint16_t *e = a.edges + static_cast<int64_t>(tile) * EDGE;
-    const uint64_t *xb = a.xbits + static_cast<int64_t>(tile) * XW;
     const int ntR = tile0 + ty * a.g.ntx + (tx + 1 == a.g.ntx ? 0 : tx + 1);
     const int ntD = tile0 + (ty + 1 == a.g.nty ? 0 : ty + 1) * a.g.ntx + tx;
-    const uint16_t *eR = a.edges + static_cast<int64_t>(ntR) * EDGE;
-    const uint16_t *eD = a.edges + static_cast<int64_t>(ntD) * EDGE;
-    uint64_t xr[XR];
+    const uint16_t *e = a.edges + static_cast<int64_t>(tile) * EDGE;
+    const uint16_t *eR = a.edges + static_cast<int64_t>(ntR) * EDGE, *eD = a.edges + static_cast<int64_t>(ntD) * EDGE;
+    const uint64_t *xb = a.xbits + static_cast<int64_t>(tile) * XW;
+    // Each pass's crossing bond c of the lane (a row of the right edge or a
+    // column of the bottom edge): the ids on both sides of it and of the bond
+    // before it (for skipping repeats), all loaded up front and inside the
+    // arrays, and whether the two bonds are there.
+    uint16_t ia[PASSES], ib[PASSES], pa[PASSES], pb[PASSES];
+    bool on[PASSES], before[PASSES];
 #pragma unroll
-    for (int j = 0; j < XR; ++j) xr[j] = xb[j];
-    const uint64_t xde = xb[XR], xdo = xb[XR + 1];  // bottom crossing bonds, even / odd columns
-    auto xr_bit = [&](int y) { return (xr[y >> 6] >> (y & 63)) & 1ull; };
-    auto xd_bit = [&](int x) { return (((x & 1) ? xdo : xde) >> (x >> 1)) & 1ull; };
-    // Passes of 64 lanes: the right edge (TH rows), then the bottom edge in
-    // two halves (TW columns).  Every edge entry a lane needs, and the one
-    // before it (for skipping repeats), is loaded up front; all lie inside
-    // the tiles' edge arrays.
-    constexpr int RP = (TH + 63) / 64;  // passes over the right edge
-    const uint16_t *er = e + 2 * TW + TH, *el = eR + 2 * TW, *eb = e + TW;
-    uint16_t r_a[RP], r_b[RP], r_ap[RP], r_bp[RP];
-#pragma unroll
-    for (int j = 0; j < RP; ++j) {
-        const int y = min(64 * j + lane, TH - 1), ym = max(y - 1, 0);
-        r_a[j] = er[y];
-        r_b[j] = el[y];
-        r_ap[j] = er[ym];
-        r_bp[j] = el[ym];
+    for (int k = 0; k < PASSES; ++k) {
+        const int pass = pass0 + k;
+        const bool right = pass < RIGHT;
+        const int c = 64 * (right ? pass : pass - RIGHT) + lane;
+        const uint16_t *ea = right ? e + 2 * TW + TH : e + TW, *eb = right ? eR + 2 * TW : eD;
+        const int cl = min(c, (right ? TH : TW) - 1), cm = max(cl - 1, 0);
+        ia[k] = ea[cl];
+        ib[k] = eb[cl];
+        pa[k] = ea[cm];
+        pb[k] = eb[cm];
+        // rows of the right edge in words of 64, the bottom edge's even
+        // columns, then its odd ones
+        auto bit_of = [&](int i) {
+            const uint64_t w = right ? xb[i >> 6] : ((i & 1) ? xb[XR + 1] : xb[XR]);
+            return ((w >> (right ? i & 63 : i >> 1)) & 1ull) != 0ull;
+        };
+        on[k] = c < (right ? th : tw) && bit_of(cl);
+        before[k] = c > 0 && bit_of(cm);
     }
-    const int lm = max(lane - 1, 0);
-    const uint16_t b1_a = eb[lane], b1_b = eD[lane], b1_ap = eb[lm], b1_bp = eD[lm];
-    const uint16_t b2_a = eb[64 + lane], b2_b = eD[64 + lane], b2_ap = eb[63 + lane], b2_bp = eD[63 + lane];
-    // Both ends of a crossing bond are border sites, whose codes are boundary
-    // ids (< CAP); the bound keeps any other entry from addressing memory
-    // outside the tiles' tables.
-    auto ids = [](uint16_t u, uint16_t v) { return u < CAP && v < CAP; };
 #pragma unroll
-    for (int j = 0; j < RP; ++j) {
-        const int y = 64 * j + lane;
-        if (y < th && xr_bit(y) && !(y > 0 && xr_bit(y - 1) && r_ap[j] == r_a[j] && r_bp[j] == r_b[j]) &&
-            ids(r_a[j], r_b[j]))
-            gunite(a.gparent, a.gkey, tile * CAP + r_a[j], ntR * CAP + r_b[j]);
+    for (int k = 0; k < PASSES; ++k) {
+        // Both ends of a crossing bond are border sites, whose codes are
+        // boundary ids (< CAP); the bound keeps any other entry from
+        // addressing memory outside the tiles' tables.
+        if (on[k] && !(before[k] && pa[k] == ia[k] && pb[k] == ib[k]) && ia[k] < CAP && ib[k] < CAP)
+            gunite(a.gparent, a.gkey, tile * CAP + ia[k], (pass0 + k < RIGHT ? ntR : ntD) * CAP + ib[k]);
     }
-    if (lane < tw && xd_bit(lane) && !(lane > 0 && xd_bit(lane - 1) && b1_ap == b1_a && b1_bp == b1_b) &&
-        ids(b1_a, b1_b))
-        gunite(a.gparent, a.gkey, tile * CAP + b1_a, ntD * CAP + b1_b);
-    const int x2 = 64 + lane;
-    if (x2 < tw && xd_bit(x2) && !(xd_bit(x2 - 1) && b2_ap == b2_a && b2_bp == b2_b) && ids(b2_a, b2_b))
-        gunite(a.gparent, a.gkey, tile * CAP + b2_a, ntD * CAP + b2_b);
 }
 
-template <bool BATCH, int TH_>
+template <bool BATCH, int TH_, bool SPLIT>
 __global__ __launch_bounds__(1024) void k_merge(MergeArgs a)
 {
-    int tile = blockIdx.x * static_cast<int>(blockDim.x >> 6) + wave_id();
+    constexpr int NP = MergePasses<TH_>::N;
+    const int job = blockIdx.x * static_cast<int>(blockDim.x >> 6) + wave_id();
+    int tile = SPLIT ? job / NP : job;
+    const int pass = SPLIT ? job - tile * NP : 0;
     if constexpr (BATCH) {
         if (tile >= a.b.ntiles) return;
         tile += a.b.tile_base;
@@ -828,7 +832,7 @@ __global__ __launch_bounds__(1024) void k_merge(MergeArgs a)
         if (tile >= a.g.ntiles) return;
         if (a.g.rev) tile = a.g.ntiles - 1 - tile;
     }
-    merge_tile<BATCH, TH_>(a, tile);
+    merge_tile<BATCH, TH_, SPLIT ? 1 : NP>(a, tile, pass);
 }
 
 // -------------------------------------------------------------- flatten ----
@@ -936,7 +940,7 @@ struct FlatSmem {
     int ncl_w[NWAVE];
     int32_t Ci[SIZES ? TSITES : 1];               // sizes of interior clusters
     int32_t Cb[SIZES ? CAP : 1];                  // per-tile part of boundary clusters
-    int32_t rowc[TH + 1];
+    int32_t rowc[TH];
     uint32_t seedw_s[MODE == M_FEW ? NWAVE : 1][32];  // M_FEW: seed-map words of each wave's rows
 };
 
@@ -956,6 +960,20 @@ __device__ __forceinline__ void load_batch_flat(FlatArgs &a, int tile, int &lt)
 }
 
 constexpr uint8_t FEW_KEEP = 0xFF;
+
+// Exclusive prefix sums of v[0 .. n - 1] in place by one wave (n <= TH <= 128).
+template <int TH>
+__device__ __forceinline__ void exclusive_rows(int32_t *v, int n, int lane)
+{
+    uint32_t carry = 0;
+#pragma unroll
+    for (int y = 0; y < TH; y += 64) {
+        const uint32_t x = y + lane < n ? static_cast<uint32_t>(v[y + lane]) : 0u;
+        const uint32_t s = wave_scan_u32(x);
+        if (y + lane < n) v[y + lane] = static_cast<int32_t>(carry + s - x);
+        carry += __builtin_amdgcn_readlane(static_cast<int>(s), 63);
+    }
+}
 
 // The flatten + flip of one tile (`tile` in the arrays, `lt` inside its
 // lattice), by a Tile<TH>::NT-thread workgroup.  M_FEW flips only the seeded
@@ -1187,15 +1205,7 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
             }
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int acc = 0;
-            for (int ly = 0; ly < th; ++ly) {
-                const int n = rowc[ly];
-                rowc[ly] = acc;
-                acc += n;
-            }
-            rowc[th] = acc;
-        }
+        if (wave == 0) exclusive_rows<TH>(rowc, th, lane);
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < RPW; ++r) {
@@ -1236,21 +1246,8 @@ __global__ __launch_bounds__(Tile<TH_>::NT) void k_flatten(FlatArgs a)
     flatten_body<MODE, SIZES, TH_>(a, tile, lt, sm);
 }
 
-// Sum of n per-tile int32 counters by one workgroup.
-__global__ __launch_bounds__(1024) void k_sum_tiles(const int32_t *v, int n, int32_t *out)
-{
-    __shared__ uint32_t red[16];
-    uint32_t acc = 0;
-    for (int i = threadIdx.x; i < n; i += 1024) acc += static_cast<uint32_t>(v[i]);
-    acc = wave_sum_u32(acc);
-    if ((threadIdx.x & 63) == 0) red[wave_id()] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t t = 0;
-        for (int w = 0; w < 16; ++w) t += red[w];
-        *out = static_cast<int32_t>(t);
-    }
-}
+// Sum of n per-tile int32 counters (256-byte aligned) by one workgroup.
+__global__ __launch_bounds__(1024) void k_sum_tiles(const int32_t *v, int n, int32_t *out) { sum_tiles(v, n, out); }
 
 // ------------------------------------------------------------ root list ----
 
@@ -1260,30 +1257,30 @@ constexpr int SCAN_ITEMS = NT * 8;
 
 __global__ __launch_bounds__(NT) void k_scan_block(const int32_t *in, int32_t *out, int64_t n, int32_t *totals)
 {
-    __shared__ int32_t part[NT];
+    __shared__ uint32_t part[NWAVE];
     const int64_t base = static_cast<int64_t>(blockIdx.x) * SCAN_ITEMS + threadIdx.x * 8;
-    int32_t v[8];
-    int32_t sum = 0;
+    uint32_t v[8], sum = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        v[j] = (base + j < n) ? in[base + j] : 0;
+        v[j] = (base + j < n) ? static_cast<uint32_t>(in[base + j]) : 0u;
         sum += v[j];
     }
-    part[threadIdx.x] = sum;
+    const uint32_t s = wave_scan_u32(sum);
+    const int w = wave_id();
+    if ((threadIdx.x & 63) == 63) part[w] = s;
     __syncthreads();
-    for (int off = 1; off < NT; off <<= 1) {
-        const int32_t add = (static_cast<int>(threadIdx.x) >= off) ? part[threadIdx.x - off] : 0;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
+    uint32_t acc = s - sum, all = 0;
+#pragma unroll
+    for (int j = 0; j < NWAVE; ++j) {
+        acc += j < w ? part[j] : 0u;
+        all += part[j];
     }
-    int32_t acc = part[threadIdx.x] - sum;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        if (base + j < n) out[base + j] = acc;
+        if (base + j < n) out[base + j] = static_cast<int32_t>(acc);
         acc += v[j];
     }
-    if (threadIdx.x == NT - 1 && totals) totals[blockIdx.x] = part[NT - 1];
+    if (threadIdx.x == 0 && totals) totals[blockIdx.x] = static_cast<int32_t>(all);
 }
 
 __global__ __launch_bounds__(NT) void k_scan_add(int32_t *out, int64_t n, const int32_t *offs)
@@ -1294,7 +1291,9 @@ __global__ __launch_bounds__(NT) void k_scan_add(int32_t *out, int64_t n, const 
 
 struct EmitArgs {
     Grid g;
-    const int32_t *row_off;   // [H*ntx + 1] exclusive offsets
+    const int32_t *row_count; // [H*ntx] roots per (row, tile column) (DIRECT)
+    const int32_t *row_off;   // [H*ntx + 1] their exclusive scan inside blocks of SCAN_ITEMS (otherwise)
+    const int32_t *block_off; // offsets of the blocks, or nullptr if there is one
     const int32_t *rl_slot;
     const int32_t *rl_size;
     const int32_t *gsize;
@@ -1306,49 +1305,123 @@ struct EmitArgs {
 
 // Write each tile's roots (ascending site index within a row) at their global
 // positions; boundary clusters take their size from the global root id.
-template <int TH_>
+// DIRECT: a tile adds up itself the counts that come before its rows' roots
+// (every count of the rows above it, then its own rows' up to its column);
+// the counts are few enough that reading them again in every tile is cheaper
+// than the scan's launches.
+// Bound by latency on small lattices.  With the rows' counts added up one after
+// the other by one thread (here and in the flatten), a three-launch scan and an
+// atomic on the largest size from every wave, a sweep with sizes took 58 us on
+// 512 x 500 (q = 3), now 44; 352 -> 159 on 4096^2 and 4726 -> 1909 on 16384^2
+// (there the atomics).
+template <int TH_, bool DIRECT>
 __device__ __forceinline__ void emit_body(const EmitArgs &a, const int tile)
 {
-    constexpr int TH = Tile<TH_>::TH, TSITES = Tile<TH_>::TSITES;
-    __shared__ int32_t rstart[TH + 1];
-    const int tx = tile % a.g.ntx, ty = tile / a.g.ntx;
+    constexpr int TH = Tile<TH_>::TH, TSITES = Tile<TH_>::TSITES, RW = (TH + NWAVE - 1) / NWAVE;
+    __shared__ int32_t rstart[TH];  // roots of the tile in the rows above
+    __shared__ int32_t rfirst[TH];  // global position of the row's first root in the tile
+    __shared__ int32_t rsum[DIRECT ? TH : 1];
+    __shared__ uint32_t red[NWAVE];
+    __shared__ int32_t n_s, mx_s;
+    const int ntx = a.g.ntx, tx = tile % ntx, ty = tile / ntx;
     const int gx0 = tx * TW, gy0 = ty * TH;
     const int th = min(TH, a.g.H - gy0);
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int ly = 0; ly < th; ++ly) {
-            const int64_t ix = static_cast<int64_t>(gy0 + ly) * a.g.ntx + tx;
-            rstart[ly] = acc;
-            acc += a.row_off[ix + 1] - a.row_off[ix];
+    const int lane = threadIdx.x & 63, w = wave_id();
+    // the thread's first entry, read ahead of its use (inside the tile's list,
+    // whatever it holds)
+    const int64_t list = static_cast<int64_t>(tile) * TSITES;
+    int slot = a.rl_slot[list + threadIdx.x], sz = a.rl_size[list + threadIdx.x];
+    if (threadIdx.x == 0) mx_s = 0;
+    if constexpr (DIRECT) {
+        uint32_t above = 0;
+        for (int i = threadIdx.x; i < gy0 * ntx; i += NT) above += static_cast<uint32_t>(a.row_count[i]);
+        uint32_t v[RW];  // the wave's rows w, w + NWAVE, ...: all loads first
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const int ly = w + r * NWAVE;
+            v[r] = ly < th && lane < ntx ? static_cast<uint32_t>(a.row_count[(gy0 + ly) * ntx + lane]) : 0u;
         }
-        rstart[th] = acc;
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const int ly = w + r * NWAVE;
+            if (ly >= th) break;
+            uint32_t all = v[r], left = lane < tx ? v[r] : 0u, own = lane == tx ? v[r] : 0u;
+            for (int x = lane + 64; x < ntx; x += 64) {
+                const uint32_t u = static_cast<uint32_t>(a.row_count[(gy0 + ly) * ntx + x]);
+                all += u;
+                left += x < tx ? u : 0u;
+                own += x == tx ? u : 0u;
+            }
+            all = wave_sum_u32(all);
+            left = wave_sum_u32(left);
+            own = wave_sum_u32(own);
+            if (lane == 0) {
+                rsum[ly] = static_cast<int32_t>(all);
+                rfirst[ly] = static_cast<int32_t>(left);
+                rstart[ly] = static_cast<int32_t>(own);
+            }
+        }
+        above = wave_sum_u32(above);
+        if (lane == 0) red[w] = above;
+    } else if (w == 0) {
+        auto off = [&](int64_t i) { return a.row_off[i] + (a.block_off ? a.block_off[i / SCAN_ITEMS] : 0); };
+        for (int ly = lane; ly < th; ly += 64) {
+            const int64_t ix = static_cast<int64_t>(gy0 + ly) * ntx + tx;
+            const int32_t first = off(ix);
+            rfirst[ly] = first;
+            rstart[ly] = off(ix + 1) - first;
+        }
+        if (a.n_clusters && tile == 0 && lane == 0) *a.n_clusters = off(static_cast<int64_t>(a.g.H) * ntx);
     }
     __syncthreads();
-    const int n = rstart[th];
+    if (w == 0) {
+        uint32_t carry = 0, carry_sum = 0;
+        if constexpr (DIRECT)
+            for (int j = 0; j < NWAVE; ++j) carry_sum += red[j];
+#pragma unroll
+        for (int y = 0; y < TH; y += 64) {
+            const bool in = y + lane < th;
+            const uint32_t own = in ? static_cast<uint32_t>(rstart[y + lane]) : 0u, s = wave_scan_u32(own);
+            if (in) rstart[y + lane] = static_cast<int32_t>(carry + s - own);
+            carry += __builtin_amdgcn_readlane(static_cast<int>(s), 63);
+            if constexpr (DIRECT) {
+                const uint32_t all = in ? static_cast<uint32_t>(rsum[y + lane]) : 0u, t = wave_scan_u32(all);
+                if (in) rfirst[y + lane] += static_cast<int32_t>(carry_sum + t - all);
+                carry_sum += __builtin_amdgcn_readlane(static_cast<int>(t), 63);
+            }
+        }
+        if (lane == 0) n_s = static_cast<int32_t>(carry);
+        // the last band of rows ends with the number of clusters
+        if (DIRECT && a.n_clusters && tile == a.g.ntiles - 1 && lane == 0) *a.n_clusters = static_cast<int32_t>(carry_sum);
+    }
+    __syncthreads();
+    const int n = n_s;
     int mx = 0;
     for (int j = threadIdx.x; j < n; j += NT) {
-        const int64_t o = static_cast<int64_t>(tile) * TSITES + j;
-        const int slot = a.rl_slot[o];
+        if (j >= NT) {
+            slot = a.rl_slot[list + j];
+            sz = a.rl_size[list + j];
+        }
         const int ly = slot >> 7;
-        const int pos = a.row_off[static_cast<int64_t>(gy0 + ly) * a.g.ntx + tx] + (j - rstart[ly]);
-        const int sz = a.rl_size[o];
+        const int pos = rfirst[ly] + (j - rstart[ly]);
         const int size = sz >= 0 ? sz : a.gsize[-sz - 1];
         a.roots[pos] = (gy0 + ly) * a.g.W + gx0 + (slot & (TW - 1));
         a.sizes[pos] = size;
         mx = max(mx, size);
     }
     if (a.max_size) {
-        mx = wave_max(mx);
-        if ((threadIdx.x & 63) == 0 && mx > 0) atomicMax(a.max_size, mx);
+        // one atomic a tile, and none from a tile whose largest is no larger
+        // than what is there (a stale value is smaller still)
+        if (mx > 0) atomicMax(&mx_s, mx);
+        __syncthreads();
+        if (threadIdx.x == 0 && mx_s > *a.max_size) atomicMax(a.max_size, mx_s);
     }
-    if (a.n_clusters && tile == 0 && threadIdx.x == 0)
-        *a.n_clusters = a.row_off[static_cast<int64_t>(a.g.H) * a.g.ntx];
 }
 
-template <int TH_>
+template <int TH_, bool DIRECT>
 __global__ __launch_bounds__(NT) void k_emit(EmitArgs a)
 {
-    emit_body<TH_>(a, xcd_remap(blockIdx.x, a.g.ntiles));
+    emit_body<TH_, DIRECT>(a, xcd_remap(blockIdx.x, a.g.ntiles));
 }
 
 // ------------------------------------------------------- small lattices ---
@@ -1767,7 +1840,7 @@ struct ReqDesc {
     uint16_t *codes, *edges;
     int32_t *gkey, *gparent, *gsize, *nb, *tile_ncl;
     uint64_t *xbits;
-    int32_t *row_count, *row_off, *rl_slot, *rl_size;  // with sizes
+    int32_t *row_count, *rl_slot, *rl_size;  // with sizes
 };
 
 struct ReqBatch {
@@ -1806,7 +1879,8 @@ __global__ __launch_bounds__(Tile<TH_>::NT) __attribute__((amdgpu_waves_per_eu(8
 template <int TH_>
 __global__ __launch_bounds__(1024) void k_merge_reqs(ReqBatch rb)
 {
-    const int t = blockIdx.x * static_cast<int>(blockDim.x >> 6) + wave_id();
+    constexpr int NP = MergePasses<TH_>::N;
+    const int job = blockIdx.x * static_cast<int>(blockDim.x >> 6) + wave_id(), t = job / NP;
     if (t >= rb.ntiles) return;
     int lt;
     const ReqDesc &R = req_of(rb, t, lt);
@@ -1816,7 +1890,7 @@ __global__ __launch_bounds__(1024) void k_merge_reqs(ReqBatch rb)
     m.xbits = R.xbits;
     m.gkey = R.gkey;
     m.gparent = R.gparent;
-    merge_tile<false, TH_>(m, lt);
+    merge_tile<false, TH_, 1>(m, lt, job - t * NP);
 }
 
 template <bool SIZES, int TH_>
@@ -1847,7 +1921,7 @@ __global__ __launch_bounds__(NT) void k_emit_reqs(ReqBatch rb)
     const ReqDesc &R = req_of(rb, xcd_remap(blockIdx.x, rb.ntiles), lt);
     EmitArgs e{};
     e.g = R.g;
-    e.row_off = R.row_off;
+    e.row_count = R.row_count;
     e.rl_slot = R.rl_slot;
     e.rl_size = R.rl_size;
     e.gsize = R.gsize;
@@ -1855,55 +1929,23 @@ __global__ __launch_bounds__(NT) void k_emit_reqs(ReqBatch rb)
     e.sizes = R.sizes;
     e.max_size = nullptr;
     e.n_clusters = R.n_clusters;
-    emit_body<TH_>(e, lt);
+    emit_body<TH_, true>(e, lt);
 }
 
-// One workgroup per request: with sizes, the exclusive scan of the request's
-// per-(row, tile column) root counts (and their total, the cluster count,
-// which the emit writes); without, the cluster count as the sum of its tiles'.
-template <bool SIZES>
-__global__ __launch_bounds__(NT) void k_scan_reqs(const ReqDesc *req)
+// Without sizes, one workgroup per request adds up its tiles' cluster counts.
+__global__ __launch_bounds__(NT) void k_count_reqs(const ReqDesc *req)
 {
     const ReqDesc &R = req[blockIdx.x];
-    __shared__ int32_t part[NT];
-    if constexpr (SIZES) {
-        const int64_t n = static_cast<int64_t>(R.g.H) * R.g.ntx + 1;  // the closing slot is 0
-        int32_t carry = 0;
-        for (int64_t b0 = 0; b0 < n; b0 += SCAN_ITEMS) {
-            const int64_t base = b0 + static_cast<int64_t>(threadIdx.x) * 8;
-            int32_t v[8], sum = 0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                v[j] = (base + j < n) ? R.row_count[base + j] : 0;
-                sum += v[j];
-            }
-            part[threadIdx.x] = sum;
-            __syncthreads();
-            for (int off = 1; off < NT; off <<= 1) {
-                const int32_t add = (static_cast<int>(threadIdx.x) >= off) ? part[threadIdx.x - off] : 0;
-                __syncthreads();
-                part[threadIdx.x] += add;
-                __syncthreads();
-            }
-            int32_t acc = carry + part[threadIdx.x] - sum;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if (base + j < n) R.row_off[base + j] = acc;
-                acc += v[j];
-            }
-            carry += part[NT - 1];
-            __syncthreads();
-        }
-    } else {
-        int32_t acc = 0;
-        for (int k = threadIdx.x; k < R.g.ntiles; k += NT) acc += R.tile_ncl[k];
-        part[threadIdx.x] = acc;
-        __syncthreads();
-        for (int off = NT / 2; off > 0; off >>= 1) {
-            if (static_cast<int>(threadIdx.x) < off) part[threadIdx.x] += part[threadIdx.x + off];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0 && R.n_clusters) *R.n_clusters = part[0];
+    __shared__ uint32_t part[NWAVE];
+    uint32_t acc = 0;
+    for (int k = threadIdx.x; k < R.g.ntiles; k += NT) acc += static_cast<uint32_t>(R.tile_ncl[k]);
+    acc = wave_sum_u32(acc);
+    if ((threadIdx.x & 63) == 0) part[wave_id()] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0 && R.n_clusters) {
+        uint32_t t = 0;
+        for (int w = 0; w < NWAVE; ++w) t += part[w];
+        *R.n_clusters = static_cast<int32_t>(t);
     }
 }
 
@@ -2057,7 +2099,7 @@ __global__ __launch_bounds__(Tile<TH_>::NT) __attribute__((amdgpu_waves_per_eu(8
             const LatticeDesc &L = a.ta.b.lat[j];
             fused_wait(&a.tiles_done[j], (launch + 1) * static_cast<unsigned long long>(L.g.ntiles), a.fault);
             const int w = wave_id();
-            if (w < grp.y) merge_tile<true, TH_>(a.ma, grp.x + w);
+            if (w < grp.y) merge_tile<true, TH_, MergePasses<TH_>::N>(a.ma, grp.x + w, 0);
             fused_signal(&a.merge_done[j]);
             continue;
         }

@@ -209,20 +209,23 @@ sw_status device_status(hipError_t e, const char *where)
 
 sw_status launch_status(const char *where) { return device_status(hipGetLastError(), where); }
 
-// Exclusive scan of n int32 values (in -> out) with block totals in tmp.
-void scan_i32(const int32_t *in, int32_t *out, int64_t n, char *tmp, hipStream_t s)
+// Exclusive scan of n int32 values (in -> out) inside blocks of SCAN_ITEMS;
+// returns the blocks' offsets (in tmp), to be added by the reader, or nullptr
+// if there is one block.
+const int32_t *scan_i32(const int32_t *in, int32_t *out, int64_t n, char *tmp, hipStream_t s)
 {
     const int64_t nb = cdiv(n, SCAN_ITEMS);
     if (nb <= 1) {
         hipLaunchKernelGGL(k_scan_block, dim3(1), dim3(NT), 0, s, in, out, n, nullptr);
-        return;
+        return nullptr;
     }
     int32_t *tot = reinterpret_cast<int32_t *>(tmp);
     int32_t *tot_off = reinterpret_cast<int32_t *>(tmp + align_up(static_cast<size_t>(nb) * 4));
     char *next = tmp + 2 * align_up(static_cast<size_t>(nb) * 4);
     hipLaunchKernelGGL(k_scan_block, dim3(static_cast<unsigned>(nb)), dim3(NT), 0, s, in, out, n, tot);
-    scan_i32(tot, tot_off, nb, next, s);
-    hipLaunchKernelGGL(k_scan_add, dim3(static_cast<unsigned>(cdiv(n, NT))), dim3(NT), 0, s, out, n, tot_off);
+    if (const int32_t *off = scan_i32(tot, tot_off, nb, next, s))
+        hipLaunchKernelGGL(k_scan_add, dim3(static_cast<unsigned>(cdiv(nb, NT))), dim3(NT), 0, s, tot_off, nb, off);
+    return tot_off;
 }
 
 TileArgs tile_args(const Layout &L, void *ws, const uint8_t *in)
@@ -266,14 +269,26 @@ void launch_tile(const Layout &L, const TileArgs &ta, hipStream_t s)
     });
 }
 
-// The merge: mw tiles per workgroup, one wave each, over ntiles tiles.
+// The merge over ntiles tiles: mw waves per workgroup, a wave per pass of a
+// tile while that leaves waves to spare on the chip, else a wave per tile.
+// A q = 3 sweep, a wave per tile -> per pass: 512 x 500 34.1 -> 27.5 us, 2048^2
+// 44.2 -> 37.9, 4096^2 (2048 tiles) 79.7 -> 76.9, 8192 x 4096 127 -> 130,
+// 16384^2 836 -> 871.
+constexpr int64_t MERGE_SPLIT = 2048;
+
 template <bool BATCH>
 void launch_merge(const Layout &L, const MergeArgs &ma, int64_t ntiles, hipStream_t s)
 {
-    const dim3 grid(static_cast<unsigned>(cdiv(ntiles, L.mw))), block(static_cast<unsigned>(64 * L.mw));
+    const dim3 block(static_cast<unsigned>(64 * L.mw));
     with_tile_h(L.d.th, [&](auto c) {
         constexpr int TH = decltype(c)::value;
-        hipLaunchKernelGGL((k_merge<BATCH, TH>), grid, block, 0, s, ma);
+        if (ntiles <= MERGE_SPLIT) {
+            const dim3 grid(static_cast<unsigned>(cdiv(ntiles * MergePasses<TH>::N, L.mw)));
+            hipLaunchKernelGGL((k_merge<BATCH, TH, true>), grid, block, 0, s, ma);
+        } else {
+            const dim3 grid(static_cast<unsigned>(cdiv(ntiles, L.mw)));
+            hipLaunchKernelGGL((k_merge<BATCH, TH, false>), grid, block, 0, s, ma);
+        }
     });
 }
 
@@ -305,16 +320,19 @@ FlatArgs flat_args(const Layout &L, void *ws)
     return f;
 }
 
+// Up to this many per-(row, tile column) root counts the tiles add up what
+// comes before them themselves; above, a scan does.  A sweep with sizes, scan ->
+// added up: 1001 x 1333 (10664 counts) 59.1 -> 55.8 us, 1024 x 2048 (16384) 60.9
+// -> 59.5, 2048^2 (32768) 75.5 -> 79.4.
+constexpr int64_t EMIT_DIRECT = 16384;
+
 // Roots in ascending order and their sizes from a flatten pass with sizes:
-// scan the per-(row, tile column) root counts, then place each tile's roots.
+// each tile's roots are placed by the per-(row, tile column) root counts.
 void emit_sizes(const Layout &L, void *ws, const FlatArgs &fa, int32_t *roots, int32_t *sizes, int32_t *max_size,
                 int32_t *n_clusters, hipStream_t s)
 {
-    int32_t *row_off = at<int32_t>(ws, L.row_off);
-    scan_i32(fa.row_count, row_off, L.nrow + 1, at<char>(ws, L.scan_tmp), s);
     EmitArgs ea{};
     ea.g = L.g;
-    ea.row_off = row_off;
     ea.rl_slot = fa.rl_slot;
     ea.rl_size = fa.rl_size;
     ea.gsize = fa.gsize;
@@ -322,9 +340,21 @@ void emit_sizes(const Layout &L, void *ws, const FlatArgs &fa, int32_t *roots, i
     ea.sizes = sizes;
     ea.max_size = max_size;
     ea.n_clusters = n_clusters;
+    const dim3 grid(static_cast<unsigned>(L.g.ntiles));
+    if (L.nrow <= EMIT_DIRECT) {
+        ea.row_count = fa.row_count;
+        with_tile_h(L.d.th, [&](auto c) {
+            constexpr int TH = decltype(c)::value;
+            hipLaunchKernelGGL((k_emit<TH, true>), grid, dim3(NT), 0, s, ea);
+        });
+        return;
+    }
+    int32_t *row_off = at<int32_t>(ws, L.row_off);
+    ea.row_off = row_off;
+    ea.block_off = scan_i32(fa.row_count, row_off, L.nrow + 1, at<char>(ws, L.scan_tmp), s);
     with_tile_h(L.d.th, [&](auto c) {
         constexpr int TH = decltype(c)::value;
-        hipLaunchKernelGGL(k_emit<TH>, dim3(static_cast<unsigned>(L.g.ntiles)), dim3(NT), 0, s, ea);
+        hipLaunchKernelGGL((k_emit<TH, false>), grid, dim3(NT), 0, s, ea);
     });
 }
 
@@ -1430,7 +1460,6 @@ sw_status label_batch(const LabelRequest *r, int32_t n, int32_t mode, bool sizes
         d.tile_ncl = at<int32_t>(ws, L.tile_ncl);
         d.xbits = at<uint64_t>(ws, L.xbits);
         d.row_count = sizes ? at<int32_t>(ws, L.row_count) : nullptr;
-        d.row_off = sizes ? at<int32_t>(ws, L.row_off) : nullptr;
         d.rl_slot = sizes ? at<int32_t>(ws, L.rl_slot) : nullptr;
         d.rl_size = sizes ? at<int32_t>(ws, L.rl_size) : nullptr;
         for (int t = 0; t < L.g.ntiles; ++t) req_of_tile[tile + t] = k;
@@ -1454,14 +1483,14 @@ sw_status label_batch(const LabelRequest *r, int32_t n, int32_t mode, bool sizes
     default: hipLaunchKernelGGL((k_tile_reqs<M_SITES, TH>), tiles, dim3(Tile<TH>::NT), 0, s, rb); break;
     }
     constexpr int MW = MERGE_WAVES_DEFAULT;
-    hipLaunchKernelGGL(k_merge_reqs<TH>, dim3(static_cast<unsigned>(cdiv(tile, MW))), dim3(64 * MW), 0, s, rb);
+    hipLaunchKernelGGL(k_merge_reqs<TH>, dim3(static_cast<unsigned>(cdiv(static_cast<int64_t>(tile) * MergePasses<TH>::N, MW))),
+                       dim3(64 * MW), 0, s, rb);
     if (sizes) {
         hipLaunchKernelGGL((k_flatten_reqs<true, TH>), tiles, dim3(Tile<TH>::NT), 0, s, rb);
-        hipLaunchKernelGGL(k_scan_reqs<true>, dim3(static_cast<unsigned>(n)), dim3(NT), 0, s, rb.req);
         hipLaunchKernelGGL(k_emit_reqs<TH>, tiles, dim3(NT), 0, s, rb);
     } else {
         hipLaunchKernelGGL((k_flatten_reqs<false, TH>), tiles, dim3(Tile<TH>::NT), 0, s, rb);
-        hipLaunchKernelGGL(k_scan_reqs<false>, dim3(static_cast<unsigned>(n)), dim3(NT), 0, s, rb.req);
+        hipLaunchKernelGGL(k_count_reqs, dim3(static_cast<unsigned>(n)), dim3(NT), 0, s, rb.req);
     }
     return launch_status("batched labeling");
 }

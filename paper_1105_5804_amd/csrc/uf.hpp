@@ -172,13 +172,13 @@ __device__ __forceinline__ int gfind(const int *G, int x)
 }
 
 // Roots of a and b, both chains walked at once (their loads overlap); the
-// body is straight-line, a finished chain just reloads its root.
-__device__ __forceinline__ void gfind2(int *G, int &a, int &b)
+// body is straight-line, a finished chain just reloads its root.  pa and pb are
+// the parents of a and b as just read.
+__device__ __forceinline__ void gfind2_from(int *G, int &a, int &b, int pa, int pb)
 {
     // path halving: a node passed over is pointed at its grandparent (an
     // ancestor, so concurrent walks stay valid), which keeps the trees of
     // clusters that span many tiles shallow
-    int pa = G[a], pb = G[b];
     while (pa != a || pb != b) {
         const int ga = G[pa], gb = G[pb];
         if (ga != pa) G[a] = ga;
@@ -189,17 +189,24 @@ __device__ __forceinline__ void gfind2(int *G, int &a, int &b)
         pb = G[b];
     }
 }
+__device__ __forceinline__ void gfind2(int *G, int &a, int &b) { gfind2_from(G, a, b, G[a], G[b]); }
 
 __device__ __forceinline__ void gunite(int *G, const int *key, int a, int b)
 {
-    gfind2(G, a, b);
+    // the keys are read with the parents: most ids are still roots
+    const int a0 = a, b0 = b, pa = G[a], pb = G[b];
+    int ka = key[a], kb = key[b];
+    gfind2_from(G, a, b, pa, pb);
+    if (a != a0) ka = key[a];
+    if (b != b0) kb = key[b];
     for (;;) {
         if (a == b) return;
-        const int ka = key[a], kb = key[b];
         if (ka < kb) {
-            const int t = a;
+            const int t = a, k = ka;
             a = b;
             b = t;
+            ka = kb;
+            kb = k;
         }
         int expect = a;
         if (__hip_atomic_compare_exchange_strong(&G[a], &expect, b, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
@@ -207,6 +214,8 @@ __device__ __forceinline__ void gunite(int *G, const int *key, int a, int b)
             return;
         a = expect;  // a was linked meanwhile: continue from its parent
         gfind2(G, a, b);
+        ka = key[a];
+        kb = key[b];
     }
 }
 
@@ -218,7 +227,8 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v)
 }
 
 // The same for 32-bit values, in all lanes: row sums by DPP row shifts, then
-// row broadcasts (rows outside a broadcast's row mask add 0).
+// row broadcasts (a read from outside the row, and rows outside a broadcast's
+// row mask, add 0).
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t u)
 {
     int v = static_cast<int>(u);
@@ -231,6 +241,19 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t u)
     return static_cast<uint32_t>(__builtin_amdgcn_readlane(v, 63));
 }
 
+// Inclusive prefix sums over the lanes (DPP row shifts, then row broadcasts).
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t u)
+{
+    int v = static_cast<int>(u);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return static_cast<uint32_t>(v);
+}
+
 // Index of the calling wave in its workgroup, as a wave-uniform (scalar)
 // value: everything derived from it (rows, row pointers, loop bounds) then
 // stays in scalar registers and branches on it need no exec masking.
@@ -239,12 +262,39 @@ __device__ __forceinline__ int wave_id()
     return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
 }
 
-// Maximum over the wave (valid in lane 0).
-__device__ __forceinline__ int wave_max(int v)
+// Sum of n int32 counters at a 16-byte aligned address, by one workgroup of
+// 1024 threads: 16 counters a thread and step, so that even the counters of the
+// largest lattices take a few steps (32768 counters, one a thread and step: 14
+// us; two launches of 64 workgroups: 9).
+__device__ __forceinline__ void sum_tiles(const int32_t *v, int n, int32_t *out)
 {
+    __shared__ uint32_t red[16];
+    uint32_t acc = 0;
+    for (int i = 0; i < n; i += 16 * 1024) {
+        uint4 x[4];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_down(v, off));
-    return v;
+        for (int j = 0; j < 4; ++j) {
+            const int k = i + 4 * (j * 1024 + static_cast<int>(threadIdx.x));
+            if (k + 4 <= n) {
+                x[j] = *reinterpret_cast<const uint4 *>(v + k);
+            } else {
+                x[j].x = k < n ? v[k] : 0;
+                x[j].y = k + 1 < n ? v[k + 1] : 0;
+                x[j].z = k + 2 < n ? v[k + 2] : 0;
+                x[j].w = 0;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc += x[j].x + x[j].y + x[j].z + x[j].w;
+    }
+    acc = wave_sum_u32(acc);
+    if ((threadIdx.x & 63) == 0) red[wave_id()] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;
+        for (int w = 0; w < 16; ++w) t += red[w];
+        *out = static_cast<int32_t>(t);
+    }
 }
 
 __device__ __forceinline__ void add_stat(unsigned long long *p, unsigned long long v)
