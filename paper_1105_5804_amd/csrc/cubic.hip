@@ -62,8 +62,6 @@ constexpr int ITER = 8;                                        // steps per wave
 constexpr int TL3 = 448;                                       // per-wave lists: a step adds at most 128 entries at a
                                                                // time, a fuller list is worked off first
 static_assert(CSITES == 128 * NW3 * ITER && CY == 2 * ITER && CZ == SUB * NW3 / 2, "the waves cover the tile");
-constexpr int MT = 256;                                        // merge workgroup
-constexpr int RT = 64;                                         // resolve workgroup: one wave per tile
 constexpr int MSEEN = 1024;                                    // merge: pair-dedup slots per face
 constexpr int FX = CY * CZ, FY = CX * CZ, FZ = CX * CY;        // sites of the +x, +y, +z faces
 constexpr uint32_t TAG_BOND = 1, TAG_FLIP = 2, TAG_BOND_Z = 5;
@@ -581,7 +579,7 @@ __device__ __forceinline__ uint32_t id_prio(int x)
 // paths as in the square-lattice merge.
 __device__ __forceinline__ void gunite_prio(int *G, int a, int b)
 {
-    gfind2(G, a, b);
+    gfind2_from<false>(G, a, b, G[a], G[b]);
     for (;;) {
         if (a == b) return;
         if (id_prio(a) > id_prio(b)) {
@@ -594,7 +592,7 @@ __device__ __forceinline__ void gunite_prio(int *G, int a, int b)
                                                  __HIP_MEMORY_SCOPE_AGENT))
             return;
         a = expect;
-        gfind2(G, a, b);
+        gfind2_again(G, a, b, true);
     }
 }
 
@@ -606,10 +604,10 @@ __device__ __forceinline__ void gunite_prio(int *G, int a, int b)
 // then the codes across the active ones, duplicates dropped), then works the list off with every lane
 // busy: a lane no longer waits for its wave's deepest union at each of its
 // face positions.
-constexpr int MPOS = (FX + FY + FZ + MT - 1) / MT;  // face positions per merge thread
-
+template <int MT>
 __global__ __launch_bounds__(MT) void k3_merge(Merge3Args a)
 {
+    constexpr int MPOS = (FX + FY + FZ + MT - 1) / MT;  // face positions per thread
     // seen[d][h]: the last pair (ca << 16 | cb) registered across face d in
     // hash slot h = ca mod MSEEN; a lane that gets its own pair back skips it
     // (the lane that registered it lists it; pairs sharing a slot are at
@@ -725,10 +723,15 @@ __device__ __forceinline__ uint32_t new_state(uint32_t R, const Flat3Args &a)
 // Every id of every tile resolved after the merge:
 // the id's entry is pointed at its root (the trees are final, so concurrent
 // walks stay valid) and the id's key (the minimum site index of its part of
-// the cluster) is taken into the root's key by an atomic minimum, issued only
-// when the root's key, read first, is larger (a stale read is larger still),
-// so the ids of a large cluster do not all contend for its root.  The root's
-// key then holds the cluster's minimum site index: its canonical label.
+// the cluster) is taken into the root's key by an atomic minimum, so that the
+// root's key then holds the cluster's minimum site index: its canonical label.
+// The ids of one cluster must not all go to its root: a tile first takes the
+// minimum per root in a small LDS table (a root whose slot is another's goes to
+// memory by itself), and a minimum is only issued if memory's key, read past
+// the caches, is larger.  Bound by latency, the walks' and that of a few
+// atomics; an atomic an id whose cached key looked larger made it wait for
+// one address in the ordered phase (cubic q = 3, K = 0.6: 160^3 47 -> 17 us,
+// 512^3 sweep 1320 -> 1022 us).
 struct Resolve3Args {
     Geo3 g;
     int32_t *gkey;
@@ -736,14 +739,26 @@ struct Resolve3Args {
     const int32_t *nb;
 };
 
+template <int RT>
 __global__ __launch_bounds__(RT) void k3_resolve(Resolve3Args a)
 {
-    // a one-wave workgroup per tile, its lanes over the tile's ids (few idle
-    // lanes in the last pass over a tile's few hundred ids)
+    // a workgroup per tile, its threads over the tile's ids
+    constexpr int SLOTS = 256;
+    __shared__ int32_t owner[SLOTS], least[SLOTS];
     const int tile = static_cast<int>(blockIdx.x);
     const int nbt = a.nb[tile];
+    for (int k = threadIdx.x; k < SLOTS; k += RT) {
+        owner[k] = -1;
+        least[k] = 0x7FFFFFFF;
+    }
+    __syncthreads();
+    auto take = [&](int root, int32_t key) {
+        const int32_t now = __hip_atomic_load(&a.gkey[root], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (key < now) atomicMin(&a.gkey[root], key);
+    };
     for (int k = threadIdx.x; k < nbt; k += RT) {
         const int id = tile * CAP + k;
+        const int32_t key = a.gkey[id];  // a root's key is not used; another id's never changes
         int x = id, p = a.gparent[x];
         while (p != x) {
             x = p;
@@ -751,9 +766,16 @@ __global__ __launch_bounds__(RT) void k3_resolve(Resolve3Args a)
         }
         if (x == id) continue;
         a.gparent[id] = x;
-        const int32_t key = a.gkey[id];  // not a root: its key never changes
-        if (key < a.gkey[x]) atomicMin(&a.gkey[x], key);
+        const int h = static_cast<int>((static_cast<uint32_t>(x) * 0x9E3779B1u) >> 24);
+        const int was = atomicCAS(&owner[h], -1, x);
+        if (was == -1 || was == x)
+            atomicMin(&least[h], key);
+        else
+            take(x, key);
     }
+    __syncthreads();
+    for (int k = threadIdx.x; k < SLOTS; k += RT)
+        if (owner[k] >= 0) take(owner[k], least[k]);
 }
 
 // LABEL: labels only (no draws, spins untouched).
@@ -869,6 +891,14 @@ using namespace swccl::cubic;
 namespace {
 
 constexpr size_t ALIGN3 = 256;
+// Up to this many tiles the merge takes 1024 threads a tile, else 256.  Critical
+// Ising sweep, 256 -> 1024: 100 x 75 x 61 (80 tiles) 55.5 -> 51.6 us, 160^3 (500)
+// 75 -> 72, 256^3 (2048) 161 -> 175.
+constexpr int MERGE3_WIDE = 512;
+// Up to this many tiles the resolve takes 512 threads a tile, else 256.  64 -> 256
+// -> 512: 160^3 105 -> 80 -> 75 us, 200 x 210 x 220 (1372 tiles) 163 -> 133 ->
+// 132, in the ordered phase 220 -> 208 -> 220; 128 or 1024 at 256^3 170, 256 162.
+constexpr int RESOLVE3_WIDE = 1024;
 size_t up3(size_t v) { return (v + ALIGN3 - 1) / ALIGN3 * ALIGN3; }
 int64_t cdiv3(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -943,6 +973,26 @@ void launch_tile3(const Tile3Args &ta, hipStream_t s)
         hipLaunchKernelGGL((k3_tile<LABEL, false>), tiles, dim3(NT3), 0, s, ta);
 }
 
+// The merge and the resolve are chains of dependent global accesses: while the
+// tiles leave waves to spare, more threads a tile shorten them.
+void launch_merge3(const Merge3Args &ma, hipStream_t s)
+{
+    const dim3 tiles(static_cast<unsigned>(ma.g.ntiles));
+    if (ma.g.ntiles <= MERGE3_WIDE)
+        hipLaunchKernelGGL(k3_merge<1024>, tiles, dim3(1024), 0, s, ma);
+    else
+        hipLaunchKernelGGL(k3_merge<256>, tiles, dim3(256), 0, s, ma);
+}
+
+void launch_resolve3(const Resolve3Args &ra, hipStream_t s)
+{
+    const dim3 tiles(static_cast<unsigned>(ra.g.ntiles));
+    if (ra.g.ntiles <= RESOLVE3_WIDE)
+        hipLaunchKernelGGL(k3_resolve<512>, tiles, dim3(512), 0, s, ra);
+    else
+        hipLaunchKernelGGL(k3_resolve<256>, tiles, dim3(256), 0, s, ra);
+}
+
 template <typename T>
 T *at3(void *ws, size_t off)
 {
@@ -1015,8 +1065,8 @@ sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, i
     fa.tile_ncl = at3<int32_t>(workspace, L.tile_ncl);
     const dim3 tiles(static_cast<unsigned>(L.g.ntiles));
     launch_tile3<true>(ta, s);
-    hipLaunchKernelGGL(k3_merge, tiles, dim3(MT), 0, s, ma);
-    hipLaunchKernelGGL(k3_resolve, tiles, dim3(RT), 0, s, ra);
+    launch_merge3(ma, s);
+    launch_resolve3(ra, s);
     hipLaunchKernelGGL(k3_flatten<true>, tiles, dim3(NT3), 0, s, fa);
     if (n_clusters) hipLaunchKernelGGL(k3_count_out, dim3(1), dim3(1024), 0, s, fa.tile_ncl, L.g.ntiles, n_clusters);
     return swccl_internal::device_error(hipGetLastError(), "ccl3_label");
@@ -1096,8 +1146,8 @@ sw_status sw3_sweep(const sw3_params *p, uint8_t *spins, uint32_t t0, int32_t n,
         fa.t = t;
         fa.labels = k + 1 == n ? labels : nullptr;
         launch_tile3<false>(ta, s);
-        hipLaunchKernelGGL(k3_merge, tiles, dim3(MT), 0, s, ma);
-        hipLaunchKernelGGL(k3_resolve, tiles, dim3(RT), 0, s, ra);
+        launch_merge3(ma, s);
+        launch_resolve3(ra, s);
         hipLaunchKernelGGL(k3_flatten<false>, tiles, dim3(NT3), 0, s, fa);
         if (records) {
             oa.out = records + static_cast<int64_t>(k) * SW3_REC_LEN;

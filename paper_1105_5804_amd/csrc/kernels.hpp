@@ -814,7 +814,8 @@ __device__ __forceinline__ void merge_tile(MergeArgs a, const int tile, const in
         // boundary ids (< CAP); the bound keeps any other entry from
         // addressing memory outside the tiles' tables.
         if (on[k] && !(before[k] && pa[k] == ia[k] && pb[k] == ib[k]) && ia[k] < CAP && ib[k] < CAP)
-            gunite(a.gparent, a.gkey, tile * CAP + ia[k], (pass0 + k < RIGHT ? ntR : ntD) * CAP + ib[k]);
+            gunite(a.gparent, a.gkey, tile * CAP + ia[k], (pass0 + k < RIGHT ? ntR : ntD) * CAP + ib[k],
+                   a.g.ntiles <= MERGE_FRESH_TILES);
     }
 }
 

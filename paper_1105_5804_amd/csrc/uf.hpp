@@ -171,32 +171,56 @@ __device__ __forceinline__ int gfind(const int *G, int x)
     }
 }
 
+// Parent of x: as this XCD's caches have it (maybe an older one, still an
+// ancestor), or FRESH, as it is in memory.
+template <bool FRESH>
+__device__ __forceinline__ int gparent_of(int *G, int x)
+{
+    return FRESH ? __hip_atomic_load(&G[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : G[x];
+}
+
 // Roots of a and b, both chains walked at once (their loads overlap); the
 // body is straight-line, a finished chain just reloads its root.  pa and pb are
 // the parents of a and b as just read.
+template <bool FRESH>
 __device__ __forceinline__ void gfind2_from(int *G, int &a, int &b, int pa, int pb)
 {
     // path halving: a node passed over is pointed at its grandparent (an
     // ancestor, so concurrent walks stay valid), which keeps the trees of
     // clusters that span many tiles shallow
     while (pa != a || pb != b) {
-        const int ga = G[pa], gb = G[pb];
+        const int ga = gparent_of<FRESH>(G, pa), gb = gparent_of<FRESH>(G, pb);
         if (ga != pa) G[a] = ga;
         if (gb != pb) G[b] = gb;
         a = ga;
         b = gb;
-        pa = G[a];
-        pb = G[b];
+        pa = gparent_of<FRESH>(G, a);
+        pb = gparent_of<FRESH>(G, b);
     }
 }
-__device__ __forceinline__ void gfind2(int *G, int &a, int &b) { gfind2_from(G, a, b, G[a], G[b]); }
+// The same after a compare-and-swap that failed.  A line cached while its ids
+// were roots keeps them roots for this XCD: near a large cluster's root each
+// step of a walk on cached parents then ends in another failed swap, so with
+// `fresh` the walk reads memory.  Cubic q = 3 sweep in the ordered phase (K =
+// 0.6), cached -> fresh: 160^3 111 -> 84 us, 256^3 267 -> 193, 512^3 1055 ->
+// 1022, at the critical point within 1%; square q = 3 lattice 8192^2 at 1.4
+// beta_c 260 -> 241.  Square lattices of more than MERGE_FRESH_TILES tiles keep
+// to the caches (16384^2 bond percolation 925 cached, 934 fresh).
+constexpr int MERGE_FRESH_TILES = 8192;
+__device__ __forceinline__ void gfind2_again(int *G, int &a, int &b, bool fresh)
+{
+    if (fresh)
+        gfind2_from<true>(G, a, b, gparent_of<true>(G, a), gparent_of<true>(G, b));
+    else
+        gfind2_from<false>(G, a, b, G[a], G[b]);
+}
 
-__device__ __forceinline__ void gunite(int *G, const int *key, int a, int b)
+__device__ __forceinline__ void gunite(int *G, const int *key, int a, int b, bool fresh)
 {
     // the keys are read with the parents: most ids are still roots
     const int a0 = a, b0 = b, pa = G[a], pb = G[b];
     int ka = key[a], kb = key[b];
-    gfind2_from(G, a, b, pa, pb);
+    gfind2_from<false>(G, a, b, pa, pb);
     if (a != a0) ka = key[a];
     if (b != b0) kb = key[b];
     for (;;) {
@@ -213,7 +237,7 @@ __device__ __forceinline__ void gunite(int *G, const int *key, int a, int b)
                                                  __HIP_MEMORY_SCOPE_AGENT))
             return;
         a = expect;  // a was linked meanwhile: continue from its parent
-        gfind2(G, a, b);
+        gfind2_again(G, a, b, fresh);
         ka = key[a];
         kb = key[b];
     }
