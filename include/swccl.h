@@ -53,8 +53,9 @@
  *
  * Streams: every call enqueues on the given stream (a hipStream_t passed as
  * void*; NULL is the null stream) and returns without waiting, except
- * sw_observables and swb_observables, which wait for the stream, and the
- * server's release and destroy, which wait for their requests.
+ * sw_observables, swb_observables and sw_cluster_count, which wait for the
+ * stream, and the server's count, release and destroy, which wait for their
+ * requests.
  *
  * Errors: every entry point returns an sw_status; arguments are checked before
  * anything is enqueued and nothing throws across the ABI.  SW_ERR_DEVICE means
@@ -251,6 +252,11 @@ sw_status sw_sweep_phase(sw_lattice *h, int32_t phase, void *stream);
  * and clusters are those of the last sweep's steps 1 and 2 (Sec. II). */
 sw_status sw_observables(sw_lattice *h, sw_obs *out, void *stream);
 
+/* Number of clusters of the last sweep of a lattice with SW_F_SIZES (how many
+ * entries of roots and sizes it filled), -1 before the first sweep; waits for
+ * the stream.  SW_ERR_ARG without SW_F_SIZES. */
+sw_status sw_cluster_count(sw_lattice *h, int64_t *n_clusters, void *stream);
+
 /* Checkpointing: the full state of a lattice is (spins, t); a restart is
  * sw_init with SW_F_KEEP_SPINS over the saved spins plus sw_set_t. */
 sw_status sw_get_t(const sw_lattice *h, uint64_t *t);
@@ -436,6 +442,12 @@ sw_status ccl_server_poll(ccl_server *s, int32_t *slots, uint64_t *tags, int32_t
  * until the request is released. */
 sw_status ccl_server_result(ccl_server *s, int32_t slot, int32_t **labels, int32_t **roots, int32_t **sizes,
                             int32_t **n_clusters);
+
+/* The cluster count of a request as a host value: it reaches the host with the
+ * request's completion, so a completed request costs no copy and no wait on
+ * any stream (one that still runs is waited for, one in the open batch flushed
+ * first).  SW_ERR_STATE if the slot is not admitted. */
+sw_status ccl_server_count(ccl_server *s, int32_t slot, int32_t *n_clusters);
 
 /* Return a request's arena block (waits for the request if it still runs). */
 sw_status ccl_server_release(ccl_server *s, int32_t slot);

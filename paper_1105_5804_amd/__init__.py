@@ -221,7 +221,10 @@ class SWLattice:
         waits for the stream)."""
         if self.roots is None:
             raise ValueError("lattice was created without sizes=True")
-        n = self.observables(stream)["n_clusters"]
+        v = ctypes.c_int64()
+        _lib.check(_lib.lib().sw_cluster_count(self._h, ctypes.byref(v), _stream(_torch(), stream)),
+                   "sw_cluster_count")
+        n = int(v.value)
         if n < 0:
             raise ValueError("no sweep yet")
         return self.roots[:n], self.sizes[:n]

@@ -116,6 +116,7 @@ SIGNATURES = {
     "sw_sweep_phase": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p]),
     "sw_sweep_history": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p]),
     "sw_observables": (ctypes.c_int32, [ctypes.c_void_p, ctypes.POINTER(SwObs), ctypes.c_void_p]),
+    "sw_cluster_count": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]),
     "sw_get_t": (ctypes.c_int32, [ctypes.c_void_p, ctypes.POINTER(ctypes.c_uint64)]),
     "sw_set_t": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_uint64]),
     "sw_destroy": (ctypes.c_int32, [ctypes.c_void_p]),
@@ -147,6 +148,7 @@ SIGNATURES = {
     "ccl_server_result": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(ctypes.c_void_p),
                                            ctypes.POINTER(ctypes.c_void_p), ctypes.POINTER(ctypes.c_void_p),
                                            ctypes.POINTER(ctypes.c_void_p)]),
+    "ccl_server_count": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]),
     "ccl_server_release": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32]),
     "ccl_server_destroy": (ctypes.c_int32, [ctypes.c_void_p]),
     "ccl_label": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,

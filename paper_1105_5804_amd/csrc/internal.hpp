@@ -19,6 +19,7 @@ struct LabelRequest {
     const uint8_t *in;
     int32_t W, H;
     int32_t *labels, *roots, *sizes, *n_clusters;
+    int32_t *n_host;  // the count again, in host memory (its device address)
     void *ws;
 };
 

@@ -105,6 +105,10 @@ struct ccl_server {
     // host copy, and the event of the batch that last used the slot
     size_t table_bytes = 0;
     char *pinned = nullptr;
+    // pinned: the cluster count of each slot's request, written by the device
+    // before the request's completion event
+    int32_t *counts = nullptr;
+    int32_t *counts_dev = nullptr;
     std::vector<int> ring_next;
     std::vector<int> slot_ev;  // [stream * TABLE_RING + slot]
     std::vector<int> last_ev;  // per stream: event of its last launch sequence, or -1
@@ -195,6 +199,12 @@ bool batchable(const ccl_server *s, int32_t W, int32_t H)
            swccl_internal::request_tiles(W, H) <= BATCH_REQ_TILES;
 }
 
+void free_pinned(ccl_server *s)
+{
+    if (s->pinned) (void)hipHostFree(s->pinned);
+    if (s->counts) (void)hipHostFree(s->counts);
+}
+
 size_t table_index(int stream, int slot) { return static_cast<size_t>(stream) * TABLE_RING + static_cast<size_t>(slot); }
 
 // Label the open batch (one launch per phase on its stream); its requests
@@ -229,6 +239,7 @@ sw_status flush_open(ccl_server *s)
         q.roots = s->p.sizes ? reinterpret_cast<int32_t *>(base + r.L.roots) : nullptr;
         q.sizes = s->p.sizes ? reinterpret_cast<int32_t *>(base + r.L.sizes) : nullptr;
         q.n_clusters = reinterpret_cast<int32_t *>(base + r.L.ncl);
+        q.n_host = s->counts_dev + k;
         q.ws = base + r.L.ws;
         lr.push_back(q);
     }
@@ -280,6 +291,15 @@ sw_status ccl_server_create(ccl_server **out, const ccl_server_params *p, void *
         delete s;
         return SW_ERR_HOST_MEMORY;
     }
+    void *dev = nullptr;
+    if (hipHostMalloc(reinterpret_cast<void **>(&s->counts), sizeof(int32_t) * static_cast<size_t>(p->max_inflight),
+                      hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer(&dev, s->counts, 0) != hipSuccess) {
+        free_pinned(s);
+        delete s;
+        return SW_ERR_HOST_MEMORY;
+    }
+    s->counts_dev = static_cast<int32_t *>(dev);
     try {
         s->free_blocks[first] = s->arena_bytes - first;
         for (int32_t i = 0; i < p->n_streams; ++i) s->streams.push_back(static_cast<hipStream_t>(streams[i]));
@@ -291,7 +311,7 @@ sw_status ccl_server_create(ccl_server **out, const ccl_server_params *p, void *
         s->slot_ev.assign(ntables, -1);
         s->open_slots.reserve(BATCH_MAX_REQS);
     } catch (const std::bad_alloc &) {
-        if (s->pinned) (void)hipHostFree(s->pinned);
+        free_pinned(s);
         delete s;
         return SW_ERR_HOST_MEMORY;
     }
@@ -299,7 +319,7 @@ sw_status ccl_server_create(ccl_server **out, const ccl_server_params *p, void *
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
             for (auto &f : s->ev)
                 if (f) (void)hipEventDestroy(f);
-            if (s->pinned) (void)hipHostFree(s->pinned);
+            free_pinned(s);
             delete s;
             return SW_ERR_DEVICE;
         }
@@ -383,6 +403,9 @@ sw_status ccl_server_submit(ccl_server *s, const uint8_t *image, int32_t W, int3
     if (ce != hipSuccess) status = SW_ERR_DEVICE;
     if (status == SW_OK && !batch) {
         status = ccl_label(in, W, H, s->p.mode, labels, roots, sizes, ncl, base + L.ws, L.ws_bytes, st);
+        if (status == SW_OK &&
+            hipMemcpyAsync(s->counts + k, ncl, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess)
+            status = SW_ERR_DEVICE;
         if (status == SW_OK && hipEventRecord(s->ev[static_cast<size_t>(ev)], st) != hipSuccess)
             status = SW_ERR_DEVICE;
         if (status == SW_OK) s->last_ev[static_cast<size_t>(si)] = ev;
@@ -460,6 +483,18 @@ sw_status ccl_server_result(ccl_server *s, int32_t slot, int32_t **labels, int32
     return SW_OK;
 }
 
+sw_status ccl_server_count(ccl_server *s, int32_t slot, int32_t *n_clusters)
+{
+    if (!s || !n_clusters || slot < 0 || slot >= static_cast<int32_t>(s->req.size())) return SW_ERR_ARG;
+    const Request &r = s->req[static_cast<size_t>(slot)];
+    if (!r.busy) return SW_ERR_STATE;
+    if (r.ev < 0)
+        if (const sw_status fs = flush_open(s)) return fs;  // still in the open batch
+    if (hipEventSynchronize(s->ev[static_cast<size_t>(r.ev)]) != hipSuccess) return SW_ERR_DEVICE;
+    *n_clusters = *static_cast<volatile int32_t *>(s->counts + slot);
+    return SW_OK;
+}
+
 sw_status ccl_server_release(ccl_server *s, int32_t slot)
 {
     if (!s || slot < 0 || slot >= static_cast<int32_t>(s->req.size())) return SW_ERR_ARG;
@@ -490,7 +525,7 @@ sw_status ccl_server_destroy(ccl_server *s)
         (void)hipEventSynchronize(e);
         (void)hipEventDestroy(e);
     }
-    if (s->pinned) (void)hipHostFree(s->pinned);
+    free_pinned(s);
     delete s;
     return SW_OK;
 }

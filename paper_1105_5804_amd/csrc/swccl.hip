@@ -141,15 +141,16 @@ Layout make_layout(int32_t W, int32_t H, bool sizes, int th = TH_DEFAULT, int mw
     };
     if (sizes) {
         L.gsize = take(nt * static_cast<size_t>(L.d.cap) * sizeof(int32_t));
-        // per-(row, tile column) root counts, their total, then the largest size
-        L.row_count = take(static_cast<size_t>(L.nrow + 2) * sizeof(int32_t));
+        // per-(row, tile column) root counts, their total, the largest size and,
+        // on a lattice, the number of clusters
+        L.row_count = take(static_cast<size_t>(L.nrow + 2 + (observed ? 1 : 0)) * sizeof(int32_t));
         L.row_off = take(static_cast<size_t>(L.nrow + 1) * sizeof(int32_t));
         L.scan_tmp = take(scan_tmp_bytes(L.nrow + 1));
         L.rl_slot = take(nt * static_cast<size_t>(L.d.tsites) * sizeof(int32_t));
         L.rl_size = take(nt * static_cast<size_t>(L.d.tsites) * sizeof(int32_t));
     }
     if (observed) L.obs_part = take(OBS_PART_BYTES);
-    if (observed && !sizes && !few && W <= SMALL_W && H <= SMALL_H)
+    if (observed && W <= SMALL_W && H <= SMALL_H)
         L.words = take(SMALL_AHEAD * 256 * static_cast<size_t>(cdiv(static_cast<int64_t>(W) * H, 128)));
     L.few = few;
     if (few) {
@@ -531,6 +532,12 @@ static sw_status launch_seeds(sw_lattice *h, hipStream_t s)
     return launch_status("k_seed");
 }
 
+// Where a sweep with sizes leaves its number of clusters.
+static int32_t *cluster_count_of(const sw_lattice *h)
+{
+    return at<int32_t>(h->b.workspace, h->L.row_count) + h->L.nrow + 2;
+}
+
 // Enqueue one phase of sweep h->t.
 static sw_status launch_phase(sw_lattice *h, int32_t phase, hipStream_t s)
 {
@@ -582,7 +589,7 @@ static sw_status launch_phase(sw_lattice *h, int32_t phase, hipStream_t s)
             return launch_status("k_flatten");
         }
         launch_flatten<M_FEW, true, false>(L, fa, L.g.ntiles, s);
-        emit_sizes(L, ws, fa, h->b.roots, h->b.sizes, fa.row_count + L.nrow + 1, nullptr, s);
+        emit_sizes(L, ws, fa, h->b.roots, h->b.sizes, fa.row_count + L.nrow + 1, cluster_count_of(h), s);
         return launch_status("k_flatten");
     }
     if (!L.sizes) {
@@ -590,7 +597,7 @@ static sw_status launch_phase(sw_lattice *h, int32_t phase, hipStream_t s)
         return launch_status("k_flatten");
     }
     launch_flatten<M_SW, true, false>(L, fa, L.g.ntiles, s);
-    emit_sizes(L, ws, fa, h->b.roots, h->b.sizes, fa.row_count + L.nrow + 1, nullptr, s);
+    emit_sizes(L, ws, fa, h->b.roots, h->b.sizes, fa.row_count + L.nrow + 1, cluster_count_of(h), s);
     return launch_status("k_flatten");
 }
 
@@ -757,6 +764,21 @@ sw_status sw_observables(sw_lattice *h, sw_obs *out, void *stream)
     const int32_t *max_dev = L.sizes ? at<int32_t>(ws, L.row_count) + L.nrow + 1 : nullptr;
     return measure(h->p, h->b, h->swept, at<int32_t>(ws, L.tile_act), at<int32_t>(ws, L.tile_ncl),
                    h->small_last ? 1 : L.g.ntiles, L, ws, max_dev, h->T, h->t, out, static_cast<hipStream_t>(stream));
+}
+
+sw_status sw_cluster_count(sw_lattice *h, int64_t *n_clusters, void *stream)
+{
+    if (!h || !n_clusters || !h->L.sizes) return SW_ERR_ARG;
+    *n_clusters = -1;
+    if (!h->swept) return SW_OK;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    int32_t n = 0;
+    if (const sw_status st = device_status(hipMemcpyAsync(&n, cluster_count_of(h), sizeof(n), hipMemcpyDeviceToHost, s),
+                                           "copy cluster count"))
+        return st;
+    if (const sw_status st = device_status(hipStreamSynchronize(s), "sync")) return st;
+    *n_clusters = n;
+    return SW_OK;
 }
 
 sw_status sw_sweep_history(sw_lattice *h, int32_t n_sweeps, int64_t *history, void *stream)
@@ -1417,7 +1439,7 @@ uint64_t bond_threshold(double K) { return threshold_of(K); }
 sw_status pull(void *dst, const void *src_dev, int64_t n, hipStream_t s)
 {
     if (n <= 0) return SW_OK;
-    hipLaunchKernelGGL(k_pull, dim3(static_cast<unsigned>(cdiv(n, static_cast<int64_t>(NT) * 4))), dim3(NT), 0, s,
+    hipLaunchKernelGGL(k_pull, dim3(static_cast<unsigned>(cdiv(n, static_cast<int64_t>(NT) * PULL))), dim3(NT), 0, s,
                        static_cast<uint8_t *>(dst), static_cast<const uint8_t *>(src_dev), n);
     return launch_status("pull");
 }
@@ -1451,6 +1473,7 @@ sw_status label_batch(const LabelRequest *r, int32_t n, int32_t mode, bool sizes
         d.roots = sizes ? r[k].roots : nullptr;
         d.sizes = sizes ? r[k].sizes : nullptr;
         d.n_clusters = r[k].n_clusters;
+        d.n_host = r[k].n_host;
         d.codes = at<uint16_t>(ws, L.codes);
         d.edges = at<uint16_t>(ws, L.edges);
         d.gkey = at<int32_t>(ws, L.gkey);

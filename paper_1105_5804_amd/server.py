@@ -58,11 +58,17 @@ class CCLServer:
         self.rejected = []                  # (tag, status) dropped from the queue by pump
         self._pslots = (ctypes.c_int32 * cap)()
         self._ptags = (ctypes.c_uint64 * cap)()
+        self._fences = {}                   # stream -> event its next submit must wait for (see release)
 
     def footprint(self, W: int, H: int) -> int:
         return int(_lib.lib().ccl_server_footprint(int(W), int(H), ctypes.byref(self.params)))
 
     def _try_submit(self, tag: int, img) -> bool:
+        if self._fences:
+            for ev in self._fences.values():
+                for s in self.streams:
+                    s.wait_event(ev)
+            self._fences.clear()
         H, W = img.shape
         slot = ctypes.c_int32()
         st = _lib.lib().ccl_server_submit(self._h, img.data_ptr(), W, H, img.stride(0), tag, ctypes.byref(slot))
@@ -150,7 +156,9 @@ class CCLServer:
             t = self._arena[off:off + 4 * count].view(torch.int32)
             return t.view(shape) if shape else t
 
-        ncl = int(view(ptrs[3].value, 1).item())
+        count = ctypes.c_int32()
+        _lib.check(_lib.lib().ccl_server_count(self._h, int(slot), ctypes.byref(count)), "ccl_server_count")
+        ncl = int(count.value)
         labels = view(ptrs[0].value, N, (H, W))
         if not self.sizes:
             return labels, None, None, ncl
@@ -159,12 +167,14 @@ class CCLServer:
     def release(self, slot: int) -> None:
         """Return a request's arena block.  Work the caller has enqueued on the
         current stream (e.g. a copy of the result views) finishes before any
-        later request can write the block: every server stream waits for it."""
+        later request can write the block: every server stream waits for it
+        before the next request is submitted (once for a run of releases, by
+        the last of their events on each stream)."""
         torch = _torch()
+        cur = torch.cuda.current_stream(self.device)
         ev = torch.cuda.Event()
-        ev.record(torch.cuda.current_stream(self.device))
-        for s in self.streams:
-            s.wait_event(ev)
+        ev.record(cur)
+        self._fences[cur.cuda_stream] = ev
         _lib.check(_lib.lib().ccl_server_release(self._h, int(slot)), "ccl_server_release")
         del self._inflight[slot]
 
