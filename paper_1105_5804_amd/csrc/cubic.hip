@@ -779,13 +779,21 @@ __global__ __launch_bounds__(RT) void k3_resolve(Resolve3Args a)
 }
 
 // LABEL: labels only (no draws, spins untouched).
-template <bool LABEL>
+// FOUR (Lx a multiple of 4): about a third of the sites of a critical lattice
+// are roots, so every site draws, a block of four words for the four sites of a
+// lane pair (the even lane for one row, the odd one for the next, as the tile
+// kernel's +z words), and a root's state is where its cluster's sites look it
+// up, its own slot; the other slots' states are not read.  Otherwise the
+// interior roots are listed and draw 64 at a time.  Bound by the ids' scattered
+// keys and VALU issue (busy 0.63); 512^3 at beta_c, listed -> all: 213 -> 201 us.
+template <bool LABEL, bool FOUR>
 __global__ __launch_bounds__(NT3) void k3_flatten(Flat3Args a)
 {
     constexpr uint32_t NCODE = CSITES + CAP;
-    __shared__ uint8_t ST[NCODE];                 // new state per code
+    constexpr bool LIST = !LABEL && !FOUR;
+    __shared__ uint8_t ST[LABEL ? 1 : NCODE];     // new state per code
     __shared__ int32_t Rb[CAP];                   // canonical label per id (labels only)
-    __shared__ uint16_t roots[NW3][128 * ITER];   // interior root slots of each wave's rows
+    __shared__ uint16_t roots[LIST ? NW3 : 1][LIST ? 128 * ITER : 1];  // interior root slots of each wave's rows
     __shared__ unsigned ncl_w[NW3];
     const Geo3 g = a.g;
     const TileOf T = tile_of(g, xcd_remap(blockIdx.x, g.ntiles));
@@ -795,46 +803,67 @@ __global__ __launch_bounds__(NT3) void k3_flatten(Flat3Args a)
     const int nr = max(0, min(ITER, T.th - ly0));
     const bool v0 = lz < T.td && lx0 < T.tw, v1 = lz < T.td && lx0 + 1 < T.tw;
     const int nbt = a.nb[T.tile];
+    // the lane's codes (two per step), loaded ahead of the ids' chains
+    const uint32_t *codes32 = reinterpret_cast<const uint32_t *>(a.codes + static_cast<int64_t>(T.tile) * CSITES) +
+                              w * ITER * 64 + lane;
+    uint32_t cc[ITER];
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) cc[it] = it < nr ? codes32[it * 64] & (CODE_MASK | CODE_MASK << 16) : 0u;
     unsigned nbroot = 0;
     for (int k = threadIdx.x; k < nbt; k += NT3) {
         const int id = T.tile * CAP + k;
         const int r = a.gparent[id];  // resolved: the entry is the root
         const int32_t key = a.gkey[r];
         if constexpr (!LABEL) ST[CSITES + k] = static_cast<uint8_t>(new_state(static_cast<uint32_t>(key), a));
-        Rb[k] = key;
+        if (LABEL || a.labels) Rb[k] = key;
         nbroot += r == id ? 1u : 0u;
     }
-    // the lane's codes (two per step); the interior roots (code: own slot) of
-    // the wave's rows are listed, then draw their states 64 at a time
-    const uint32_t *codes32 = reinterpret_cast<const uint32_t *>(a.codes + static_cast<int64_t>(T.tile) * CSITES) +
-                              w * ITER * 64 + lane;
+    const uint32_t i_first = (static_cast<uint32_t>(T.gz0 + lz) * static_cast<uint32_t>(g.Ly) +
+                              static_cast<uint32_t>(T.gy0 + ly0)) * static_cast<uint32_t>(g.Lx) +
+                             static_cast<uint32_t>(T.gx0 + lx0);
     const uint64_t in0 = __ballot(v0), in1 = __ballot(v1);
     const int own_first = lz * PLANE + ly0 * CX + lx0;
-    uint32_t cc[ITER];
+    const bool odd_lane = (lane & 1) != 0;
+    uint32_t next0 = 0, next1 = 0;  // words of the next row's sites, drawn with this one
     int nroot = 0;
-    uint16_t *mylist = roots[w];
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) cc[it] = it < nr ? codes32[it * 64] & (CODE_MASK | CODE_MASK << 16) : 0u;
+    uint16_t *mylist = roots[LIST ? w : 0];
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
         if (it >= nr) break;
-        const int s = own_first + it * CX;
+        const int s = own_first + it * CX;  // interior roots carry their own slot as code
         const EO m = EO{lanes_eq(cc[it] & 0xFFFFu, static_cast<uint32_t>(s)) & in0,
                         lanes_eq(cc[it] >> 16, static_cast<uint32_t>(s + 1)) & in1};
-        eo_append(mylist, nroot, m, s, s + 1);
+        if constexpr (LIST) {
+            eo_append(mylist, nroot, m, s, s + 1);
+        } else {
+            nroot += __popcll(m.e) + __popcll(m.o);
+            if constexpr (!LABEL) {
+                uint32_t w0 = next0, w1 = next1;
+                if ((it & 1) == 0) {
+                    const uint32_t i0 = i_first + static_cast<uint32_t>(it) * static_cast<uint32_t>(g.Lx);
+                    const uint32_t four = odd_lane ? i0 - 2u + static_cast<uint32_t>(g.Lx) : i0;
+                    const U4 f = philox4x32_10(four >> 2, a.t, TAG_FLIP, a.sid, a.k0, a.k1);
+                    const uint32_t ra = swap_pair_lanes(odd_lane ? f.v0 : f.v2);
+                    const uint32_t rb = swap_pair_lanes(odd_lane ? f.v1 : f.v3);
+                    w0 = odd_lane ? ra : f.v0;
+                    w1 = odd_lane ? rb : f.v1;
+                    next0 = odd_lane ? f.v2 : ra;
+                    next1 = odd_lane ? f.v3 : rb;
+                }
+                *reinterpret_cast<uint16_t *>(&ST[s]) =
+                    static_cast<uint16_t>(draw_state(w0, a.q) | (draw_state(w1, a.q) << 8));
+            }
+        }
     }
-    wave_lds_fence();
-    if constexpr (!LABEL) {
+    if constexpr (LIST) {
+        wave_lds_fence();
         for (int k = lane; k < nroot; k += 64) {
             const int s = mylist[k];
             ST[s] = static_cast<uint8_t>(new_state(static_cast<uint32_t>(site_of(g, T, s)), a));
         }
     }
     __syncthreads();
-    const bool even_lx = (g.Lx & 1) == 0;  // every row starts even: both sites in one store
-    const uint32_t i_first = (static_cast<uint32_t>(T.gz0 + lz) * static_cast<uint32_t>(g.Ly) +
-                              static_cast<uint32_t>(T.gy0 + ly0)) * static_cast<uint32_t>(g.Lx) +
-                             static_cast<uint32_t>(T.gx0 + lx0);
+    const bool even_lx = FOUR || (g.Lx & 1) == 0;  // every row starts even: both sites in one store
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
         if (it >= nr) break;
@@ -993,6 +1022,16 @@ void launch_resolve3(const Resolve3Args &ra, hipStream_t s)
         hipLaunchKernelGGL(k3_resolve<256>, tiles, dim3(256), 0, s, ra);
 }
 
+template <bool LABEL>
+void launch_flatten3(const Flat3Args &fa, hipStream_t s)
+{
+    const dim3 tiles(static_cast<unsigned>(fa.g.ntiles));
+    if (fa.g.Lx % 4 == 0)
+        hipLaunchKernelGGL((k3_flatten<LABEL, true>), tiles, dim3(NT3), 0, s, fa);
+    else
+        hipLaunchKernelGGL((k3_flatten<LABEL, false>), tiles, dim3(NT3), 0, s, fa);
+}
+
 template <typename T>
 T *at3(void *ws, size_t off)
 {
@@ -1067,7 +1106,7 @@ sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, i
     launch_tile3<true>(ta, s);
     launch_merge3(ma, s);
     launch_resolve3(ra, s);
-    hipLaunchKernelGGL(k3_flatten<true>, tiles, dim3(NT3), 0, s, fa);
+    launch_flatten3<true>(fa, s);
     if (n_clusters) hipLaunchKernelGGL(k3_count_out, dim3(1), dim3(1024), 0, s, fa.tile_ncl, L.g.ntiles, n_clusters);
     return swccl_internal::device_error(hipGetLastError(), "ccl3_label");
 }
@@ -1148,7 +1187,7 @@ sw_status sw3_sweep(const sw3_params *p, uint8_t *spins, uint32_t t0, int32_t n,
         launch_tile3<false>(ta, s);
         launch_merge3(ma, s);
         launch_resolve3(ra, s);
-        hipLaunchKernelGGL(k3_flatten<false>, tiles, dim3(NT3), 0, s, fa);
+        launch_flatten3<false>(fa, s);
         if (records) {
             oa.out = records + static_cast<int64_t>(k) * SW3_REC_LEN;
             launch_observe<true, OBS_RECORD3>(oa, fa.ising != 0, s);
