@@ -927,20 +927,22 @@ __global__ __launch_bounds__(NT) void k_seed(SeedArgs a)
     }
 }
 
-// New state of the cluster whose canonical root is R (Sec. II.D: one uniform
-// draw per cluster, here taken at the minimum site index).
-__device__ __forceinline__ uint8_t flip_state(uint32_t R, const FlatArgs &a)
+// New spin byte of the cluster whose canonical root is R (Sec. II.D: one
+// uniform draw per cluster, here taken at the minimum site index).
+__device__ __forceinline__ uint8_t flip_byte(uint32_t R, const FlatArgs &a)
 {
     const U4 b = philox4x32_10(R >> 2, a.t, TAG_FLIP, a.sid, a.k0, a.k1);
-    return static_cast<uint8_t>(draw_state(pick(b, R & 3u), a.q));
+    const uint32_t st = draw_state(pick(b, R & 3u), a.q);
+    return static_cast<uint8_t>(a.ising ? 2u * st - 1u : st);
 }
 
 // LDS of the flatten phase.
 template <int MODE, bool SIZES, int TH_>
 struct FlatSmem {
     static constexpr int TH = TH_, TSITES = TW * TH, CAP = 2 * (TW + TH), NWAVE = TH / RPW;
-    uint8_t ST[MODE == M_SW || MODE == M_FEW ? TSITES + CAP : 1];  // new state per code (root slot or TSITES +
-                                                                    // boundary id); M_FEW: FEW_KEEP = no change
+    // new spin byte per code (root slot or TSITES + boundary id); M_FEW: new
+    // state, FEW_KEEP = no change
+    uint8_t ST[MODE == M_SW || MODE == M_FEW ? TSITES + CAP : 1];
     int32_t Rb[CAP];                              // canonical root (site index) per boundary id
     int32_t Gid[CAP];                             // root id per boundary id
     uint16_t rl[NWAVE][WLIST];                    // interior roots of each wave's rows
@@ -1042,7 +1044,7 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
     uint32_t cc[RPW];
     const uint32_t *codes32 = reinterpret_cast<const uint32_t *>(a.codes + static_cast<int64_t>(tile) * TSITES);
 #pragma unroll
-    for (int r = 0; r < RPW; ++r) cc[r] = r < nr ? codes32[((ly0 + r) * TW + lx0) >> 1] : 0xFFFFFFFFu;
+    for (int r = 0; r < RPW; ++r) cc[r] = r < nr ? codes32[((ly0 + r) * TW + lx0) >> 1] : 0u;
 
     // interior roots (code = own slot) of the wave's rows, compacted
     int nroot = 0;
@@ -1059,7 +1061,7 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
     if constexpr (MODE == M_SW) {
         for (int i = lane; i < nroot; i += 64) {
             const int slot = mylist[i];
-            ST[slot] = flip_state(static_cast<uint32_t>((gy0 + (slot >> 7)) * W + gx0 + (slot & (TW - 1))), a);
+            ST[slot] = flip_byte(static_cast<uint32_t>((gy0 + (slot >> 7)) * W + gx0 + (slot & (TW - 1))), a);
         }
     } else if constexpr (MODE == M_FEW) {
         // a seeded interior cluster that flips takes the other state of its
@@ -1100,7 +1102,7 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
             Rb[k] = key;
             Gid[k] = r;
             nbr += r == id;
-            if constexpr (MODE == M_SW) ST[TSITES + k] = flip_state(static_cast<uint32_t>(key), a);
+            if constexpr (MODE == M_SW) ST[TSITES + k] = flip_byte(static_cast<uint32_t>(key), a);
             if constexpr (MODE == M_FEW) {
                 // seeded iff its root carries this sweep's mark; the old state
                 // was read at the id's own tile-local root (a site of this
@@ -1123,58 +1125,79 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
         a.tile_ncl[tile] = n;
     }
 
+    // The lookups of all rows first, then the stores: a branch between the rows
+    // would have each wait for its own LDS reads (16384^2, branches -> none: spins
+    // 255 -> 249 us, labels of random bonds 383 -> 358).  `whole`: every row
+    // starts on an even site and ends past the wave's last lane, so a lane's
+    // pair is one store; otherwise rows that start on an odd site are stored
+    // site by site.
     const bool v0 = lx0 < tw, v1 = lx0 + 1 < tw;
+    const bool whole = tw == TW && (W & 1) == 0;
+    auto first_of = [&](int r) { return static_cast<int64_t>(gy0 + ly0 + r) * W + gx0; };
+    if constexpr (MODE == M_SW || MODE == M_FEW) {
+        // (sites past a ragged tile edge carry CODE_BG: any entry is looked up,
+        // none stored)
+        uint32_t st0[RPW], st1[RPW];
 #pragma unroll
-    for (int r = 0; r < RPW; ++r) {
-        if (r >= nr) break;
-        const int ly = ly0 + r;
-        const int64_t i0 = static_cast<int64_t>(gy0 + ly) * W + gx0 + lx0;
-        const uint32_t c0 = cc[r] & 0xFFFFu, c1 = cc[r] >> 16;
-        if constexpr (MODE == M_SW) {
-            // sites past a ragged tile edge carry CODE_BG: clamp the lookup, never store
-            const uint32_t st0 = ST[min(c0, static_cast<uint32_t>(NCODE - 1))];
-            const uint32_t st1 = ST[min(c1, static_cast<uint32_t>(NCODE - 1))];
-            const uint32_t b0 = a.ising ? (2u * st0 - 1u) & 0xFFu : st0;
-            const uint32_t b1 = a.ising ? (2u * st1 - 1u) & 0xFFu : st1;
-            if (v1 && !(i0 & 1)) {
-                *reinterpret_cast<uint16_t *>(a.spins + i0) = static_cast<uint16_t>(b0 | (b1 << 8));
-            } else {
-                if (v0) a.spins[i0] = static_cast<uint8_t>(b0);
-                if (v1) a.spins[i0 + 1] = static_cast<uint8_t>(b1);
+        for (int r = 0; r < RPW; ++r) {
+            st0[r] = ST[min(cc[r] & 0xFFFFu, static_cast<uint32_t>(NCODE - 1))];
+            st1[r] = ST[min(cc[r] >> 16, static_cast<uint32_t>(NCODE - 1))];
+        }
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+            if (r >= nr) break;
+            const int64_t row = first_of(r);
+            uint8_t *out = a.spins + row;
+            // only the sites of flipping clusters are written (M_FEW)
+            const bool f0 = v0 && (MODE == M_SW || st0[r] != FEW_KEEP), f1 = v1 && (MODE == M_SW || st1[r] != FEW_KEEP);
+            uint32_t b0 = st0[r], b1 = st1[r];
+            if (MODE == M_FEW && a.ising) {
+                b0 = (2u * b0 - 1u) & 0xFFu;
+                b1 = (2u * b1 - 1u) & 0xFFu;
             }
-        } else if constexpr (MODE == M_FEW) {
-            // only the sites of flipping clusters are written
-            const uint32_t st0 = ST[min(c0, static_cast<uint32_t>(NCODE - 1))];
-            const uint32_t st1 = ST[min(c1, static_cast<uint32_t>(NCODE - 1))];
-            const bool f0 = v0 && st0 != FEW_KEEP, f1 = v1 && st1 != FEW_KEEP;
-            const uint32_t b0 = a.ising ? (2u * st0 - 1u) & 0xFFu : st0;
-            const uint32_t b1 = a.ising ? (2u * st1 - 1u) & 0xFFu : st1;
-            if (f0 && f1 && !(i0 & 1)) {
-                *reinterpret_cast<uint16_t *>(a.spins + i0) = static_cast<uint16_t>(b0 | (b1 << 8));
+            if (MODE == M_SW && whole) {
+                *reinterpret_cast<uint16_t *>(out + lx0) = static_cast<uint16_t>(b0 | (b1 << 8));
+            } else if (f0 && f1 && (row & 1) == 0) {
+                *reinterpret_cast<uint16_t *>(out + lx0) = static_cast<uint16_t>(b0 | (b1 << 8));
             } else {
-                if (f0) a.spins[i0] = static_cast<uint8_t>(b0);
-                if (f1) a.spins[i0 + 1] = static_cast<uint8_t>(b1);
+                if (f0) out[lx0] = static_cast<uint8_t>(b0);
+                if (f1) out[lx0 + 1] = static_cast<uint8_t>(b1);
             }
         }
-        if (a.labels) {
-            int32_t R[2];
-            const uint32_t cs[2] = {c0, c1};
+    }
+    if (a.labels) {
+        auto label_of = [&](uint32_t c) {  // straight-line: the table entry of a boundary id, else the root's site
+            const int b = Rb[min(max(static_cast<int>(c) - TSITES, 0), CAP - 1)];
+            const int own = (gy0 + static_cast<int>(c >> 7)) * W + gx0 + static_cast<int>(c & (TW - 1));
+            const int v = c >= static_cast<uint32_t>(TSITES) ? b : own;
+            return c == CODE_BG ? -1 : v;
+        };
+        int32_t R0[RPW], R1[RPW];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const uint32_t c = cs[j];
-                const int slot = static_cast<int>(c);
-                R[j] = c == CODE_BG ? -1
-                     : c >= static_cast<uint32_t>(TSITES) ? Rb[c - TSITES]
-                                                          : (gy0 + (slot >> 7)) * W + gx0 + (slot & (TW - 1));
-            }
-            if (v1 && !(i0 & 1)) {
-                *reinterpret_cast<int2 *>(a.labels + i0) = make_int2(R[0], R[1]);
+        for (int r = 0; r < RPW; ++r) {
+            R0[r] = label_of(cc[r] & 0xFFFFu);
+            R1[r] = label_of(cc[r] >> 16);
+        }
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+            if (r >= nr) break;
+            const int64_t row = first_of(r);
+            int32_t *out = a.labels + row;
+            if (whole) {
+                *reinterpret_cast<int2 *>(out + lx0) = make_int2(R0[r], R1[r]);
+            } else if (v1 && (row & 1) == 0) {
+                *reinterpret_cast<int2 *>(out + lx0) = make_int2(R0[r], R1[r]);
             } else {
-                if (v0) a.labels[i0] = R[0];
-                if (v1) a.labels[i0 + 1] = R[1];
+                if (v0) out[lx0] = R0[r];
+                if (v1) out[lx0 + 1] = R1[r];
             }
         }
-        if constexpr (SIZES) {
+    }
+    if constexpr (SIZES) {
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+            if (r >= nr) break;
+            const uint32_t c0 = cc[r] & 0xFFFFu, c1 = cc[r] >> 16;
             if (v0 && c0 != CODE_BG) atomicAdd(c0 < static_cast<uint32_t>(TSITES) ? &Ci[c0] : &Cb[c0 - TSITES], 1);
             if (v1 && c1 != CODE_BG) atomicAdd(c1 < static_cast<uint32_t>(TSITES) ? &Ci[c1] : &Cb[c1 - TSITES], 1);
         }
