@@ -258,9 +258,9 @@ __device__ __forceinline__ int wave_max_below(int v)
 }
 
 // LDS of the tile phase: under 40 KB per 64 rows.
-template <int MODE, int TH_>
+template <int MODE, int TH_, int RPW_ = RPW>
 struct TileSmem {
-    static constexpr int TH = TH_, TSITES = TW * TH, NWAVE = TH / RPW;
+    static constexpr int TH = TH_, TSITES = TW * TH, NWAVE = TH / RPW_;
     int P[TSITES + 4];                 // union-find parent per site slot, as 4 x slot; P[TSITES]: background
     uint16_t wl[NWAVE][TLIST];         // per-wave work list (contacts, then linked labels)
     uint32_t xr_w[NWAVE];              // right crossing bonds of each wave's rows (bit r: its row r)
@@ -305,12 +305,12 @@ __device__ __forceinline__ KernTileArgs *kernel_tile_args()
 // output pointers are re-read from it where they are used; with RKEYS (a
 // single-lattice sweep) so is the bond generator's key schedule, row by row
 // (scalar loads in place of 18 scalar adds per row).
-template <int MODE, bool EVENW, int TH_, bool KARG = false, bool RKEYS = false>
-__device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int lt, TileSmem<MODE, TH_> &sm)
+template <int MODE, bool EVENW, int TH_, bool KARG = false, bool RKEYS = false, int RPW_ = RPW>
+__device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int lt, TileSmem<MODE, TH_, RPW_> &sm)
 {
     using S = Tile<TH_>;
     constexpr int TH = S::TH, TSITES = S::TSITES, CAP = S::CAP, EDGE = S::EDGE, XR = S::XR, XW = S::XW;
-    constexpr int NT = S::NT, NWAVE = S::NWAVE;
+    constexpr int RPW = RPW_, NWAVE = TH / RPW, NT = 64 * NWAVE;  // rows per wave
     constexpr bool NEED_DOWN = MODE == M_SW || MODE == M_SITES;  // bonds from two rows
     constexpr bool NEED_HALO = MODE == M_SW || MODE == M_SITES;  // column right of the tile
     constexpr int TL = TLIST;
@@ -727,10 +727,13 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
 // under 40 KB per 64 rows and the registers are held to what 8 waves allow
 // (some scalar registers spill to vector lanes; the extra latency hiding is
 // worth more).
-template <int MODE, bool EVENW, bool BATCH, int TH_>
-__global__ __launch_bounds__(Tile<TH_>::NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_tile(TileArgs a)
+// RPW_ = RPW_SMALL: twice the waves with half the rows each, for lattices of few
+// tiles (see the launch).
+constexpr int RPW_SMALL = 4;
+template <int MODE, bool EVENW, bool BATCH, int TH_, int RPW_ = RPW>
+__global__ __launch_bounds__(64 * TH_ / RPW_) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_tile(TileArgs a)
 {
-    __shared__ TileSmem<MODE, TH_> sm;
+    __shared__ TileSmem<MODE, TH_, RPW_> sm;
     int tile, lt;  // tile in the arrays, tile inside its lattice
     if constexpr (BATCH) {
         tile = a.b.tile_base + xcd_remap(blockIdx.x, a.b.ntiles);
@@ -739,7 +742,7 @@ __global__ __launch_bounds__(Tile<TH_>::NT) __attribute__((amdgpu_waves_per_eu(8
         tile = lt = xcd_remap(blockIdx.x, a.g.ntiles);
         if (a.g.rev) tile = lt = a.g.ntiles - 1 - tile;
     }
-    tile_body<MODE, EVENW, TH_, true, !BATCH && MODE == M_SW>(a, tile, lt, sm);
+    tile_body<MODE, EVENW, TH_, true, !BATCH && MODE == M_SW, RPW_>(a, tile, lt, sm);
 }
 
 // ---------------------------------------------------------------- merge ----
@@ -1891,10 +1894,10 @@ __device__ __forceinline__ const ReqDesc &req_of(const ReqBatch &rb, int t, int 
     return R;
 }
 
-template <int MODE, int TH_>
-__global__ __launch_bounds__(Tile<TH_>::NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_tile_reqs(ReqBatch rb)
+template <int MODE, int TH_, int RPW_>
+__global__ __launch_bounds__(64 * TH_ / RPW_) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_tile_reqs(ReqBatch rb)
 {
-    __shared__ TileSmem<MODE, TH_> sm;
+    __shared__ TileSmem<MODE, TH_, RPW_> sm;
     int lt;
     const ReqDesc &R = req_of(rb, xcd_remap(blockIdx.x, rb.ntiles), lt);
     TileArgs a{};
@@ -1908,7 +1911,7 @@ __global__ __launch_bounds__(Tile<TH_>::NT) __attribute__((amdgpu_waves_per_eu(8
     a.xbits = R.xbits;
     a.nb = R.nb;
     // any width: the odd-width form of the row loads serves even widths too
-    tile_body<MODE, false, TH_>(a, lt, lt, sm);
+    tile_body<MODE, false, TH_, false, false, RPW_>(a, lt, lt, sm);
 }
 
 template <int TH_>

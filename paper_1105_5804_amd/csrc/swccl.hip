@@ -256,6 +256,13 @@ MergeArgs merge_args(const Layout &L, void *ws)
     return m;
 }
 
+// Up to this many tiles of the default shape a tile is worked by twice the waves
+// with half the rows each: the chip has waves to spare, and the rows of a wave
+// follow each other.  A q = 3 sweep, 8 -> 4 rows a wave: 512 x 500 (32 tiles)
+// 26.9 -> 24.4 us, 1001 x 2001 (256) 32.8 -> 29.8, 2048^2 (512) 35.4 -> 34.4 and at
+// 1.4 beta_c 38.2 -> 38.4, 4096 x 2048 (1024) 49.7 -> 51.8.
+constexpr int64_t TILE_SMALL = 256;
+
 // Even W keeps every row start even: one 16-bit load per lane pair.
 template <int MODE>
 void launch_tile(const Layout &L, const TileArgs &ta, hipStream_t s)
@@ -263,6 +270,16 @@ void launch_tile(const Layout &L, const TileArgs &ta, hipStream_t s)
     with_tile_h(L.d.th, [&](auto c) {
         constexpr int TH = decltype(c)::value;
         const dim3 grid(static_cast<unsigned>(L.g.ntiles)), block(Tile<TH>::NT);
+        if constexpr (TH == TH_DEFAULT) {
+            if (L.g.ntiles <= TILE_SMALL) {
+                const dim3 wide(64 * TH / RPW_SMALL);
+                if (L.g.W % 2 == 0)
+                    hipLaunchKernelGGL((k_tile<MODE, true, false, TH, RPW_SMALL>), grid, wide, 0, s, ta);
+                else
+                    hipLaunchKernelGGL((k_tile<MODE, false, false, TH, RPW_SMALL>), grid, wide, 0, s, ta);
+                return;
+            }
+        }
         if (L.g.W % 2 == 0)
             hipLaunchKernelGGL((k_tile<MODE, true, false, TH>), grid, block, 0, s, ta);
         else
@@ -1500,11 +1517,19 @@ sw_status label_batch(const LabelRequest *r, int32_t n, int32_t mode, bool sizes
     rb.ntiles = tile;
     constexpr int TH = TH_DEFAULT;
     const dim3 tiles(static_cast<unsigned>(tile));
-    switch (mode) {
-    case CCL_BONDS_PERIODIC: hipLaunchKernelGGL((k_tile_reqs<M_BONDS_PERIODIC, TH>), tiles, dim3(Tile<TH>::NT), 0, s, rb); break;
-    case CCL_BONDS_OPEN: hipLaunchKernelGGL((k_tile_reqs<M_BONDS_OPEN, TH>), tiles, dim3(Tile<TH>::NT), 0, s, rb); break;
-    default: hipLaunchKernelGGL((k_tile_reqs<M_SITES, TH>), tiles, dim3(Tile<TH>::NT), 0, s, rb); break;
-    }
+    auto launch = [&](auto rpw) {
+        constexpr int R = decltype(rpw)::value;
+        const dim3 block(64 * TH / R);
+        switch (mode) {
+        case CCL_BONDS_PERIODIC: hipLaunchKernelGGL((k_tile_reqs<M_BONDS_PERIODIC, TH, R>), tiles, block, 0, s, rb); break;
+        case CCL_BONDS_OPEN: hipLaunchKernelGGL((k_tile_reqs<M_BONDS_OPEN, TH, R>), tiles, block, 0, s, rb); break;
+        default: hipLaunchKernelGGL((k_tile_reqs<M_SITES, TH, R>), tiles, block, 0, s, rb); break;
+        }
+    };
+    if (tile <= TILE_SMALL)
+        launch(std::integral_constant<int, RPW_SMALL>{});
+    else
+        launch(std::integral_constant<int, RPW>{});
     constexpr int MW = MERGE_WAVES_DEFAULT;
     hipLaunchKernelGGL(k_merge_reqs<TH>, dim3(static_cast<unsigned>(cdiv(static_cast<int64_t>(tile) * MergePasses<TH>::N, MW))),
                        dim3(64 * MW), 0, s, rb);
