@@ -334,7 +334,7 @@ def ccl3_label(bonds, workspace=None, stream=None):
         if workspace.device.type != "cuda" or workspace.numel() < ws or wptr % 256:
             raise ValueError(f"workspace must be a 256-byte aligned GPU buffer of at least {ws} bytes")
     labels = torch.empty((Lz, Ly, Lx), dtype=torch.int32, device=bonds.device)
-    ncl = torch.zeros(1, dtype=torch.int32, device=bonds.device)
+    ncl = torch.empty(1, dtype=torch.int32, device=bonds.device)  # written by the library
     s = stream if stream is not None else torch.cuda.current_stream(bonds.device)
     _lib.check(L.ccl3_label(bonds.data_ptr(), Lx, Ly, Lz, labels.data_ptr(), ncl.data_ptr(), wptr, ws,
                             _stream(torch, s)), "ccl3_label")

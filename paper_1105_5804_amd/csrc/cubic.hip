@@ -185,9 +185,12 @@ __device__ __forceinline__ int face_slot(int t, const TileOf &T)
 // kernel 868 -> 473 us at 512^3 and beta_c, the sweep 1.539 -> 1.083 ms.
 // FOUR: Lx is a multiple of 4 (pairs of sites load and store as one, and
 // share random blocks); the general form serves every Lx.
-template <bool LABEL, bool FOUR>
-__global__ __launch_bounds__(NT3) __attribute__((amdgpu_waves_per_eu(8, 8))) void k3_tile(Tile3Args a)
+// ROWS: steps (tile rows along y) of a wave; half of ITER with twice the waves
+// on lattices of few tiles (see the launch).
+template <bool LABEL, bool FOUR, int ROWS>
+__global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_eu(8, 8))) void k3_tile(Tile3Args a)
 {
+    constexpr int ITER = ROWS, YW = CY / ROWS, NW3 = YW * CZ / SUB, NT3 = 64 * NW3;  // waves along y, and in all
     __shared__ int P[CSITES];             // union-find parent per slot, as 4 x slot
     __shared__ uint16_t wl[NW3][TL3];     // per-wave list: 4 x slot | direction (0 +y, 1 +z) of a bond, or a label
     __shared__ uint32_t zb[NW3][LPR];     // +z bonds of the wave's last plane: bit 2 it + j of a lane's sites
@@ -197,7 +200,7 @@ __global__ __launch_bounds__(NT3) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     const TileOf T = tile_of(g, xcd_remap(blockIdx.x, g.ntiles));
     const int lane = threadIdx.x & 63, w = wave_id();
     const int sub = lane / LPR, lx0 = 2 * (lane % LPR), x4 = 4 * lx0;
-    const int lz = (w >> 1) * SUB + sub, ly0 = (w & 1) * ITER;
+    const int lz = w / YW * SUB + sub, ly0 = w % YW * ITER;
     const int nr = max(0, min(ITER, T.th - ly0));  // tile rows along y owned by this wave
     const bool zin = lz < T.td;
     const bool v0 = zin && lx0 < T.tw, v1 = zin && lx0 + 1 < T.tw;
@@ -441,11 +444,11 @@ __global__ __launch_bounds__(NT3) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
                               lanes_eq(static_cast<uint32_t>(got1), static_cast<uint32_t>(n1))};
         append(eo_andnot(m, met), own | dir);
     };
-    if (nr == ITER && ly0 + ITER < T.th)  // the y range's second half
+    if (nr == ITER && ly0 + ITER < T.th)  // the next part of the y range
         link_across(prevY, own_first + (ITER - 1) * 4 * CX, 4 * CX, lab0[ITER - 1], lab1[ITER - 1], 0);
     {
         // the wave's last plane to the next wave's first: RPI rows a step
-        const int lz_last = (w >> 1) * SUB + SUB - 1;
+        const int lz_last = w / YW * SUB + SUB - 1;
 #pragma unroll
         for (int s = 0; s < ITER / RPI; ++s) {
             const int it = s * RPI + sub;
@@ -521,7 +524,7 @@ __global__ __launch_bounds__(NT3) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     // carry ids)
     {
         uint32_t *codes32 = reinterpret_cast<uint32_t *>(a.codes + static_cast<int64_t>(T.tile) * CSITES) +
-                            w * ITER * 64 + lane;
+                            (w / YW * CY + ly0) * 64 + lane;
         uint16_t *xf = a.xface + static_cast<int64_t>(T.tile) * (2 * FX) + lz * CY + ly0;
         const bool z_last = lz == T.td - 1;
 #pragma unroll
@@ -920,6 +923,12 @@ using namespace swccl::cubic;
 namespace {
 
 constexpr size_t ALIGN3 = 256;
+// Up to this many tiles the tile kernel takes 16 waves a tile, four steps each,
+// else 8 of eight: a wave's steps follow each other, and there are waves to spare.
+// Critical Ising sweep, 8 -> 16 waves: 100 x 75 x 61 (80 tiles) 51.3 -> 45.8 us,
+// 101 x 75 x 61 59.0 -> 51.5, 160^3 (500) 71.2 -> 67.4; 200 x 210 x 200 (1274) takes
+// 123 with 8.
+constexpr int TILE3_SMALL = 512;
 // Up to this many tiles the merge takes 1024 threads a tile, else 256.  Critical
 // Ising sweep, 256 -> 1024: 100 x 75 x 61 (80 tiles) 55.5 -> 51.6 us, 160^3 (500)
 // 75 -> 72, 256^3 (2048) 161 -> 175.
@@ -996,10 +1005,17 @@ template <bool LABEL>
 void launch_tile3(const Tile3Args &ta, hipStream_t s)
 {
     const dim3 tiles(static_cast<unsigned>(ta.g.ntiles));
-    if (ta.g.Lx % 4 == 0)
-        hipLaunchKernelGGL((k3_tile<LABEL, true>), tiles, dim3(NT3), 0, s, ta);
-    else
-        hipLaunchKernelGGL((k3_tile<LABEL, false>), tiles, dim3(NT3), 0, s, ta);
+    const bool four = ta.g.Lx % 4 == 0;
+    if (ta.g.ntiles <= TILE3_SMALL) {
+        if (four)
+            hipLaunchKernelGGL((k3_tile<LABEL, true, ITER / 2>), tiles, dim3(2 * NT3), 0, s, ta);
+        else
+            hipLaunchKernelGGL((k3_tile<LABEL, false, ITER / 2>), tiles, dim3(2 * NT3), 0, s, ta);
+    } else if (four) {
+        hipLaunchKernelGGL((k3_tile<LABEL, true, ITER>), tiles, dim3(NT3), 0, s, ta);
+    } else {
+        hipLaunchKernelGGL((k3_tile<LABEL, false, ITER>), tiles, dim3(NT3), 0, s, ta);
+    }
 }
 
 // The merge and the resolve are chains of dependent global accesses: while the
