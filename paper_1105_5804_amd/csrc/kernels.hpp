@@ -42,7 +42,6 @@ namespace swccl {
 
 constexpr int TW = 128;               // tile width: a wave covers a tile row, 2 sites per lane
 constexpr int RPW = 8;                // tile rows per wave
-constexpr int WLIST = RPW * TW;       // per-wave work list capacity (one entry per site at most)
 constexpr int TLIST = 3 * TW;         // k_tile's per-wave lists: a row adds at most TW entries, a
                                       // fuller list is worked off first (keeps the LDS per wave small)
 constexpr uint16_t ID_NONE = 0xFFFF;
@@ -940,20 +939,20 @@ __device__ __forceinline__ uint8_t flip_byte(uint32_t R, const FlatArgs &a)
 }
 
 // LDS of the flatten phase.
-template <int MODE, bool SIZES, int TH_>
+template <int MODE, bool SIZES, int TH_, int RPW_ = RPW>
 struct FlatSmem {
-    static constexpr int TH = TH_, TSITES = TW * TH, CAP = 2 * (TW + TH), NWAVE = TH / RPW;
+    static constexpr int TH = TH_, TSITES = TW * TH, CAP = 2 * (TW + TH), NWAVE = TH / RPW_;
     // new spin byte per code (root slot or TSITES + boundary id); M_FEW: new
     // state, FEW_KEEP = no change
     uint8_t ST[MODE == M_SW || MODE == M_FEW ? TSITES + CAP : 1];
     int32_t Rb[CAP];                              // canonical root (site index) per boundary id
     int32_t Gid[CAP];                             // root id per boundary id
-    uint16_t rl[NWAVE][WLIST];                    // interior roots of each wave's rows
+    uint16_t rl[NWAVE][RPW_ * TW];                // interior roots of each wave's rows
     int ncl_w[NWAVE];
     int32_t Ci[SIZES ? TSITES : 1];               // sizes of interior clusters
     int32_t Cb[SIZES ? CAP : 1];                  // per-tile part of boundary clusters
     int32_t rowc[TH];
-    uint32_t seedw_s[MODE == M_FEW ? NWAVE : 1][32];  // M_FEW: seed-map words of each wave's rows
+    uint32_t seedw_s[MODE == M_FEW ? NWAVE : 1][RPW_ * TW / 32];  // M_FEW: seed-map words of each wave's rows
 };
 
 __device__ __forceinline__ void load_batch_flat(FlatArgs &a, int tile, int &lt)
@@ -990,11 +989,13 @@ __device__ __forceinline__ void exclusive_rows(int32_t *v, int n, int lane)
 // The flatten + flip of one tile (`tile` in the arrays, `lt` inside its
 // lattice), by a Tile<TH>::NT-thread workgroup.  M_FEW flips only the seeded
 // clusters whose draw says so and writes only their sites.
-template <int MODE, bool SIZES, int TH_>
-__device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const int lt, FlatSmem<MODE, SIZES, TH_> &sm)
+template <int MODE, bool SIZES, int TH_, int RPW_ = RPW>
+__device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const int lt,
+                                             FlatSmem<MODE, SIZES, TH_, RPW_> &sm)
 {
     using S = Tile<TH_>;
-    constexpr int TH = S::TH, TSITES = S::TSITES, CAP = S::CAP, NT = S::NT, NWAVE = S::NWAVE;
+    constexpr int TH = S::TH, TSITES = S::TSITES, CAP = S::CAP;
+    constexpr int RPW = RPW_, NWAVE = TH / RPW, NT = 64 * NWAVE;  // rows per wave
     constexpr int BPT = (CAP + NT - 1) / NT;  // boundary ids per thread
     constexpr int NCODE = CAP + TSITES;
     uint8_t *ST = sm.ST;
@@ -1033,12 +1034,13 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
         for (int k = threadIdx.x; k < TSITES; k += NT) Ci[k] = 0;
         for (int k = threadIdx.x; k < CAP; k += NT) Cb[k] = 0;
     }
-    // M_FEW: the seed-map words of this wave's rows (RPW * TW / 32 = 32 of
-    // them, word l in lane l), cleared for the next sweep
+    // M_FEW: the seed-map words of this wave's rows (word l in lane l), cleared
+    // for the next sweep
+    constexpr int SEEDW = RPW * TW / 32;
+    static_assert(SEEDW <= 64, "a seed-map word per lane");
     uint32_t seedw = 0;
     if constexpr (MODE == M_FEW) {
-        static_assert(RPW * TW / 32 == 32, "one seed-map word per lane of the lower half");
-        if (lane < 32) {
+        if (lane < SEEDW) {
             uint32_t *w = a.seedmap + static_cast<int64_t>(tile) * (TSITES / 32) + ly0 * (TW / 32) + lane;
             seedw = *w;
             if (seedw) *w = 0u;
@@ -1073,7 +1075,7 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
         // wave keeps in its own LDS words; a seeded root's spin is loaded
         // ahead of the draw
         uint32_t *myseed = sm.seedw_s[wave];
-        if (lane < 32) myseed[lane] = seedw;
+        if (lane < SEEDW) myseed[lane] = seedw;
         wave_lds_fence();
         for (int i = lane; i < nroot; i += 64) {
             const int slot = mylist[i];
@@ -1264,10 +1266,10 @@ __device__ __forceinline__ void flatten_body(FlatArgs a, const int tile, const i
     }
 }
 
-template <int MODE, bool SIZES, bool BATCH, int TH_>
-__global__ __launch_bounds__(Tile<TH_>::NT) void k_flatten(FlatArgs a)
+template <int MODE, bool SIZES, bool BATCH, int TH_, int RPW_ = RPW>
+__global__ __launch_bounds__(64 * TH_ / RPW_) void k_flatten(FlatArgs a)
 {
-    __shared__ FlatSmem<MODE, SIZES, TH_> sm;
+    __shared__ FlatSmem<MODE, SIZES, TH_, RPW_> sm;
     int tile, lt;  // tile in the arrays, tile inside its lattice
     if constexpr (BATCH) {
         tile = a.b.tile_base + xcd_remap(blockIdx.x, a.b.ntiles);
@@ -1276,7 +1278,7 @@ __global__ __launch_bounds__(Tile<TH_>::NT) void k_flatten(FlatArgs a)
         tile = lt = xcd_remap(blockIdx.x, a.g.ntiles);
         if (a.g.rev) tile = lt = a.g.ntiles - 1 - tile;
     }
-    flatten_body<MODE, SIZES, TH_>(a, tile, lt, sm);
+    flatten_body<MODE, SIZES, TH_, RPW_>(a, tile, lt, sm);
 }
 
 // Sum of n per-tile int32 counters (256-byte aligned) by one workgroup.
@@ -1931,10 +1933,10 @@ __global__ __launch_bounds__(1024) void k_merge_reqs(ReqBatch rb)
     merge_tile<false, TH_, 1>(m, lt, job - t * NP);
 }
 
-template <bool SIZES, int TH_>
-__global__ __launch_bounds__(Tile<TH_>::NT) void k_flatten_reqs(ReqBatch rb)
+template <bool SIZES, int TH_, int RPW_>
+__global__ __launch_bounds__(64 * TH_ / RPW_) void k_flatten_reqs(ReqBatch rb)
 {
-    __shared__ FlatSmem<M_BONDS_PERIODIC, SIZES, TH_> sm;
+    __shared__ FlatSmem<M_BONDS_PERIODIC, SIZES, TH_, RPW_> sm;
     int lt;
     const ReqDesc &R = req_of(rb, xcd_remap(blockIdx.x, rb.ntiles), lt);
     FlatArgs f{};
@@ -1949,7 +1951,7 @@ __global__ __launch_bounds__(Tile<TH_>::NT) void k_flatten_reqs(ReqBatch rb)
     f.row_count = R.row_count;
     f.rl_slot = R.rl_slot;
     f.rl_size = R.rl_size;
-    flatten_body<M_BONDS_PERIODIC, SIZES, TH_>(f, lt, lt, sm);
+    flatten_body<M_BONDS_PERIODIC, SIZES, TH_, RPW_>(f, lt, lt, sm);
 }
 
 template <int TH_>

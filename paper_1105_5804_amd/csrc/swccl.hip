@@ -310,13 +310,25 @@ void launch_merge(const Layout &L, const MergeArgs &ma, int64_t ntiles, hipStrea
     });
 }
 
+// The same for the flatten: a q = 3 sweep of 512 x 500 24.5 -> 23.9 us, with its
+// cluster list 40.9 -> 38.2, 1001 x 2001 (256 tiles) 54.4 -> 52.0; 2048^2 (512) 73.8
+// -> 74.7.
+constexpr int64_t FLAT_SMALL = 256;
+
 template <int MODE, bool SIZES, bool BATCH>
 void launch_flatten(const Layout &L, const FlatArgs &fa, int64_t ntiles, hipStream_t s)
 {
     with_tile_h(L.d.th, [&](auto c) {
         constexpr int TH = decltype(c)::value;
-        hipLaunchKernelGGL((k_flatten<MODE, SIZES, BATCH, TH>), dim3(static_cast<unsigned>(ntiles)),
-                           dim3(Tile<TH>::NT), 0, s, fa);
+        const dim3 grid(static_cast<unsigned>(ntiles));
+        if constexpr (TH == TH_DEFAULT && !BATCH) {
+            if (ntiles <= FLAT_SMALL) {
+                hipLaunchKernelGGL((k_flatten<MODE, SIZES, BATCH, TH, RPW_SMALL>), grid, dim3(64 * TH / RPW_SMALL), 0, s,
+                                   fa);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_flatten<MODE, SIZES, BATCH, TH>), grid, dim3(Tile<TH>::NT), 0, s, fa);
     });
 }
 
@@ -1533,11 +1545,18 @@ sw_status label_batch(const LabelRequest *r, int32_t n, int32_t mode, bool sizes
     constexpr int MW = MERGE_WAVES_DEFAULT;
     hipLaunchKernelGGL(k_merge_reqs<TH>, dim3(static_cast<unsigned>(cdiv(static_cast<int64_t>(tile) * MergePasses<TH>::N, MW))),
                        dim3(64 * MW), 0, s, rb);
+    auto flatten = [&](auto with_sizes) {
+        constexpr bool SZ = decltype(with_sizes)::value;
+        if (tile <= FLAT_SMALL)
+            hipLaunchKernelGGL((k_flatten_reqs<SZ, TH, RPW_SMALL>), tiles, dim3(64 * TH / RPW_SMALL), 0, s, rb);
+        else
+            hipLaunchKernelGGL((k_flatten_reqs<SZ, TH, RPW>), tiles, dim3(Tile<TH>::NT), 0, s, rb);
+    };
     if (sizes) {
-        hipLaunchKernelGGL((k_flatten_reqs<true, TH>), tiles, dim3(Tile<TH>::NT), 0, s, rb);
+        flatten(std::true_type{});
         hipLaunchKernelGGL(k_emit_reqs<TH>, tiles, dim3(NT), 0, s, rb);
     } else {
-        hipLaunchKernelGGL((k_flatten_reqs<false, TH>), tiles, dim3(Tile<TH>::NT), 0, s, rb);
+        flatten(std::false_type{});
         hipLaunchKernelGGL(k_count_reqs, dim3(static_cast<unsigned>(n)), dim3(NT), 0, s, rb.req);
     }
     return launch_status("batched labeling");
