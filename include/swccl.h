@@ -132,9 +132,9 @@ typedef struct sw_params {
                            tile size is a free parameter of the paper's
                            local/global split (Sec. II.E, Eqs. optimaltile1-2);
                            results do not depend on it                      */
-    int32_t merge_waves; /* merge schedule: tiles per merge workgroup (one
-                           wave each), 4, 8 or 16, or 0 for the default 8;
-                           results do not depend on it                      */
+    int32_t merge_waves; /* merge schedule: waves per merge workgroup (each
+                           merging a tile or a part of one), 4, 8 or 16, or 0
+                           for the default 8; results do not depend on it   */
     double p_flip;      /* few-cluster update only: flip probability of a
                            seeded cluster, 0 <= p_flip < 1                  */
     int32_t few_b;      /* 0: the SW update (every cluster draws a new

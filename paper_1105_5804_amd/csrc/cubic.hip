@@ -968,7 +968,9 @@ sw_status check3(const sw3_params *p)
     return check_shape3(p->Lx, p->Ly, p->Lz);
 }
 
-Layout3 layout3(int32_t Lx, int32_t Ly, int32_t Lz)
+// observed: a sweep's workspace, which also holds the observables' ticket and
+// partial sums (a labeling takes none).
+Layout3 layout3(int32_t Lx, int32_t Ly, int32_t Lz, bool observed)
 {
     Layout3 L{};
     L.g.Lx = Lx;
@@ -993,13 +995,15 @@ Layout3 layout3(int32_t Lx, int32_t Ly, int32_t Lz)
     L.nb = take(nt * sizeof(int32_t));
     L.tile_act = take(nt * sizeof(int32_t));
     L.tile_ncl = take(nt * sizeof(int32_t));
-    L.ticket = take(sizeof(uint32_t));
-    L.obs_part = take(OBS_PART_BYTES);
+    if (observed) {
+        L.ticket = take(sizeof(uint32_t));
+        L.obs_part = take(OBS_PART_BYTES);
+    }
     L.total = off;
     return L;
 }
 
-Layout3 layout3(const sw3_params *p) { return layout3(p->Lx, p->Ly, p->Lz); }
+Layout3 layout3(const sw3_params *p) { return layout3(p->Lx, p->Ly, p->Lz, true); }
 
 template <bool LABEL>
 void launch_tile3(const Tile3Args &ta, hipStream_t s)
@@ -1077,7 +1081,7 @@ sw_status sw3_init_spins(const sw3_params *p, uint8_t *spins, void *stream)
 size_t ccl3_workspace_bytes(int32_t Lx, int32_t Ly, int32_t Lz)
 {
     if (check_shape3(Lx, Ly, Lz) != SW_OK) return 0;
-    return layout3(Lx, Ly, Lz).total;
+    return layout3(Lx, Ly, Lz, false).total;
 }
 
 sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, int32_t *labels, int32_t *n_clusters,
@@ -1086,7 +1090,7 @@ sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, i
     const sw_status st = check_shape3(Lx, Ly, Lz);
     if (st != SW_OK) return st;
     if (!bonds || !labels) return SW_ERR_ARG;
-    const Layout3 L = layout3(Lx, Ly, Lz);
+    const Layout3 L = layout3(Lx, Ly, Lz, false);
     if (!workspace || workspace_bytes < L.total || reinterpret_cast<uintptr_t>(workspace) % ALIGN3)
         return SW_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
