@@ -73,6 +73,12 @@ __device__ __forceinline__ uint32_t from_next_lane(uint32_t x)
     return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x130, 0xF, 0xF, false));
 }
 
+// The same, the last lane getting `last` (wave-uniform).
+__device__ __forceinline__ uint32_t from_next_lane_or(uint32_t x, int last)
+{
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(last, static_cast<int>(x), 0x130, 0xF, 0xF, false));
+}
+
 // ---- LDS union-find (workgroup scope) ----
 __device__ __forceinline__ int lds_ld(int *p)
 {
