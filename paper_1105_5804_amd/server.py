@@ -63,12 +63,16 @@ class CCLServer:
     def footprint(self, W: int, H: int) -> int:
         return int(_lib.lib().ccl_server_footprint(int(W), int(H), ctypes.byref(self.params)))
 
+    def _wait_released(self) -> None:
+        """Every server stream waits for the work that callers had enqueued on
+        the blocks released since the last time (see release)."""
+        for ev in self._fences.values():
+            for s in self.streams:
+                s.wait_event(ev)
+        self._fences.clear()
+
     def _try_submit(self, tag: int, img) -> bool:
-        if self._fences:
-            for ev in self._fences.values():
-                for s in self.streams:
-                    s.wait_event(ev)
-            self._fences.clear()
+        self._wait_released()
         H, W = img.shape
         slot = ctypes.c_int32()
         st = _lib.lib().ccl_server_submit(self._h, img.data_ptr(), W, H, img.stride(0), tag, ctypes.byref(slot))
@@ -167,9 +171,10 @@ class CCLServer:
     def release(self, slot: int) -> None:
         """Return a request's arena block.  Work the caller has enqueued on the
         current stream (e.g. a copy of the result views) finishes before any
-        later request can write the block: every server stream waits for it
-        before the next request is submitted (once for a run of releases, by
-        the last of their events on each stream)."""
+        later request can write the block, and before the server's end: every
+        server stream waits for it before the next request is submitted and
+        before the server is destroyed (once for a run of releases, by the last
+        of their events on each stream)."""
         torch = _torch()
         cur = torch.cuda.current_stream(self.device)
         ev = torch.cuda.Event()
@@ -183,9 +188,14 @@ class CCLServer:
         return len(self._queue) + len(self._inflight)
 
     def close(self) -> None:
+        """End the server; waits for its streams, and with them for the work
+        enqueued on released blocks (the arena may be freed afterwards)."""
         if getattr(self, "_h", None) is not None and self._h.value:
-            _lib.lib().ccl_server_destroy(self._h)
-            self._h = ctypes.c_void_p()
+            try:
+                self._wait_released()
+            finally:
+                _lib.lib().ccl_server_destroy(self._h)
+                self._h = ctypes.c_void_p()
 
     def __del__(self):
         try:
