@@ -58,7 +58,7 @@ class CCLServer:
         self.rejected = []                  # (tag, status) dropped from the queue by pump
         self._pslots = (ctypes.c_int32 * cap)()
         self._ptags = (ctypes.c_uint64 * cap)()
-        self._fences = {}                   # stream -> event its next submit must wait for (see release)
+        self._fences = {}                   # per stream: event the next submit must wait for (see release)
 
     def footprint(self, W: int, H: int) -> int:
         return int(_lib.lib().ccl_server_footprint(int(W), int(H), ctypes.byref(self.params)))
@@ -174,12 +174,16 @@ class CCLServer:
         later request can write the block, and before the server's end: every
         server stream waits for it before the next request is submitted and
         before the server is destroyed (once for a run of releases, by the last
-        of their events on each stream)."""
+        of their events on each of torch's streams)."""
         torch = _torch()
         cur = torch.cuda.current_stream(self.device)
         ev = torch.cuda.Event()
         ev.record(cur)
-        self._fences[cur.cuda_stream] = ev
+        # torch keeps its own streams (and the null stream) for good, so a later
+        # event on one covers the earlier; a caller's stream (its id is its
+        # handle) may be gone and the handle come again: each event counts
+        own = cur.cuda_stream == 0 or cur.stream_id != cur.cuda_stream
+        self._fences[cur.cuda_stream if own else object()] = ev
         _lib.check(_lib.lib().ccl_server_release(self._h, int(slot)), "ccl_server_release")
         del self._inflight[slot]
 

@@ -83,3 +83,29 @@ def test_close_waits_for_released_blocks(monkeypatch):
     n = len(log)
     srv.close()  # a second close does nothing
     assert len(log) == n
+
+
+def test_a_run_of_releases_waits_once(monkeypatch):
+    srv, log, current = _server(monkeypatch)
+    current["stream"] = _Stream(7, 11, log)
+    for k in range(4):
+        srv.release(k)
+    img = torch.zeros((2, 2), dtype=torch.uint8)
+    assert srv._try_submit(9, img)
+    waits = _waited_before(log, "ccl_server_submit")
+    assert all(waits[s] == {3} for s in (1000, 1001))  # the stream's last event covers the ones before it
+    n = sum(e[0] == "wait" for e in log)
+    assert srv._try_submit(10, img)
+    assert sum(e[0] == "wait" for e in log) == n
+
+
+def test_streams_of_the_caller_keep_every_event(monkeypatch):
+    """A caller's own stream may be destroyed and its handle come again: the
+    event of a later release there says nothing about the earlier one's work."""
+    srv, log, current = _server(monkeypatch)
+    for k in range(3):
+        current["stream"] = _Stream(4096, 4096, log)
+        srv.release(k)
+    assert srv._try_submit(9, torch.zeros((2, 2), dtype=torch.uint8))
+    waits = _waited_before(log, "ccl_server_submit")
+    assert all(waits[s] == {0, 1, 2} for s in (1000, 1001))
