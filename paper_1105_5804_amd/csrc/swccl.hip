@@ -655,6 +655,8 @@ static bool small_path(const sw_lattice *h)
     return h->p.W <= SMALL_W && h->p.H <= SMALL_H && !h->L.sizes && !h->L.few;
 }
 
+// Advances t with every piece enqueued, so that it follows the spins when a
+// later piece fails.
 static sw_status launch_small(sw_lattice *h, int32_t n, int64_t *hist, hipStream_t s)
 {
     const Layout &L = h->L;
@@ -678,7 +680,7 @@ static sw_status launch_small(sw_lattice *h, int32_t n, int64_t *hist, hipStream
     // sweep's bonds and labels are written by the last piece
     for (int32_t done = 0; done < n; done += a.n) {
         a.n = std::min(n - done, SMALL_AHEAD);
-        a.t0 = static_cast<uint32_t>(h->t) + static_cast<uint32_t>(done);
+        a.t0 = static_cast<uint32_t>(h->t);
         const bool end = done + a.n == n;
         a.bonds_out = end ? h->b.bonds : nullptr;
         a.labels = end ? h->b.labels : nullptr;
@@ -687,9 +689,13 @@ static sw_status launch_small(sw_lattice *h, int32_t n, int64_t *hist, hipStream
             hipLaunchKernelGGL(k_small<false>, dim3(1), dim3(SMALL_NT), 0, s, a);
         } else {
             hipLaunchKernelGGL(k_small_words, dim3(static_cast<unsigned>(cdiv(a.n * nchunk, 4))), dim3(256), 0, s, a);
+            if (const sw_status st = launch_status("k_small_words")) return st;
             hipLaunchKernelGGL(k_small<true>, dim3(1), dim3(SMALL_NT), 0, s, a);
         }
         if (const sw_status st = launch_status("k_small")) return st;
+        h->t += static_cast<uint64_t>(a.n);
+        h->swept = true;
+        h->small_last = true;
     }
     return SW_OK;
 }
@@ -700,14 +706,7 @@ sw_status sw_sweep(sw_lattice *h, int32_t n_sweeps, void *stream)
     if (h->next_phase != SW_PHASE_TILE) return SW_ERR_STATE;
     if (h->t + static_cast<uint64_t>(n_sweeps) > 0xFFFFFFFFull) return SW_ERR_STATE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (n_sweeps > 0 && small_path(h)) {
-        const sw_status st = launch_small(h, n_sweeps, nullptr, s);
-        if (st != SW_OK) return st;
-        h->t += static_cast<uint64_t>(n_sweeps);
-        h->swept = true;
-        h->small_last = true;
-        return SW_OK;
-    }
+    if (n_sweeps > 0 && small_path(h)) return launch_small(h, n_sweeps, nullptr, s);
     for (int32_t n = 0; n < n_sweeps; ++n) {
         for (int32_t ph = SW_PHASE_TILE; ph <= SW_PHASE_FLIP; ++ph) {
             const sw_status st = launch_phase(h, ph, s);
@@ -817,14 +816,7 @@ sw_status sw_sweep_history(sw_lattice *h, int32_t n_sweeps, int64_t *history, vo
     if (h->t + static_cast<uint64_t>(n_sweeps) > 0xFFFFFFFFull) return SW_ERR_STATE;
     if (n_sweeps == 0) return SW_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (small_path(h)) {
-        const sw_status st = launch_small(h, n_sweeps, history, s);
-        if (st != SW_OK) return st;
-        h->t += static_cast<uint64_t>(n_sweeps);
-        h->swept = true;
-        h->small_last = true;
-        return SW_OK;
-    }
+    if (small_path(h)) return launch_small(h, n_sweeps, history, s);
     const Layout &L = h->L;
     void *ws = h->b.workspace;
     ObsArgs oa = obs_args(h->p, h->b.spins, L, ws);

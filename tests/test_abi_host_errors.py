@@ -1,0 +1,71 @@
+"""Failures of the HIP runtime as the library's host code meets them, with no
+device: the launches (and the error they leave) are a stub's, loaded ahead of
+the runtime in a process of its own."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+STUB = r"""
+#include <stdlib.h>
+static int launches, failing, last;
+void stub_fail_at(int n) { failing = n; launches = 0; }
+int __hipPushCallConfiguration() { return 0; }
+int __hipPopCallConfiguration() { return 0; }
+int stub_launches(void) { return launches; }
+int hipLaunchKernel() { if (++launches != failing) return 0; return last = 719; }
+int hipGetLastError(void) { int e = last; last = 0; return e; }
+"""
+
+PROGRAM = r"""
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+sys.path.insert(0, sys.argv[2])
+from paper_1105_5804_amd import _lib
+L = _lib.lib()
+W, H = 40, 30
+p = _lib.SwParams(W=W, H=H, q=2, spin_kind=0, K=0.88, seed=1, stream_id=0, flags=0)
+ws = L.sw_workspace_bytes(ctypes.byref(p))
+base = ctypes.create_string_buffer(ws + 256)
+at = ctypes.addressof(base)
+at += -at % 256
+spins = ctypes.create_string_buffer(W * H)
+b = _lib.SwBuffers(spins=ctypes.addressof(spins), workspace=at, workspace_bytes=ws)
+h = ctypes.c_void_p()
+assert L.sw_init(ctypes.byref(h), ctypes.byref(p), ctypes.byref(b), None) == _lib.SW_OK
+t = ctypes.c_uint64()
+hist = ctypes.create_string_buffer(200 * 96)
+done = 0
+# 130 sweeps go out as 64 + 64 + 2: two launches, two, one
+for fail_at, moved in ((1, 0), (2, 0), (3, 64), (4, 64), (5, 128), (0, 130)):
+    for records in (False, True):
+        stub.stub_fail_at(fail_at)
+        st = (L.sw_sweep_history(h, 130, ctypes.addressof(hist), None) if records else L.sw_sweep(h, 130, None))
+        assert st == (_lib.SW_OK if moved == 130 else _lib.SW_ERR_DEVICE), (fail_at, st)
+        assert stub.stub_launches() == (fail_at or 5)  # nothing goes out after a launch that failed
+        assert L.sw_get_t(h, ctypes.byref(t)) == _lib.SW_OK
+        done += moved
+        assert t.value == done, (fail_at, records, t.value, done)
+assert L.sw_destroy(h) == _lib.SW_OK
+print("ok")
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    d = tmp_path_factory.mktemp("stub")
+    src = d / "stub.c"
+    src.write_text(STUB)
+    lib = d / "libstub.so"
+    subprocess.check_call(["gcc", "-shared", "-fPIC", "-w", "-o", str(lib), str(src)])
+    return str(lib)
+
+
+def test_small_lattice_counts_the_sweeps_enqueued(stub):
+    """The sweep number follows the spins when a launch fails between the
+    pieces of a call."""
+    r = subprocess.run([sys.executable, "-c", PROGRAM, stub, ROOT], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr
