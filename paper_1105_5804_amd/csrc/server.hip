@@ -291,15 +291,6 @@ sw_status ccl_server_create(ccl_server **out, const ccl_server_params *p, void *
         delete s;
         return SW_ERR_HOST_MEMORY;
     }
-    void *dev = nullptr;
-    if (hipHostMalloc(reinterpret_cast<void **>(&s->counts), sizeof(int32_t) * static_cast<size_t>(p->max_inflight),
-                      hipHostMallocDefault) != hipSuccess ||
-        hipHostGetDevicePointer(&dev, s->counts, 0) != hipSuccess) {
-        free_pinned(s);
-        delete s;
-        return SW_ERR_HOST_MEMORY;
-    }
-    s->counts_dev = static_cast<int32_t *>(dev);
     try {
         s->free_blocks[first] = s->arena_bytes - first;
         for (int32_t i = 0; i < p->n_streams; ++i) s->streams.push_back(static_cast<hipStream_t>(streams[i]));
@@ -315,15 +306,22 @@ sw_status ccl_server_create(ccl_server **out, const ccl_server_params *p, void *
         delete s;
         return SW_ERR_HOST_MEMORY;
     }
-    for (auto &e : s->ev) {
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-            for (auto &f : s->ev)
-                if (f) (void)hipEventDestroy(f);
-            free_pinned(s);
-            delete s;
-            return SW_ERR_DEVICE;
-        }
-    }
+    auto give_back = [s](sw_status st) {
+        for (auto &f : s->ev)
+            if (f) (void)hipEventDestroy(f);
+        free_pinned(s);
+        delete s;
+        (void)hipGetLastError();  // reported here: not for the next launch to find
+        return st;
+    };
+    for (auto &e : s->ev)
+        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return give_back(SW_ERR_DEVICE);
+    void *dev = nullptr;
+    if (hipHostMalloc(reinterpret_cast<void **>(&s->counts), sizeof(int32_t) * static_cast<size_t>(p->max_inflight),
+                      hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer(&dev, s->counts, 0) != hipSuccess)
+        return give_back(SW_ERR_HOST_MEMORY);
+    s->counts_dev = static_cast<int32_t *>(dev);
     *out = s;
     return SW_OK;
 }

@@ -18,6 +18,16 @@ int __hipPopCallConfiguration() { return 0; }
 int stub_launches(void) { return launches; }
 int hipLaunchKernel() { if (++launches != failing) return 0; return last = 719; }
 int hipGetLastError(void) { int e = last; last = 0; return e; }
+static int events, memory, live;
+void stub_server(int e, int m) { events = e; memory = m; }
+int stub_live(void) { return live; }
+int hipEventCreateWithFlags(void **e) { if (events-- <= 0) return last = 100; *e = &live; ++live; return 0; }
+int hipEventSynchronize() { return 0; }
+int hipStreamSynchronize() { return 0; }
+int hipEventDestroy() { --live; return 0; }
+int hipHostMalloc(void **p, size_t n) { if (memory-- <= 0) return last = 2; *p = malloc(n); ++live; return 0; }
+int hipHostGetDevicePointer(void **d, void *h) { *d = h; return 0; }
+int hipHostFree(void *p) { free(p); --live; return 0; }
 """
 
 PROGRAM = r"""
@@ -68,4 +78,35 @@ def test_small_lattice_counts_the_sweeps_enqueued(stub):
     """The sweep number follows the spins when a launch fails between the
     pieces of a call."""
     r = subprocess.run([sys.executable, "-c", PROGRAM, stub, ROOT], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr
+
+
+CREATE = r"""
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+sys.path.insert(0, sys.argv[2])
+from paper_1105_5804_amd import _lib
+L = _lib.lib()
+p = _lib.CclServerParams(_lib.CCL_SITES_OPEN, 1, 4, 1, 0)
+arena = ctypes.create_string_buffer((1 << 20) + 256)
+at = ctypes.addressof(arena)
+at += -at % 256
+h = ctypes.c_void_p()
+streams = (ctypes.c_void_p * 1)(None)
+for events, memory, want in ((0, 0, _lib.SW_ERR_DEVICE), (3, 1, _lib.SW_ERR_DEVICE),
+                             (4, 0, _lib.SW_ERR_HOST_MEMORY), (4, 1, _lib.SW_OK)):
+    stub.stub_server(events, memory)
+    st = L.ccl_server_create(ctypes.byref(h), ctypes.byref(p), at, 1 << 20, streams)
+    assert st == want, (events, memory, st)
+    if st == _lib.SW_OK:
+        assert L.ccl_server_destroy(h) == _lib.SW_OK
+    assert stub.stub_live() == 0, (events, memory)  # whatever was made is given back
+    assert stub.hipGetLastError() == 0  # and no error is left for another call to find
+print("ok")
+"""
+
+
+def test_server_create_reports_what_failed(stub):
+    """No device: SW_ERR_DEVICE; no pinned memory: SW_ERR_HOST_MEMORY."""
+    r = subprocess.run([sys.executable, "-c", CREATE, stub, ROOT], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr
