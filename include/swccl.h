@@ -71,7 +71,7 @@
 extern "C" {
 #endif
 
-#define SWCCL_ABI_VERSION 7
+#define SWCCL_ABI_VERSION 8
 
 typedef int32_t sw_status;
 enum {

@@ -7,7 +7,7 @@ import os
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libswccl.so")
 
-ABI_VERSION = 7  # the SWCCL_ABI_VERSION these declarations follow
+ABI_VERSION = 8  # the SWCCL_ABI_VERSION these declarations follow
 
 # status codes
 SW_OK, SW_ERR_ARG, SW_ERR_SIZE, SW_ERR_WORKSPACE, SW_ERR_DEVICE, SW_ERR_STATE, SW_ERR_UNSUPPORTED, SW_ERR_HOST_MEMORY = range(8)
@@ -177,12 +177,14 @@ def lib():
                 f"{LIB_PATH} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`"
             )
         L = ctypes.CDLL(LIB_PATH)
+        # the version first: an older library may lack some of the functions
+        L.swccl_abi_version.restype = ctypes.c_int32
+        if L.swccl_abi_version() != ABI_VERSION:
+            raise RuntimeError(f"{LIB_PATH} has ABI {L.swccl_abi_version()}, expected {ABI_VERSION}: rebuild it")
         for name, (res, args) in SIGNATURES.items():
             fn = getattr(L, name)
             fn.restype = res
             fn.argtypes = args
-        if L.swccl_abi_version() != ABI_VERSION:
-            raise RuntimeError(f"{LIB_PATH} has ABI {L.swccl_abi_version()}, expected {ABI_VERSION}: rebuild it")
         _lib = L
     return _lib
 

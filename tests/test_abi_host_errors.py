@@ -110,3 +110,19 @@ def test_server_create_reports_what_failed(stub):
     """No device: SW_ERR_DEVICE; no pinned memory: SW_ERR_HOST_MEMORY."""
     r = subprocess.run([sys.executable, "-c", CREATE, stub, ROOT], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr
+
+
+def test_library_of_an_older_interface_is_refused(tmp_path, monkeypatch):
+    """A library built before sw_cluster_count and ccl_server_count carries a
+    lower version, and the binding says that it has to be rebuilt."""
+    from paper_1105_5804_amd import _lib
+
+    src = tmp_path / "old.c"
+    older = sorted(set(_lib.SIGNATURES) - {"sw_cluster_count", "ccl_server_count", "swccl_abi_version"})
+    src.write_text("int swccl_abi_version(void) { return 7; }\n" + "".join(f"void {n}(void) {{}}\n" for n in older))
+    lib = tmp_path / "libold.so"
+    subprocess.check_call(["gcc", "-shared", "-fPIC", "-o", str(lib), str(src)])
+    monkeypatch.setattr(_lib, "LIB_PATH", str(lib))
+    monkeypatch.setattr(_lib, "_lib", None)
+    with pytest.raises(RuntimeError, match="ABI 7.*rebuild"):
+        _lib.lib()
