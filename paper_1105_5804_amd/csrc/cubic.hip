@@ -191,7 +191,8 @@ template <bool LABEL, bool FOUR, int ROWS>
 __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_eu(8, 8))) void k3_tile(Tile3Args a)
 {
     constexpr int ITER = ROWS, YW = CY / ROWS, NW3 = YW * CZ / SUB, NT3 = 64 * NW3;  // waves along y, and in all
-    __shared__ int P[CSITES];             // union-find parent per slot, as 4 x slot
+    // union-find parent per slot, as 4 x slot (read and written in pairs)
+    __shared__ alignas(8) int P[CSITES];
     __shared__ uint16_t wl[NW3][TL3];     // per-wave list: 4 x slot | direction (0 +y, 1 +z) of a bond, or a label
     __shared__ uint32_t zb[NW3][LPR];     // +z bonds of the wave's last plane: bit 2 it + j of a lane's sites
     __shared__ int nb_s;
@@ -794,7 +795,7 @@ __global__ __launch_bounds__(NT3) void k3_flatten(Flat3Args a)
 {
     constexpr uint32_t NCODE = CSITES + CAP;
     constexpr bool LIST = !LABEL && !FOUR;
-    __shared__ uint8_t ST[LABEL ? 1 : NCODE];     // new state per code
+    __shared__ alignas(4) uint8_t ST[LABEL ? 1 : NCODE];  // new state per code (written in pairs)
     __shared__ int32_t Rb[CAP];                   // canonical label per id (labels only)
     __shared__ uint16_t roots[LIST ? NW3 : 1][LIST ? 128 * ITER : 1];  // interior root slots of each wave's rows
     __shared__ unsigned ncl_w[NW3];

@@ -260,7 +260,7 @@ __device__ __forceinline__ int wave_max_below(int v)
 template <int MODE, int TH_, int RPW_ = RPW>
 struct TileSmem {
     static constexpr int TH = TH_, TSITES = TW * TH, NWAVE = TH / RPW_;
-    int P[TSITES + 4];                 // union-find parent per site slot, as 4 x slot; P[TSITES]: background
+    alignas(8) int P[TSITES + 4];      // union-find parent per site slot, as 4 x slot; P[TSITES]: background
     uint16_t wl[NWAVE][TLIST];         // per-wave work list (contacts, then linked labels)
     uint32_t xr_w[NWAVE];              // right crossing bonds of each wave's rows (bit r: its row r)
     EO xd_s;                           // bottom crossing bonds
@@ -1554,8 +1554,8 @@ struct SmallSmem {
     // off first (workgroups of 16 waves have a CU to themselves; the others
     // share its LDS).
     static constexpr int TL = NT_ >= 1024 ? 448 : 132;
-    int P[SITES];           // union-find parent per site, as 4 x site
-    uint8_t S[SITES + 4];   // states 0..q-1
+    alignas(8) int P[SITES];          // union-find parent per site, as 4 x site (read and written in pairs)
+    alignas(4) uint8_t S[SITES + 4];  // states 0..q-1 (in pairs too)
     uint32_t red[NT_ / 64][12];
     uint16_t wl[NT_ / 64][TL];
 };
@@ -1588,6 +1588,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, SmallSmem<NT_, SI
     constexpr int MAXM = (SITES / 128 + NWAVE - 1) / NWAVE;  // chunks per wave
     constexpr int U = MAXM <= 4 ? MAXM : 1;  // chunks worked at once (more would not fit the registers)
     constexpr int TL = SmallSmem<NT_, SITES>::TL;
+    static_assert(alignof(SmallSmem<NT_, SITES>) >= alignof(int2), "entries are read in pairs");
     static_assert(SITES % 128 == 0 && MAXM <= 8 && SITES <= 1 << 13, "four bits a chunk, 13-bit sites");
     int *P = sm.P;
     uint8_t *S = sm.S;
