@@ -197,6 +197,8 @@ __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_
     __shared__ uint32_t zb[NW3][LPR];     // +z bonds of the wave's last plane: bit 2 it + j of a lane's sites
     __shared__ int nb_s;
     __shared__ unsigned act_w[NW3];
+    static_assert(sizeof(P) + sizeof(wl) + sizeof(zb) + sizeof(act_w) + sizeof(nb_s) <= 160 * 1024 / 32 * NW3,
+                  "8 waves per SIMD");
     const Geo3 g = a.g;
     const TileOf T = tile_of(g, xcd_remap(blockIdx.x, g.ntiles));
     const int lane = threadIdx.x & 63, w = wave_id();
@@ -219,13 +221,13 @@ __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_
         int i = lane, u = 0, v = 0;
         auto next = [&]() {
             const int e = mylist[i], c = e & ~3;
-            u = lds_ld(lds_entry<true>(P, c));
-            v = lds_ld(lds_entry<true>(P, c + ((e & 1) ? 4 * PLANE : 4 * CX)));
+            u = lds_ld(lds_entry(P, c));
+            v = lds_ld(lds_entry(P, c + ((e & 1) ? 4 * PLANE : 4 * CX)));
         };
         if (i < n) next();
         while (i < n) {
             int done;
-            unite_step<true, true>(P, u, v, done);
+            unite_step(P, u, v, done);
             if (done) {
                 i += 64;
                 if (i < n) next();
@@ -388,19 +390,19 @@ __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_
         const int own = own_first + it * 4 * CX, row4 = own - x4;
         int n0 = row4 + (e_start ? x4 : below4);
         int n1 = o_start ? own + 4 : n0;
-        *reinterpret_cast<int2 *>(lds_entry<true>(P, own)) = make_int2(n0, n1);
+        *reinterpret_cast<int2 *>(lds_entry(P, own)) = make_int2(n0, n1);
         if (it > 0) {
             // every +y bond offers its site's label to the next row's run
             // (one wave's LDS operations run in order; whichever offer lands
             // last stands); a bond whose label lost needs a union
             const int up0 = lab0[it > 0 ? it - 1 : 0], up1 = lab1[it > 0 ? it - 1 : 0];
             wave_lds_fence();
-            if (lane_bit(prevY.e, lane)) lds_st(lds_entry<true>(P, n0), up0);
-            if (lane_bit(prevY.o, lane)) lds_st(lds_entry<true>(P, n1), up1);
+            if (lane_bit(prevY.e, lane)) lds_st(lds_entry(P, n0), up0);
+            if (lane_bit(prevY.o, lane)) lds_st(lds_entry(P, n1), up1);
             wave_lds_fence();
-            n0 = lds_ld(lds_entry<true>(P, n0));
-            n1 = lds_ld(lds_entry<true>(P, n1));
-            *reinterpret_cast<int2 *>(lds_entry<true>(P, own)) = make_int2(n0, n1);
+            n0 = lds_ld(lds_entry(P, n0));
+            n1 = lds_ld(lds_entry(P, n1));
+            *reinterpret_cast<int2 *>(lds_entry(P, own)) = make_int2(n0, n1);
             append(EO{lanes_ne(static_cast<uint32_t>(n0), static_cast<uint32_t>(up0)) & prevY.e,
                       lanes_ne(static_cast<uint32_t>(n1), static_cast<uint32_t>(up1)) & prevY.o},
                    own - 4 * CX);
@@ -415,8 +417,8 @@ __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_
             wave_lds_fence();
             int got0 = -1, got1 = -1, up0 = 0, up1 = 0;
             if (sub < SUB - 1) {
-                up0 = lds_ld(lds_entry<true>(P, own + 4 * PLANE));
-                up1 = lds_ld(lds_entry<true>(P, own + 4 * PLANE + 4));
+                up0 = lds_ld(lds_entry(P, own + 4 * PLANE));
+                up1 = lds_ld(lds_entry(P, own + 4 * PLANE + 4));
             }
             if (lane_bit(Z.e, lane) && up0 >= next_plane4) got0 = link_root(P, up0, n0);
             if (lane_bit(Z.o, lane) && up1 >= next_plane4) got1 = link_root(P, up1, n1);
@@ -434,7 +436,7 @@ __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_
     auto link_across = [&](EO m, int own, int up4, int n0, int n1, int dir) {
         // the sites at `own` with labels n0, n1 and bonds m to the sites
         // `up4` bytes on; labels there below their first slot are left to the list
-        const int q0 = lds_ld(lds_entry<true>(P, own + up4)), q1 = lds_ld(lds_entry<true>(P, own + up4 + 4));
+        const int q0 = lds_ld(lds_entry(P, own + up4)), q1 = lds_ld(lds_entry(P, own + up4 + 4));
         const int first = dir == 0 ? own + up4 - x4 : (own + up4) & ~(4 * PLANE - 1);
         int got0 = -1, got1 = -1;
         if (lane_bit(m.e, lane) && q0 >= first) got0 = link_root(P, q0, n0);
@@ -457,7 +459,7 @@ __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_
             const EO m = EO{lanes_ne(z & 1u, 0u), lanes_ne(z & 2u, 0u)};
             if ((m.e | m.o) == 0ull) continue;
             const int own = 4 * (lz_last * PLANE + (ly0 + it) * CX) + x4;
-            const int n0 = lds_ld(lds_entry<true>(P, own)), n1 = lds_ld(lds_entry<true>(P, own + 4));
+            const int n0 = lds_ld(lds_entry(P, own)), n1 = lds_ld(lds_entry(P, own + 4));
             link_across(m, own, 4 * PLANE, n0, n1, 1);
         }
     }
@@ -470,10 +472,10 @@ __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_
         if (slot < 0) continue;
         const int r4 = lroot(P, 4 * slot);
         int expect = r4;
-        if (__hip_atomic_compare_exchange_strong(lds_entry<true>(P, r4), &expect, CLAIMING, __ATOMIC_RELAXED,
+        if (__hip_atomic_compare_exchange_strong(lds_entry(P, r4), &expect, CLAIMING, __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
             const int k = atomicAdd(&nb_s, 1);
-            lds_st(lds_entry<true>(P, r4), final_entry(static_cast<uint32_t>(CSITES + k)));
+            lds_st(lds_entry(P, r4), final_entry(static_cast<uint32_t>(CSITES + k)));
             const int id = T.tile * CAP + k;
             a.gkey[id] = site_of(g, T, r4 >> 2);
             a.gparent[id] = id;
@@ -489,11 +491,11 @@ __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_
         int i = lane, s0 = 0, x = 0;
         if (i < n) s0 = x = mylist[i];
         while (i < n) {
-            const int p = lds_ld(lds_entry<true>(P, x));
+            const int p = lds_ld(lds_entry(P, x));
             if (p >= 0 && p != x) {
                 x = p;
             } else {
-                lds_st(lds_entry<true>(P, s0), p | static_cast<int>(0x80000000u));
+                lds_st(lds_entry(P, s0), p | static_cast<int>(0x80000000u));
                 i += 64;
                 if (i < n) s0 = x = mylist[i];
             }
@@ -511,7 +513,7 @@ __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_
         // a label site whose entry is an offset below its own (a final entry
         // is negative, above every offset as an unsigned number)
         const uint32_t own = static_cast<uint32_t>(own_first + it * 4 * CX);
-        const int2 p = *reinterpret_cast<const int2 *>(lds_entry<true>(P, static_cast<int>(own)));
+        const int2 p = *reinterpret_cast<const int2 *>(lds_entry(P, static_cast<int>(own)));
         const EO linked = EO{lanes_eq(static_cast<uint32_t>(lab0[it]), own) & lanes_lt(static_cast<uint32_t>(p.x), own),
                              lanes_eq(static_cast<uint32_t>(lab1[it]), own + 4) &
                                  lanes_lt(static_cast<uint32_t>(p.y), own + 4)};
@@ -531,8 +533,8 @@ __global__ __launch_bounds__(NT3 * ITER / ROWS) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int it = 0; it < ITER; ++it) {
             if (it >= nr) break;
-            const uint32_t c0 = entry_code(lds_ld(lds_entry<true>(P, lab0[it])));
-            const uint32_t c1 = entry_code(lds_ld(lds_entry<true>(P, lab1[it])));
+            const uint32_t c0 = entry_code(lds_ld(lds_entry(P, lab0[it])));
+            const uint32_t c1 = entry_code(lds_ld(lds_entry(P, lab1[it])));
             uint32_t c = c0 | (c1 << 16);
             if (ly0 + it == T.th - 1)
                 c |= (lane_bit(prevY.e, lane) ? 0x8000u : 0u) | (lane_bit(prevY.o, lane) ? 0x80000000u : 0u);
@@ -927,8 +929,10 @@ constexpr size_t ALIGN3 = 256;
 // Up to this many tiles the tile kernel takes 16 waves a tile, four steps each,
 // else 8 of eight: a wave's steps follow each other, and there are waves to spare.
 // Critical Ising sweep, 8 -> 16 waves: 100 x 75 x 61 (80 tiles) 51.3 -> 45.8 us,
-// 101 x 75 x 61 59.0 -> 51.5, 160^3 (500) 71.2 -> 67.4; 200 x 210 x 200 (1274) takes
-// 123 with 8.
+// 101 x 75 x 61 59.0 -> 51.5, 160^3 (500) 71.2 -> 67.4; 192 x 192 x 176 (792) 96.5 ->
+// 97.7, 200 x 210 x 200 (1274) 122.8 -> 122.7, 256 x 256 x 192 (1536) 133 -> 137, 256^3
+// 159 -> 166, and in the ordered phase (q = 3, K = 0.6) 117 -> 119, 140 -> 144, 162 ->
+// 167, 193 -> 203.
 constexpr int TILE3_SMALL = 512;
 // Up to this many tiles the merge takes 1024 threads a tile, else 256.  Critical
 // Ising sweep, 256 -> 1024: 100 x 75 x 61 (80 tiles) 55.5 -> 51.6 us, 160^3 (500)
@@ -1123,7 +1127,6 @@ sw_status ccl3_label(const uint8_t *bonds, int32_t Lx, int32_t Ly, int32_t Lz, i
     fa.gparent = ta.gparent;
     fa.nb = ta.nb;
     fa.tile_ncl = at3<int32_t>(workspace, L.tile_ncl);
-    const dim3 tiles(static_cast<unsigned>(L.g.ntiles));
     launch_tile3<true>(ta, s);
     launch_merge3(ma, s);
     launch_resolve3(ra, s);
@@ -1189,7 +1192,6 @@ sw_status sw3_sweep(const sw3_params *p, uint8_t *spins, uint32_t t0, int32_t n,
     ra.gparent = ta.gparent;
     ra.nb = ta.nb;
 
-    const dim3 tiles(static_cast<unsigned>(L.g.ntiles));
     ObsArgs oa{};
     oa.spins = spins;
     oa.Lx = static_cast<uint32_t>(L.g.Lx);

@@ -256,7 +256,10 @@ __device__ __forceinline__ int wave_max_below(int v)
     return out;
 }
 
-// LDS of the tile phase: under 40 KB per 64 rows.
+// LDS of the tile phase, a 128 x 64 tile: 39 KB with eight rows a wave (eight
+// lists), 45 KB with four (sixteen).  A CU holds 32 waves of these kernels (8 a
+// SIMD), which share its 160 KB: LDS_PER_WAVE each.
+constexpr size_t LDS_PER_WAVE = 160 * 1024 / 32;
 template <int MODE, int TH_, int RPW_ = RPW>
 struct TileSmem {
     static constexpr int TH = TH_, TSITES = TW * TH, NWAVE = TH / RPW_;
@@ -267,6 +270,8 @@ struct TileSmem {
     int nb_s;
     int act_w[NWAVE];
 };
+template <int MODE, int TH_, int RPW_>
+constexpr bool tile_fits = sizeof(TileSmem<MODE, TH_, RPW_>) <= LDS_PER_WAVE * (TH_ / RPW_);
 
 // A batched launch's tile: take the lattice's shape, buffers and keys from
 // its descriptor; lt is the tile's index inside its lattice.
@@ -340,18 +345,18 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         int i = lane, a = 0, b = 0;
         if (i < n) {
             const int c = mylist[i];  // byte offset of the upper site
-            a = lds_ld(lds_entry<true>(P, c));
-            b = lds_ld(lds_entry<true>(P, c + 4 * TW));
+            a = lds_ld(lds_entry(P, c));
+            b = lds_ld(lds_entry(P, c + 4 * TW));
         }
         while (i < n) {
             int done;
-            unite_step<true, true>(P, a, b, done);
+            unite_step(P, a, b, done);
             if (done) {
                 i += 64;
                 if (i < n) {
                     const int c = mylist[i];
-                    a = lds_ld(lds_entry<true>(P, c));
-                    b = lds_ld(lds_entry<true>(P, c + 4 * TW));
+                    a = lds_ld(lds_entry(P, c));
+                    b = lds_ld(lds_entry(P, c + 4 * TW));
                 }
             }
         }
@@ -545,11 +550,11 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
             // lands last stands); a contact whose label lost needs a union
             const int up0 = lab0[r > 0 ? r - 1 : 0], up1 = lab1[r > 0 ? r - 1 : 0];
             wave_lds_fence();
-            if (lane_bit(prevD.e, lane)) lds_st(lds_entry<true>(P, n0), up0);
-            if (lane_bit(prevD.o, lane)) lds_st(lds_entry<true>(P, n1), up1);
+            if (lane_bit(prevD.e, lane)) lds_st(lds_entry(P, n0), up0);
+            if (lane_bit(prevD.o, lane)) lds_st(lds_entry(P, n1), up1);
             wave_lds_fence();
             // (the background entry reads as itself: background keeps BG4)
-            const int q0 = lds_ld(lds_entry<true>(P, n0)), q1 = lds_ld(lds_entry<true>(P, n1));
+            const int q0 = lds_ld(lds_entry(P, n0)), q1 = lds_ld(lds_entry(P, n1));
             n0 = MODE == M_SITES && n0 == BG4 ? BG4 : q0;
             n1 = MODE == M_SITES && n1 == BG4 ? BG4 : q1;
             *reinterpret_cast<int2 *>(&P[base + lx0]) = make_int2(n0, n1);
@@ -622,11 +627,11 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         int i = lane, s0 = 0, x = 0;
         if (i < n) s0 = x = mylist[i];
         while (i < n) {
-            const int p = lds_ld(lds_entry<true>(P, x));
+            const int p = lds_ld(lds_entry(P, x));
             if (p >= 0 && p != x) {
                 x = p;
             } else {
-                lds_st(lds_entry<true>(P, s0), p | static_cast<int>(0x80000000u));
+                lds_st(lds_entry(P, s0), p | static_cast<int>(0x80000000u));
                 i += 64;
                 if (i < n) s0 = x = mylist[i];
             }
@@ -646,10 +651,10 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         const int root4 = lroot(P, 4 * slot), root = root4 >> 2;
         int expect = root4;
         // (background ends at its own entry, which no claim matches)
-        if (__hip_atomic_compare_exchange_strong(lds_entry<true>(P, root4), &expect, CLAIMING, __ATOMIC_RELAXED,
+        if (__hip_atomic_compare_exchange_strong(lds_entry(P, root4), &expect, CLAIMING, __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
             const int k = atomicAdd(&nb_s, 1);
-            lds_st(lds_entry<true>(P, root4), final_entry(static_cast<uint32_t>(TSITES + k)));
+            lds_st(lds_entry(P, root4), final_entry(static_cast<uint32_t>(TSITES + k)));
             const int id = tile * CAP + k;
             gkey[id] = (gy0 + (root >> 7)) * W + gx0 + (root & (TW - 1));
             gparent[id] = id;
@@ -701,8 +706,8 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         if (r >= nr) break;
-        const uint32_t code0 = entry_code(lds_ld(lds_entry<true>(P, lab0[r])));
-        const uint32_t code1 = entry_code(lds_ld(lds_entry<true>(P, lab1[r])));
+        const uint32_t code0 = entry_code(lds_ld(lds_entry(P, lab0[r])));
+        const uint32_t code1 = entry_code(lds_ld(lds_entry(P, lab1[r])));
         codes32[r * (TW / 2)] = code0 | (code1 << 16);
     }
     uint16_t *edg = edges + static_cast<int64_t>(tile) * EDGE;
@@ -711,7 +716,7 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
         uint16_t eid = ID_NONE;
         if (slot >= 0) {
             int e = P[slot];  // a claimed root or coded label, or the site's label
-            if (e >= 0) e = *lds_entry<true>(P, e);
+            if (e >= 0) e = *lds_entry(P, e);
             eid = static_cast<uint16_t>(entry_code(e) - TSITES);  // a boundary id; background ends up past CAP
         }
         edg[t] = eid;
@@ -734,16 +739,17 @@ __device__ __forceinline__ void tile_body(TileArgs a, const int tile, const int 
     }
 }
 
-// 8 waves per SIMD (four 128 x 64 workgroups per CU): the LDS use stays
-// under 40 KB per 64 rows and the registers are held to what 8 waves allow
-// (some scalar registers spill to vector lanes; the extra latency hiding is
-// worth more).
+// 8 waves per SIMD (four 128 x 64 workgroups of eight waves per CU, or two of
+// sixteen): the LDS leaves room for them and the registers are held to what 8
+// waves allow (some scalar registers spill to vector lanes; the extra latency
+// hiding is worth more).
 // RPW_ = RPW_SMALL: twice the waves with half the rows each, for lattices of few
 // tiles (see the launch).
 constexpr int RPW_SMALL = 4;
 template <int MODE, bool EVENW, bool BATCH, int TH_, int RPW_ = RPW>
 __global__ __launch_bounds__(64 * TH_ / RPW_) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_tile(TileArgs a)
 {
+    static_assert(tile_fits<MODE, TH_, RPW_>, "8 waves per SIMD");
     __shared__ TileSmem<MODE, TH_, RPW_> sm;
     int tile, lt;  // tile in the arrays, tile inside its lattice
     if constexpr (BATCH) {
@@ -1687,7 +1693,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, SmallSmem<NT_, SI
         if (i < n) next();
         while (i < n) {
             int done;
-            unite_step<true, true>(P, u, v, done);
+            unite_step(P, u, v, done);
             if (done) {
                 i += 64;
                 if (i < n) next();
@@ -1801,7 +1807,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, SmallSmem<NT_, SI
                 more = false;
 #pragma unroll
                 for (int m = 0; m < U; ++m) {
-                    const int p0 = lds_ld(lds_entry<true>(P, x0[m])), p1 = lds_ld(lds_entry<true>(P, x1[m]));
+                    const int p0 = lds_ld(lds_entry(P, x0[m])), p1 = lds_ld(lds_entry(P, x1[m]));
                     more |= (p0 != x0[m]) | (p1 != x1[m]);
                     x0[m] = p0;
                     x1[m] = p1;
@@ -1939,6 +1945,7 @@ __device__ __forceinline__ const ReqDesc &req_of(const ReqBatch &rb, int t, int 
 template <int MODE, int TH_, int RPW_>
 __global__ __launch_bounds__(64 * TH_ / RPW_) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_tile_reqs(ReqBatch rb)
 {
+    static_assert(tile_fits<MODE, TH_, RPW_>, "8 waves per SIMD");
     __shared__ TileSmem<MODE, TH_, RPW_> sm;
     int lt;
     const ReqDesc &R = req_of(rb, xcd_remap(blockIdx.x, rb.ntiles), lt);
@@ -2120,6 +2127,7 @@ __global__ __launch_bounds__(Tile<TH_>::NT) __attribute__((amdgpu_waves_per_eu(8
         SmallSmem<NT, SMALL> small;
     } sm;
     __shared__ unsigned long long ticket_s;
+    static_assert(sizeof(sm) + sizeof(ticket_s) <= LDS_PER_WAVE * NWAVE, "8 waves per SIMD");
     const uint32_t t = *a.t;  // every workgroup reads it before the last one leaves and advances it
     const long long n_items = static_cast<long long>(a.n_small) + 2ll * a.n_tiles + a.n_mgroups;
     const unsigned long long per_launch = static_cast<unsigned long long>(n_items) + gridDim.x;
@@ -2198,7 +2206,6 @@ __global__ __launch_bounds__(Tile<TH_>::NT) __attribute__((amdgpu_waves_per_eu(8
             __syncthreads();  // the LDS is reused by the next item
         }
     }
-    (void)NWAVE;
     if (threadIdx.x == 0) {
         __threadfence();
         const unsigned long long left = __hip_atomic_fetch_add(a.exit_ctr, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1;

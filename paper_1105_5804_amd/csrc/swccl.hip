@@ -260,7 +260,11 @@ MergeArgs merge_args(const Layout &L, void *ws)
 // with half the rows each: the chip has waves to spare, and the rows of a wave
 // follow each other.  A q = 3 sweep, 8 -> 4 rows a wave: 512 x 500 (32 tiles)
 // 26.9 -> 24.4 us, 1001 x 2001 (256) 32.8 -> 29.8, 2048^2 (512) 35.4 -> 34.4 and at
-// 1.4 beta_c 38.2 -> 38.4, 4096 x 2048 (1024) 49.7 -> 51.8.
+// 1.4 beta_c 38.2 -> 38.4, 4096 x 2048 (1024) 49.7 -> 51.8.  Batched sweeps keep eight
+// rows at every size: with four (here and in the flatten) batches of few tiles
+// would gain as single lattices do (4 of 512^2, 128 tiles, 33.3 -> 30.4 us; 64 of
+// 64^2 26.1 -> 24.5; 16 of 512^2, 512 tiles, 40.0 -> 39.2), the larger ones lose (64 of
+// 257^2, 960 tiles, 54.2 -> 57.4; 16 of 1024^2, 2048, 85.0 -> 95.6).
 constexpr int64_t TILE_SMALL = 256;
 
 // Even W keeps every row start even: one 16-bit load per lane pair.

@@ -89,6 +89,13 @@ __device__ __forceinline__ void lds_st(int *p, int v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// A node's value is the byte offset of its entry (4 x index): directly an LDS
+// address.
+__device__ __forceinline__ int *lds_entry(int *P, int v)
+{
+    return reinterpret_cast<int *>(reinterpret_cast<char *>(P) + v);
+}
+
 // One step of a union of the trees holding a and b, with a straight-line body
 // (nested find/link loops cost more in exec-mask bookkeeping than in LDS
 // traffic).  A step climbs both nodes two levels (parent, then grandparent);
@@ -102,31 +109,20 @@ __device__ __forceinline__ void lds_st(int *p, int v)
 // ancestor (entries only ever decrease), which is a no-op when a or its
 // parent is a root, so every lane issues the atomic and the step needs no
 // branch; the halving keeps the trees shallow for later steps and for the
-// compression that follows the unions.
-// With BYTES the node values are byte offsets of the entries (4 x index), so
-// a value is directly an LDS address.
-template <bool BYTES = false>
-__device__ __forceinline__ int *lds_entry(int *P, int v)
-{
-    return BYTES ? reinterpret_cast<int *>(reinterpret_cast<char *>(P) + v) : &P[v];
-}
-
-template <bool BYTES = false, bool SAME_PARENT = false>
+// compression that follows the unions.  A union also ends when both nodes have
+// the same parent, which already makes one tree: a step before both reach the
+// root, whose entry every finished lane would otherwise hit.
 __device__ __forceinline__ void unite_step(int *P, int &a, int &b, int &done)
 {
-    const int pa = lds_ld(lds_entry<BYTES>(P, a)), pb = lds_ld(lds_entry<BYTES>(P, b));
-    const int ga = lds_ld(lds_entry<BYTES>(P, pa)), gb = lds_ld(lds_entry<BYTES>(P, pb));
+    const int pa = lds_ld(lds_entry(P, a)), pb = lds_ld(lds_entry(P, b));
+    const int ga = lds_ld(lds_entry(P, pa)), gb = lds_ld(lds_entry(P, pb));
     const bool roots = pa == a && pb == b;
     const bool link = roots && a != b;
     const int hi = max(a, b), lo = min(a, b);
-    const int old = __hip_atomic_fetch_min(lds_entry<BYTES>(P, link ? hi : a), link ? lo : ga, __ATOMIC_RELAXED,
+    const int old = __hip_atomic_fetch_min(lds_entry(P, link ? hi : a), link ? lo : ga, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
-    // with SAME_PARENT a common parent already makes one tree: the union ends
-    // a step before both nodes reach the root (whose entry every finished
-    // lane would hit; the label unions of the tile kernel gain from it,
-    // the site unions of the small-lattice kernel do not)
     // bitwise, not short-circuit: the flags stay lane masks (no selects)
-    done = static_cast<int>((SAME_PARENT && pa == pb) | (roots & (!link | (old == hi))));
+    done = static_cast<int>((pa == pb) | (roots & (!link | (old == hi))));
     a = link ? old : ga;
     b = link ? lo : gb;
 }
@@ -136,7 +132,7 @@ __device__ __forceinline__ void unite_step(int *P, int &a, int &b, int &done)
 __device__ __forceinline__ int lroot(int *P, int x)
 {
     for (;;) {
-        const int p = lds_ld(lds_entry<true>(P, x));
+        const int p = lds_ld(lds_entry(P, x));
         if (p == x || p < 0) return x;
         x = p;
     }
@@ -155,7 +151,7 @@ __device__ __forceinline__ uint32_t entry_code(int e) { return (static_cast<uint
 __device__ __forceinline__ int link_root(int *P, int x, int up)
 {
     int expect = x;
-    __hip_atomic_compare_exchange_strong(lds_entry<true>(P, x), &expect, up, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+    __hip_atomic_compare_exchange_strong(lds_entry(P, x), &expect, up, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_WORKGROUP);
     return expect;
 }
@@ -211,7 +207,12 @@ __device__ __forceinline__ void gfind2_from(int *G, int &a, int &b, int pa, int 
 // 0.6), cached -> fresh: 160^3 111 -> 84 us, 256^3 267 -> 193, 512^3 1055 ->
 // 1022, at the critical point within 1%; square q = 3 lattice 8192^2 at 1.4
 // beta_c 260 -> 241.  Square lattices of more than MERGE_FRESH_TILES tiles keep
-// to the caches (16384^2 bond percolation 925 cached, 934 fresh).
+// to the caches: at 16384^2 (32768 tiles) a sweep takes 846 cached, 851 fresh at
+// beta_c, 909 and 920 at 1.1 beta_c, 874 and 874 at 1.4, 849 and 846 at 2.0, bond
+// percolation 908 and 913 at p = 0.5, 964 and 983 at 0.55, 966 and 953 at 0.7.
+// The true crossing lies between: at 11520^2 (16200 tiles) fresh walks would take
+// 437 for 436 at beta_c, 490 -> 480 at 1.1, 470 -> 460 at 1.4, and percolation at
+// 0.55 556 -> 509.
 constexpr int MERGE_FRESH_TILES = 8192;
 __device__ __forceinline__ void gfind2_again(int *G, int &a, int &b, bool fresh)
 {
